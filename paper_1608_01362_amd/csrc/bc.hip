@@ -36,18 +36,23 @@ __global__ void k_zero_words(uint32_t *__restrict__ w, int32_t n) {
 // per non-zero word; the new-frontier count is reduced in the workgroup and
 // added once. (One global atomic per wave on a handful of words serialises:
 // half a million of them took 1.5-1.9 ms per level at scale 25.)
-constexpr int kBcSpan = 16384;                    // vertices per workgroup
-constexpr int kBcMaskWords = kBcSpan / 32 + 2;    // segments of a span, in 32-bit words, for N >= 1
+// The span shrinks with the graph so that about kBcWorkgroups workgroups
+// cover it: with 16,384 vertices each, 2 M vertices gave 128 workgroups, half
+// the chip's CUs, each walking 64 dependent steps.
+constexpr int kBcMaxSpan = 16384;                 // vertices per workgroup
+constexpr int kBcMinSpan = 1024;
+constexpr int kBcWorkgroups = 2048;
+constexpr int kBcMaskWords = kBcMaxSpan / 32 + 2; // segments of a span, in 32-bit words, for N >= 1
 
 struct SpanMask {
     int64_t v0, v1;     // the workgroup's vertices [v0, v1)
     int32_t w_lo, w_hi; // global mask words covering their segments
 };
 
-__device__ __forceinline__ SpanMask span_begin(int32_t V, int32_t N, uint32_t *lmask) {
+__device__ __forceinline__ SpanMask span_begin(int32_t V, int32_t N, int32_t span, uint32_t *lmask) {
     SpanMask m;
-    m.v0 = (int64_t)blockIdx.x * kBcSpan;
-    m.v1 = m.v0 + kBcSpan < V ? m.v0 + kBcSpan : V;
+    m.v0 = (int64_t)blockIdx.x * span;
+    m.v1 = m.v0 + span < V ? m.v0 + span : V;
     m.w_lo = (int32_t)(m.v0 / N) >> 5;
     m.w_hi = (int32_t)((m.v1 - 1) / N) >> 5;
     for (int i = threadIdx.x; i <= m.w_hi - m.w_lo; i += kBcThreads) lmask[i] = 0u;
@@ -79,13 +84,13 @@ __device__ __forceinline__ void span_flush(const SpanMask &m, const uint32_t *lm
 }
 
 // vals[u] = sigma[u] for the frontier (depth d), else 0; frontier segments marked.
-__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_values(int32_t V, int32_t N, int32_t d,
+__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
                                                               const int32_t *__restrict__ depth,
                                                               const float *__restrict__ sigma,
                                                               float *__restrict__ vals, uint32_t *__restrict__ mask,
                                                               int32_t *__restrict__ count) {
     __shared__ uint32_t lmask[kBcMaskWords];
-    const SpanMask m = span_begin(V, N, lmask);
+    const SpanMask m = span_begin(V, N, span, lmask);
     if (blockIdx.x == 0 && threadIdx.x == 0) *count = 0;  // next frontier size, counted by k_bc_fwd_update
     for (int64_t v0 = m.v0; v0 < m.v1; v0 += kBcThreads) {
         const int64_t v = v0 + threadIdx.x;
@@ -97,13 +102,13 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_fwd_values(int32_t V, int32_t
 }
 
 // Unvisited vertices reached at this level: depth d + 1, sigma = the sum.
-__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_update(int32_t V, int32_t d, const float *__restrict__ sums,
+__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_update(int32_t V, int32_t span, int32_t d, const float *__restrict__ sums,
                                                               int32_t *__restrict__ depth,
                                                               float *__restrict__ sigma,
                                                               int32_t *__restrict__ count) {
     __shared__ int32_t red[kBcThreads / kWave];
-    const int64_t v0 = (int64_t)blockIdx.x * kBcSpan;
-    const int64_t v1 = v0 + kBcSpan < V ? v0 + kBcSpan : V;
+    const int64_t v0 = (int64_t)blockIdx.x * span;
+    const int64_t v1 = v0 + span < V ? v0 + span : V;
     int32_t reached = 0;
     for (int64_t v = v0 + threadIdx.x; v < v1; v += kBcThreads) {
         if (depth[v] < 0) {
@@ -127,13 +132,13 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_fwd_update(int32_t V, int32_t
 
 // vals[w] = (1 + delta[w]) / sigma[w] for the vertices at depth d + 1, else 0;
 // their segments (in the reverse graph's segmentation) marked.
-__global__ __launch_bounds__(kBcThreads) void k_bc_bwd_values(int32_t V, int32_t N, int32_t d,
+__global__ __launch_bounds__(kBcThreads) void k_bc_bwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
                                                               const int32_t *__restrict__ depth,
                                                               const float *__restrict__ sigma,
                                                               const float *__restrict__ delta,
                                                               float *__restrict__ vals, uint32_t *__restrict__ mask) {
     __shared__ uint32_t lmask[kBcMaskWords];
-    const SpanMask m = span_begin(V, N, lmask);
+    const SpanMask m = span_begin(V, N, span, lmask);
     for (int64_t v0 = m.v0; v0 < m.v1; v0 += kBcThreads) {
         const int64_t v = v0 + threadIdx.x;
         const bool in = v < m.v1 && depth[v] == d + 1;
@@ -157,7 +162,12 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_bwd_update(int32_t V, int32_t
     if (v != source) bc[v] += dl;
 }
 
-static unsigned spans_for(int64_t V) { return (unsigned)ceil_div(V > 0 ? V : 1, kBcSpan); }
+// Vertices per workgroup: whole rounds of the workgroup's threads.
+static int32_t span_for(int32_t V) {
+    const int64_t s = ceil_div(ceil_div(V, kBcWorkgroups), kBcThreads) * kBcThreads;
+    return (int32_t)(s < kBcMinSpan ? kBcMinSpan : (s > kBcMaxSpan ? kBcMaxSpan : s));
+}
+static unsigned spans_for(int32_t V) { return (unsigned)ceil_div(V > 0 ? V : 1, span_for(V)); }
 
 static unsigned blocks_for(int64_t n) { return (unsigned)ceil_div(n > 0 ? n : 1, kBcThreads); }
 
@@ -174,12 +184,12 @@ cagra_status launch_bc_forward(const cagra_segments *seg, int32_t d, int32_t *de
     const int32_t V = seg->V, words = (int32_t)bc_mask_words(seg);
     k_zero_words<<<(unsigned)ceil_div(words, 256), 256, 0, st>>>(mask, words);
     CAGRA_LAUNCH_CHECK();
-    k_bc_fwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg->N, d, depth, sigma, vals, mask, count);
+    k_bc_fwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg->N, span_for(V), d, depth, sigma, vals, mask, count);
     CAGRA_LAUNCH_CHECK();
     cagra_status s;
     if ((s = launch_gather_active(seg, CAGRA_SUM_F32, CAGRA_F32, vals, partial, mask, st)) != CAGRA_OK) return s;
     if ((s = launch_merge_active(seg, CAGRA_SUM_F32, partial, sums, mask, st)) != CAGRA_OK) return s;
-    k_bc_fwd_update<<<spans_for(V), kBcThreads, 0, st>>>(V, d, sums, depth, sigma, count);
+    k_bc_fwd_update<<<spans_for(V), kBcThreads, 0, st>>>(V, span_for(V), d, sums, depth, sigma, count);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -190,7 +200,7 @@ cagra_status launch_bc_backward(const cagra_segments *seg_t, int32_t d, int32_t 
     const int32_t V = seg_t->V, words = (int32_t)bc_mask_words(seg_t);
     k_zero_words<<<(unsigned)ceil_div(words, 256), 256, 0, st>>>(mask, words);
     CAGRA_LAUNCH_CHECK();
-    k_bc_bwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg_t->N, d, depth, sigma, delta, vals, mask);
+    k_bc_bwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg_t->N, span_for(V), d, depth, sigma, delta, vals, mask);
     CAGRA_LAUNCH_CHECK();
     cagra_status s;
     if ((s = launch_gather_active(seg_t, CAGRA_SUM_F32, CAGRA_F32, vals, partial, mask, st)) != CAGRA_OK) return s;

@@ -8,7 +8,7 @@
 //
 // Two schedules:
 //  * k_merge_ordered: the paper's order exactly -- subgraphs in ascending
-//    order, one wave per block, lanes over the entries of one subgraph's range
+//    order, the workgroup's threads over the entries of one subgraph's range
 //    (distinct destinations, so no conflicts). Used by cagra_merge for float
 //    sums (plain or Neumaier-compensated) and int minimum.
 //  * k_merge_pr / k_merge_lp: all 16 waves of the workgroup stream the block's
@@ -35,22 +35,26 @@ size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes) {
 
 // ---------------------------------------------------------------- ordered (paper) merge
 
-// One wave per block, subgraphs strictly in ascending order. The block's range
-// bounds are staged in LDS first (when they fit), and the entries of the next
-// kOrdDepth - 1 non-empty subgraphs (up to kOrdBatch per range) are in flight
-// while the current one is applied, so the wave does not wait on memory once
-// per subgraph.
-// Entries of one subgraph have distinct destinations, so the lanes of a batch
-// never collide; the order across subgraphs is the program order of the wave.
-constexpr int kOrdLoads = 4;                    // entries per lane per batch
-constexpr int kOrdBatch = kOrdLoads * kWave;    // entries of a range loaded ahead
-constexpr int kOrdDepth = 6;                    // ranges in flight (8 loads each)
-
-template <typename T>
-struct OrdBatch {
-    T x[kOrdLoads];
-    int32_t d[kOrdLoads];  // entries past the range hold the range's first entry again
-};
+// A workgroup of W waves per block (or per part of a block), subgraphs strictly
+// in ascending order: the entries of one subgraph's range have distinct
+// destinations, so they are spread over the workgroup's threads, and a barrier
+// separates the subgraphs. The ranges are first listed without the empty and
+// the inactive ones, so that a sparse frontier pays for its own ranges only,
+// and each thread keeps its entries of the next kOrdDepth - 1 ranges in flight.
+//
+// What bounds it is the chain of one LDS update and one barrier per subgraph,
+// so W follows the mean range length (see ordered_waves). Blocks of high
+// in-degree destinations (after clustering the first few hold 30 times the mean
+// entries, and one workgroup per block left the chip waiting for the heaviest)
+// are cut by destination into kOrdParts parts, each a workgroup of its own with
+// its piece of every range found by binary search; the order per destination
+// stays the same. One wave per block before -> now, us, FP32 sum: R-MAT 21 / ef
+// 16 165 -> 23, R-MAT 25 / ef 32 1,698 -> 1,457 (compensated 3,722 -> 2,200),
+// the same graphs clustered 1,977 -> 57 and 41,000 -> 2,970.
+constexpr int kOrdDepth = 8;       // pieces of ranges in flight
+constexpr int kOrdWindow = 2048;   // subgraphs whose ranges are listed at a time
+constexpr int kOrdParts = 8;       // parts of a heavy block
+constexpr int kOrdHeavyWaves = 16;
 
 template <class Op, bool COMP>
 __device__ __forceinline__ void ord_apply(typename Op::T *acc, typename Op::T *cmp, int32_t d,
@@ -67,168 +71,188 @@ __device__ __forceinline__ void ord_apply(typename Op::T *acc, typename Op::T *c
     }
 }
 
-// Applies the entries of one loaded batch (lane entries lo + j * 64 + lane
-// below hi). A range's entries have distinct destinations, so every
-// accumulator of the batch is read before any is written: one LDS round trip
-// per batch instead of one per entry (R-MAT 25 FP32 sum: 1.80 -> 1.70 ms).
-// Entries past the range read the destination of the range's first entry and
-// write nothing.
-template <class Op, bool COMP>
-__device__ __forceinline__ void ord_apply_batch(typename Op::T *acc, typename Op::T *cmp,
-                                                const OrdBatch<typename Op::T> &q, int32_t lo, int32_t hi,
-                                                int lane) {
-    using T = typename Op::T;
-    T a[kOrdLoads], cm[kOrdLoads];
-#pragma unroll
-    for (int j = 0; j < kOrdLoads; ++j) {
-        a[j] = acc[q.d[j]];
-        if (COMP) cm[j] = cmp[q.d[j]];
+// First entry in [lo, hi) whose block offset is at least d (hi if none).
+__device__ __forceinline__ int32_t first_dst(const uint16_t *__restrict__ dlo, int32_t lo, int32_t hi, int32_t d) {
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if ((int32_t)dlo[mid] < d) lo = mid + 1;
+        else hi = mid;
     }
-#pragma unroll
-    for (int j = 0; j < kOrdLoads; ++j) {
-        if (lo + j * kWave + lane >= hi) continue;
-        const T x = q.x[j];
-        if (COMP) {
-            // the Neumaier step of ord_apply on the values read above
-            const float sacc = a[j];
-            const float tsum = sacc + x;
-            if (fabsf(sacc) >= fabsf(x)) cmp[q.d[j]] = cm[j] + ((sacc - tsum) + x);
-            else cmp[q.d[j]] = cm[j] + ((x - tsum) + sacc);
-            acc[q.d[j]] = tsum;
-        } else {
-            acc[q.d[j]] = Op::apply(a[j], x);
-        }
-    }
+    return lo;
 }
 
-template <class Op, bool COMP, bool STAGED>
-__global__ __launch_bounds__(64) void k_merge_ordered(const uint16_t *__restrict__ row_dst_lo,
-                                                      const int32_t *__restrict__ block_ptr,
-                                                      const typename Op::T *__restrict__ partial, int32_t V,
-                                                      int32_t k, int32_t B, int32_t nb,
-                                                      typename Op::T *__restrict__ out,
-                                                      const uint32_t *__restrict__ seg_active) {
+// Lists the non-empty, active ranges of subgraphs [s0, s1) in block b, cut to
+// the block offsets [d0, d1) when PARTS, into lo_s/hi_s in ascending subgraph
+// order; returns their count. tmp: one int per wave. Every thread calls it.
+template <int W, bool PARTS>
+__device__ __forceinline__ int32_t list_ranges(const uint16_t *__restrict__ dlo,
+                                               const int32_t *__restrict__ block_ptr, int b, int32_t k, int32_t s0,
+                                               int32_t s1, int32_t d0, int32_t d1,
+                                               const uint32_t *__restrict__ seg_active, int32_t *lo_s, int32_t *hi_s,
+                                               int32_t *tmp) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t n = 0;
+    for (int32_t sb = s0; sb < s1; sb += W * kWave) {  // uniform
+        const int32_t s = sb + (int32_t)threadIdx.x;
+        int32_t lo = 0, hi = 0;
+        if (s < s1 && (!seg_active || ((seg_active[s >> 5] >> (s & 31)) & 1u))) {
+            lo = block_ptr[(int64_t)b * k + s];
+            hi = block_ptr[(int64_t)(b + 1) * k + s];
+            if (PARTS) {
+                lo = first_dst(dlo, lo, hi, d0);
+                hi = first_dst(dlo, lo, hi, d1);
+            }
+        }
+        const uint64_t m = __ballot(hi > lo);
+        if (lane == 0) tmp[w] = (int32_t)__popcll(m);
+        __syncthreads();
+        int32_t at = n + (int32_t)__popcll(m & lanemask_lt());
+        for (int x = 0; x < W; ++x) {
+            if (x < w) at += tmp[x];
+            n += tmp[x];
+        }
+        if (hi > lo) {
+            lo_s[at] = lo;
+            hi_s[at] = hi;
+        }
+        __syncthreads();
+    }
+    return n;
+}
+
+// HEAVY = false merges the blocks that are one work item (every block when
+// block_items is null), HEAVY = true the split ones, in kOrdParts parts.
+template <class Op, bool COMP, int W, bool HEAVY>
+__global__ __launch_bounds__(W * 64) void k_merge_ordered(const uint16_t *__restrict__ row_dst_lo,
+                                                          const int32_t *__restrict__ block_ptr,
+                                                          const int32_t *__restrict__ block_items,
+                                                          const typename Op::T *__restrict__ partial, int32_t V,
+                                                          int32_t k, int32_t B, int32_t nb,
+                                                          typename Op::T *__restrict__ out,
+                                                          const uint32_t *__restrict__ seg_active) {
     using T = typename Op::T;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    T *acc = reinterpret_cast<T *>(smem);
-    T *cmp = acc + B;  // Neumaier compensation terms (COMP only)
-    int32_t *lo_s = reinterpret_cast<int32_t *>(smem + (size_t)B * sizeof(T) * (COMP ? 2 : 1));
-    int32_t *hi_s = lo_s + k;
-    const int b = xcd_remap(blockIdx.x, nb);
+    __shared__ int32_t tmp[W];
+    const int b = HEAVY ? (int)(blockIdx.x / kOrdParts) : xcd_remap(blockIdx.x, nb);
+    if (HEAVY || block_items)
+        if ((block_items[b + 1] - block_items[b] > 1) != HEAVY) return;  // uniform over the workgroup
     const int64_t vb = (int64_t)b * B;
-    int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);
-    const int lane = threadIdx.x;
-    for (int i = lane; i < nv; i += 64) {
+    const int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);
+    const int32_t part = HEAVY ? (int32_t)(blockIdx.x % kOrdParts) : 0, parts = HEAVY ? kOrdParts : 1;
+    const int32_t d0 = (int32_t)((int64_t)nv * part / parts), d1 = (int32_t)((int64_t)nv * (part + 1) / parts);
+    const int32_t window = k < kOrdWindow ? k : kOrdWindow;
+    int32_t *lo_s = reinterpret_cast<int32_t *>(smem), *hi_s = lo_s + window;
+    T *acc = reinterpret_cast<T *>(hi_s + window) - d0;  // indexed by block offset in [d0, d1)
+    T *cmp = acc + (HEAVY ? B / kOrdParts + 1 : B);      // Neumaier compensation terms (COMP only)
+    constexpr int NT = W * kWave;
+    const int tid = threadIdx.x;
+    for (int i = d0 + tid; i < d1; i += NT) {
         acc[i] = Op::identity();
         if (COMP) cmp[i] = Op::identity();
     }
-    // range of subgraph s in this block; inactive subgraphs (no rows written) are empty
-    auto range = [&](int32_t s, int32_t &lo, int32_t &hi) {
-        if (STAGED) {
-            lo = lo_s[s];
-            hi = hi_s[s];
-        } else {
-            lo = block_ptr[(int64_t)b * k + s];
-            hi = block_ptr[(int64_t)(b + 1) * k + s];
-            if (seg_active && !((seg_active[s >> 5] >> (s & 31)) & 1u)) hi = lo;
-        }
-    };
-    if (STAGED) {
-        for (int32_t s = lane; s < k; s += 64) {
-            const int32_t lo = block_ptr[(int64_t)b * k + s], hi = block_ptr[(int64_t)(b + 1) * k + s];
-            const bool act = !seg_active || ((seg_active[s >> 5] >> (s & 31)) & 1u);
-            lo_s[s] = lo;
-            hi_s[s] = act ? hi : lo;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    // next subgraph at or after s with entries in this block (k if none); uniform
-    auto next = [&](int32_t s, int32_t &lo, int32_t &hi) {
-        for (; s < k; ++s) {
-            range(s, lo, hi);
-            if (hi > lo) break;
-        }
-        return s;
-    };
-    // Loads only: nothing here uses their values, so none waits; whether an
-    // entry belongs to the range is decided when it is applied.
-    auto issue = [&](int32_t lo, int32_t hi, OrdBatch<T> &q) {
-#pragma unroll
-        for (int j = 0; j < kOrdLoads; ++j) {
-            const int32_t i = lo + j * kWave + lane;
-            const int32_t ii = i < hi ? i : lo;
-            q.x[j] = partial[ii];
-            q.d[j] = (int32_t)row_dst_lo[ii];
-        }
-    };
-    // A ring of kOrdDepth non-empty ranges: the loads of the range kOrdDepth - 1
-    // places ahead are issued before the current one is applied, and ranges
-    // are applied strictly in ascending subgraph order. Every slot issues its
-    // loads (past the last range, of a known entry) so that the waits for one
-    // slot do not cover the slots behind it.
-    int32_t safe_lo = 0, safe_hi = 0;
-    int32_t scan = next(0, safe_lo, safe_hi);  // next subgraph to examine
-    if (scan < k) {  // uniform: the block has entries; safe_lo indexes one of them
-        OrdBatch<T> q[kOrdDepth];
-        int32_t qs[kOrdDepth], qlo[kOrdDepth], qhi[kOrdDepth];
-        auto fetch = [&](OrdBatch<T> &b, int32_t &bs, int32_t &blo, int32_t &bhi) {
-            int32_t l = safe_lo, h = safe_lo;
-            scan = next(scan, l, h);
-            bs = scan;
-            if (scan < k) ++scan;
-            else l = h = safe_lo;
-            blo = l;
-            bhi = h;
-            issue(l, h, b);
+    for (int32_t s0 = 0; s0 < k; s0 += window) {
+        // its barriers also order the accumulators' start values and the
+        // previous window's last updates before what follows
+        const int32_t n = list_ranges<W, HEAVY>(row_dst_lo, block_ptr, b, k, s0, min(s0 + window, k), d0, d1,
+                                                seg_active, lo_s, hi_s, tmp);
+        if (n == 0) continue;  // uniform
+        // A step is a piece of at most NT entries of one range. Loads are
+        // unconditional: threads past the piece read its first entry and steps
+        // past the last one read it again; both are dropped on use.
+        // the offsets stay 16-bit until used: widened, they would be converted
+        // at the loop's end, which waits for every load in flight
+        T x[kOrdDepth];
+        uint16_t d[kOrdDepth];
+        int32_t cnt[kOrdDepth];
+        // lane l of every wave holds range rb + l of the list, so that a step's
+        // bounds cost a lane read instead of an LDS round trip
+        int32_t rb = 0, r = 0;
+        const int lane = tid & 63;
+        int32_t vlo = lo_s[min(lane, n - 1)], vhi = hi_s[min(lane, n - 1)];
+        int32_t lo = __builtin_amdgcn_readfirstlane(vlo), hi = __builtin_amdgcn_readfirstlane(vhi);
+        auto fetch = [&](int slot) {
+            const int32_t c = min(hi - lo, NT);  // 0 past the last piece
+            const int32_t i = c > 0 ? lo + (tid < c ? tid : 0) : lo - 1;
+            cnt[slot] = c;
+            x[slot] = partial[i];
+            d[slot] = row_dst_lo[i];
+            lo += c;
+            if (lo >= hi && r + 1 < n) {  // uniform
+                ++r;
+                if (r - rb == kWave) {
+                    rb = r;
+                    vlo = lo_s[min(rb + lane, n - 1)];
+                    vhi = hi_s[min(rb + lane, n - 1)];
+                }
+                lo = __builtin_amdgcn_readlane(vlo, r - rb);
+                hi = __builtin_amdgcn_readlane(vhi, r - rb);
+            }
         };
 #pragma unroll
-        for (int c = 0; c < kOrdDepth - 1; ++c) fetch(q[c], qs[c], qlo[c], qhi[c]);
+        for (int c = 0; c < kOrdDepth - 1; ++c) fetch(c);
         for (bool more = true; more;) {
 #pragma unroll
             for (int c = 0; c < kOrdDepth; ++c) {
-                constexpr int kLast = kOrdDepth - 1;
-                const int nx = (c + kLast) % kOrdDepth;
-                fetch(q[nx], qs[nx], qlo[nx], qhi[nx]);
-                if (qs[c] >= k) {  // uniform; every later slot is empty too
+                fetch((c + kOrdDepth - 1) % kOrdDepth);
+                if (cnt[c] == 0) {  // uniform; every later step is empty too
                     more = false;
                     break;
                 }
-                ord_apply_batch<Op, COMP>(acc, cmp, q[c], qlo[c], qhi[c], lane);
-                // the rest of a long range, still before the next subgraph
-                for (int32_t i = qlo[c] + kOrdBatch + lane; i < qhi[c]; i += 64)
-                    ord_apply<Op, COMP>(acc, cmp, row_dst_lo[i], partial[i]);
-                __builtin_amdgcn_wave_barrier();
+                // used before the branch, so that the wait for this step's loads is
+                // on both paths and none is left for the loop's start to cover
+                asm volatile("" ::"v"(x[c]), "v"(d[c]));
+                if (tid < cnt[c]) ord_apply<Op, COMP>(acc, cmp, (int32_t)d[c], x[c]);
+                __syncthreads();  // the next subgraph's entries may update the same destinations
             }
         }
     }
-    __builtin_amdgcn_wave_barrier();
-    for (int i = lane; i < nv; i += 64) out[vb + i] = COMP ? (T)(acc[i] + cmp[i]) : acc[i];
+    __syncthreads();
+    for (int i = d0 + tid; i < d1; i += NT) out[vb + i] = COMP ? (T)(acc[i] + cmp[i]) : acc[i];
 }
 
-// Staged range bounds fit next to the accumulators.
-static bool ordered_ranges_staged(int32_t B, int32_t k, bool comp) {
-    return (size_t)B * 4 * (comp ? 2 : 1) + (size_t)k * 8 <= CAGRA_LDS_BYTES - 1024;
+static size_t ordered_lds(int32_t B, int32_t k, bool comp, bool heavy) {
+    const size_t window = (size_t)(k < kOrdWindow ? k : kOrdWindow);
+    const size_t n = heavy ? (size_t)(B / kOrdParts + 1) : (size_t)B;
+    return window * 2 * sizeof(int32_t) + n * 4 * (comp ? 2 : 1);
 }
 
-template <class Op, bool COMP, bool STAGED>
-static cagra_status launch_ordered_t(const cagra_segments *seg, const void *partial, void *out,
+template <class Op, bool COMP, int W, bool HEAVY>
+static cagra_status launch_ordered_w(const cagra_segments *seg, const void *partial, void *out,
                                      const uint32_t *seg_active, hipStream_t st) {
     using T = typename Op::T;
-    auto kern = k_merge_ordered<Op, COMP, STAGED>;
-    size_t lds = (size_t)seg->B * sizeof(T) * (COMP ? 2 : 1) + (STAGED ? (size_t)seg->k * 8 : 0);
+    auto kern = k_merge_ordered<Op, COMP, W, HEAVY>;
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
-    kern<<<seg->nb, 64, lds, st>>>(seg->row_dst_lo, seg->block_ptr, (const T *)partial, seg->V, seg->k, seg->B,
-                                   seg->nb, (T *)out, seg_active);
+    // no block is split when the item bound equals nb: the item table is not read then
+    const int32_t *items = seg->max_items > seg->nb ? seg->block_items : nullptr;
+    kern<<<(unsigned)seg->nb * (HEAVY ? kOrdParts : 1), W * 64, ordered_lds(seg->B, seg->k, COMP, HEAVY), st>>>(
+        seg->row_dst_lo, seg->block_ptr, items, (const T *)partial, seg->V, seg->k, seg->B, seg->nb, (T *)out,
+        seg_active);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
+}
+
+// Waves per block from the mean range length Q / (k nb): a range should about
+// fill the threads; more waves only make the barrier dearer. FP32 sum, us with
+// 2 / 4 / 8 / 16 waves: mean 40 (V = 2 M, N = 4,096) 109 / 126 / 172 / 475,
+// mean 137 (R-MAT 25) 2,125 / 1,457 / 1,503 / 4,055, mean 246 (R-MAT 23)
+// 153 / 120 / 104 / 269, mean 670 (R-MAT 21) 67 / 41 / 33 / 23.
+static int ordered_waves(const cagra_segments *seg) {
+    const double mean = (double)seg->Q / ((double)seg->k * (double)seg->nb);
+    return mean <= 60.0 ? 2 : mean <= 160.0 ? 4 : mean <= 384.0 ? 8 : 16;
 }
 
 template <class Op, bool COMP>
 static cagra_status launch_ordered(const cagra_segments *seg, const void *partial, void *out,
                                    const uint32_t *seg_active, hipStream_t st) {
-    if (ordered_ranges_staged(seg->B, seg->k, COMP))
-        return launch_ordered_t<Op, COMP, true>(seg, partial, out, seg_active, st);
-    return launch_ordered_t<Op, COMP, false>(seg, partial, out, seg_active, st);
+    cagra_status s;
+    switch (ordered_waves(seg)) {
+        case 2: s = launch_ordered_w<Op, COMP, 2, false>(seg, partial, out, seg_active, st); break;
+        case 4: s = launch_ordered_w<Op, COMP, 4, false>(seg, partial, out, seg_active, st); break;
+        case 8: s = launch_ordered_w<Op, COMP, 8, false>(seg, partial, out, seg_active, st); break;
+        default: s = launch_ordered_w<Op, COMP, 16, false>(seg, partial, out, seg_active, st);
+    }
+    if (s != CAGRA_OK || seg->max_items == seg->nb) return s;
+    return launch_ordered_w<Op, COMP, kOrdHeavyWaves, true>(seg, partial, out, seg_active, st);
 }
 
 size_t merge_ordered_lds_bytes(int32_t B, int32_t op) {
