@@ -43,6 +43,23 @@ __device__ __forceinline__ float gelu_grad(float x) {
            x * __builtin_amdgcn_exp2f(-0.5f * x * x * 1.4426950408889634f) * 0.39894228040143268f;
 }
 
+// gelu(x) and gelu_grad(x) together: the exponential of the erf formula at
+// x / sqrt(2) is the exp(-x^2 / 2) of the density.
+__device__ __forceinline__ void gelu_both(float x, float &g, float &dg) {
+    const float ax = fabsf(x) * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
+    float p = fmaf(1.061405429f, t, -1.453152027f);
+    p = fmaf(p, t, 1.421413741f);
+    p = fmaf(p, t, -0.284496736f);
+    p = fmaf(p, t, 0.254829592f);
+    p *= t;
+    const float e = __builtin_amdgcn_exp2f(-ax * ax * 1.4426950408889634f);
+    const float phi = 0.5f * (1.0f + copysignf(fmaf(-p, e, 1.0f), x));
+    g = x * phi;
+    dg = fmaf(x * e, 0.39894228040143268f, phi);
+    asm volatile("" : "+v"(dg));  // finished here: moved to its use, it would hold two registers
+}
+
 // ------------------------------------------------------------------ features
 
 __global__ void k_log1p_outdeg(const int32_t *__restrict__ outdeg, int32_t V, float *__restrict__ vals) {
@@ -82,11 +99,6 @@ cagra_status launch_features(const cagra_graph *g, const cagra_segments *seg, fl
 }
 
 // ------------------------------------------------------------------ network
-
-// BF16 weights to FP32 in LDS, shared by all rows of the workgroup.
-__device__ __forceinline__ void load_weights(const uint16_t *__restrict__ wb, float *w) {
-    for (int i = threadIdx.x; i < kNParam; i += blockDim.x) w[i] = bf16_to_f32(wb[i]);
-}
 
 constexpr int kFwdThreads = 256;
 
@@ -215,13 +227,67 @@ __global__ __launch_bounds__(kFwdThreads) void k_mlp_forward(const float *__rest
     }
 }
 
-// Backward: persistent workgroups of 128 rows per pass; each thread owns a
-// fixed set of parameters and accumulates their gradient over the rows the
-// workgroup processes; workgroup partials are summed in a fixed order.
-constexpr int kBwdThreads = 128;
-constexpr int kBwdRows = 128;
-constexpr int kPad = kH + 1;  // row pitch in LDS (avoids bank conflicts on row-private reads)
-constexpr int kBwdGrid = 256;
+// Backward. A wave takes 32 rows at a time and runs the three 64 x 64 products
+// of a row tile (hidden layer, its transpose, the weight gradient) on the FP32
+// matrix instructions (v_mfma_f32_32x32x2_f32: FP32 operands and sums, so no
+// operand is rounded). The order of the summation index is free as long as both
+// operands use it, and it is chosen so that registers carry over from one
+// product to the next: half h of the wave (lane / 32) holds index
+// 32 t + 8 q + 4 h + j in its register (t, q, j), which is also how the product
+// returns its rows. With lane = row, first-layer units are computed in place as
+// the A operand of the hidden product; with lane = output unit, its result
+// times w3 and dy is the A operand of the weight gradient; what needs the other
+// orientation (h1, dz2, dz1) goes through the wave's own LDS tile, one after
+// the other. The weights sit in LDS as FP32, once in each orientation.
+//
+// Bound by the matrix instructions (10 us for 65,536 rows at the FP32 rate) and
+// by 128 GELUs with their derivatives per row. 65,536 rows: 318 us with scalar
+// FP32 and one thread per row, 34 us now (30 and 4 of the reduction).
+constexpr int kBwdWaves = 8;
+constexpr int kBwdThreads = kBwdWaves * kWave;
+constexpr int kBwdRows = 32;   // rows of a wave's tile
+constexpr int kBwdGrid = 256;  // most workgroups (one partial gradient each)
+constexpr int kPitch = 68;     // LDS row pitch: 16-byte rows whose starts cycle through the banks
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Orders one wave's LDS accesses: lanes read what other lanes of the wave wrote.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The value of the lane whose number differs in bit M < 32 (ds_swizzle, xor mode).
+template <int M>
+__device__ __forceinline__ float swap_lanes(float x) {
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), (M << 10) | 0x1f));
+}
+
+// Each lane keeps K of the 2 K sums in a (the upper K when its bit M is set),
+// its own plus those of the lane across bit M.
+template <int M, int K>
+__device__ __forceinline__ void halve_rows(float (&a)[16], int lane) {
+    const bool up = lane & M;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        const float send = up ? a[q] : a[q + K], keep = up ? a[q + K] : a[q];
+        a[q] = keep + swap_lanes<M>(send);
+    }
+}
+
+struct BwdLds {
+    float w2[kH * kPitch];                     // W2[n][i]
+    float w2t[kH * kPitch];                    // W2[n][i] at [i][n]
+    float w1[kH * 4];                          // W1[i][0..2], b1[i]
+    float tile[kBwdWaves][kBwdRows * kPitch];  // [row][unit]: h1, then dz2, then dz1
+    float x[kBwdWaves][kBwdRows * 4];          // [row]: standardized features, 1
+    float dy[kBwdWaves][kBwdRows];             // [row]: y, then the loss gradient
+};
+// after the row loop the same memory holds the waves' sums (see wave_sums)
+constexpr int kBwdRegs = 64 + 2 + 2 + 8 + 1;   // W2, w3, b2, W1 and b1, b3
+static_assert(sizeof(BwdLds) <= CAGRA_LDS_BYTES - 1024, "backward LDS");
+static_assert((size_t)(kBwdWaves / 2) * kBwdRegs * kWave * 4 <= sizeof(BwdLds), "wave sums");
 
 __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__restrict__ feats,
                                                               const float *__restrict__ target, int64_t n,
@@ -230,137 +296,303 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
                                                               float *__restrict__ part_grad,
                                                               double *__restrict__ part_loss) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    float *w = reinterpret_cast<float *>(smem);              // kNParam (+3 pad)
-    float *xs = w + ((kNParam + 3 + 3) & ~3);                 // [rows][4]
-    float *dys = xs + kBwdRows * 4;                           // [rows]
-    float *h1s = dys + kBwdRows;                              // [rows][kPad]
-    float *z2s = h1s + kBwdRows * kPad;                       // [rows][kPad]
-    float *dz2s = z2s + kBwdRows * kPad;                      // [rows][kPad]
-    float *dz1s = dz2s + kBwdRows * kPad;                     // [rows][kPad]
-    load_weights(wb, w);
-    __syncthreads();
-    const int t = threadIdx.x;
+    __shared__ double lred[kBwdWaves];
+    BwdLds &L = *reinterpret_cast<BwdLds *>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, h = lane >> 5;  // row or unit within a 32-wide tile, half
+    for (int i = tid; i < kH * kH; i += kBwdThreads) {
+        const float v = bf16_to_f32(wb[kOffW2 + i]);
+        L.w2[(i >> 6) * kPitch + (i & 63)] = v;
+        L.w2t[(i & 63) * kPitch + (i >> 6)] = v;
+    }
+    if (tid < kH) {
+        for (int q = 0; q < 3; ++q) L.w1[tid * 4 + q] = bf16_to_f32(wb[kOffW1 + 3 * tid + q]);
+        L.w1[tid * 4 + 3] = bf16_to_f32(wb[kOffB1 + tid]);
+    }
+    float w3[2], b2[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        w3[t] = bf16_to_f32(wb[kOffW3 + 32 * t + c]);
+        b2[t] = bf16_to_f32(wb[kOffB2 + 32 * t + c]);
+    }
+    const float b3 = bf16_to_f32(wb[kOffB3]);
     const float m0 = norm[0], m1 = norm[1], m2 = norm[2], s0 = norm[3], s1 = norm[4], s2 = norm[5];
     const float inv_n2 = 2.0f / (float)n;
-    // owned parameters: W2[j][i0..i0+31], and for t < 64: w3[t], b2[t], W1[t][0..2], b1[t]; t == 0: b3
-    const int jw = t >> 1, i0 = (t & 1) * 32;
-    float gW2[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) gW2[q] = 0.0f;
-    float gw3 = 0.0f, gb2 = 0.0f, gW1a = 0.0f, gW1b = 0.0f, gW1c = 0.0f, gb1 = 0.0f, gb3 = 0.0f;
-    double loss = 0.0;
+    __syncthreads();
 
-    for (int64_t base = (int64_t)blockIdx.x * kBwdRows; base < n; base += (int64_t)gridDim.x * kBwdRows) {
-        const int64_t r = base + t;
+    f32x16 gW2[2][2] = {};  // [n tile][i tile], rows n, lane = i
+    float gw3[2] = {0.0f, 0.0f}, gb2[2] = {0.0f, 0.0f}, gW1[2][4] = {}, gb3 = 0.0f;
+    double loss = 0.0;
+    float *xs = L.x[w], *dys = L.dy[w];
+    // this lane's corner of each LDS array: all accesses below are at constant
+    // offsets from these (a separate address each would fill the registers)
+    float *by_row = &L.tile[w][c * kPitch + 4 * h];        // lane = row: units 32 t + 8 q + 4 h ...
+    float *by_unit = &L.tile[w][4 * h * kPitch + c];       // lane = unit: rows 8 q + 4 h ...
+    const float *w1 = &L.w1[16 * h], *wn = &L.w2[c * kPitch + 4 * h], *wi = &L.w2t[c * kPitch + 4 * h];
+    const float *x_half = &xs[16 * h], *dy_half = &dys[4 * h];
+
+    // tiles go to workgroups first, then to their waves, so that few rows still use many CUs
+    const int64_t tiles = (n + kBwdRows - 1) / kBwdRows;
+    for (int64_t tl = blockIdx.x + (int64_t)gridDim.x * w; tl < tiles; tl += (int64_t)gridDim.x * kBwdWaves) {
+        const int64_t r = tl * kBwdRows + c;
         const bool live = r < n;
-        // forward for this thread's row
-        const float x0 = live ? (feats[r * 3 + 0] - m0) * s0 : 0.0f;
-        const float x1 = live ? (feats[r * 3 + 1] - m1) * s1 : 0.0f;
-        const float x2 = live ? (feats[r * 3 + 2] - m2) * s2 : 0.0f;
-        float h1[kH];
-#pragma unroll
-        for (int i = 0; i < kH; ++i) {
-            const float z1 = fmaf(w[kOffW1 + 3 * i + 2], x2,
-                                  fmaf(w[kOffW1 + 3 * i + 1], x1, fmaf(w[kOffW1 + 3 * i], x0, w[kOffB1 + i])));
-            h1[i] = gelu(z1);
-            h1s[t * kPad + i] = h1[i];
+        const int64_t rr = live ? r : n - 1;
+        const float f0 = feats[rr * 3 + 0], f1 = feats[rr * 3 + 1], f2 = feats[rr * 3 + 2], tg = target[rr];
+        const float x0 = live ? (f0 - m0) * s0 : 0.0f;
+        const float x1 = live ? (f1 - m1) * s1 : 0.0f;
+        const float x2 = live ? (f2 - m2) * s2 : 0.0f;
+        wave_lds_order();  // the last tile's reads are done
+        if (h == 0) {
+            xs[c * 4 + 0] = x0;
+            xs[c * 4 + 1] = x1;
+            xs[c * 4 + 2] = x2;
+            xs[c * 4 + 3] = 1.0f;
         }
-        float out = w[kOffB3];
-        for (int j = 0; j < kH; ++j) {
-            float z = w[kOffB2 + j];
+        // first layer (lane = row) and hidden product z2 (lane = output unit, registers = rows)
+        float dg1[32];
+        f32x16 z2[2];
 #pragma unroll
-            for (int i = 0; i < kH; ++i) z = fmaf(w[kOffW2 + j * kH + i], h1[i], z);
-            z2s[t * kPad + j] = z;
-            out = fmaf(w[kOffW3 + j], gelu(z), out);
+        for (int t = 0; t < 2; ++t) {
+            float bt = b2[t];
+            asm volatile("" : "+v"(bt));  // spread here, not kept as 16 registers across the loop
+#pragma unroll
+            for (int q = 0; q < 16; ++q) z2[t][q] = bt;
         }
-        const float res = live ? out - target[r] : 0.0f;
-        loss += (double)res * (double)res;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                constexpr int kHalf = 32 * kPitch;
+                const int u = 32 * t + 8 * q;
+                f32x4 hv;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(&w1[(u + j) * 4]);
+                    float g;
+                    gelu_both(fmaf(wv[2], x2, fmaf(wv[1], x1, fmaf(wv[0], x0, wv[3]))), g, dg1[16 * t + 4 * q + j]);
+                    hv[j] = g;
+                }
+                *reinterpret_cast<f32x4 *>(&by_row[u]) = hv;
+                const f32x4 wa = *reinterpret_cast<const f32x4 *>(&wn[u]);
+                const f32x4 wc = *reinterpret_cast<const f32x4 *>(&wn[kHalf + u]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    z2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(hv[j], wa[j], z2[0], 0, 0, 0);
+                    z2[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(hv[j], wc[j], z2[1], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        // output layer: a[q] = this lane's two units of row (q, h); h2 and its derivative replace z2
+        f32x16 h2[2];
+        float a[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            float g0, g1, d0, d1;
+            gelu_both(z2[0][q], g0, d0);
+            gelu_both(z2[1][q], g1, d1);
+            h2[0][q] = g0;
+            h2[1][q] = g1;
+            z2[0][q] = d0;
+            z2[1][q] = d1;
+            a[q] = fmaf(w3[1], g1, w3[0] * g0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // sum over the 32 lanes: each exchange halves the rows a lane carries
+        halve_rows<16, 8>(a, lane);
+        halve_rows<8, 4>(a, lane);
+        halve_rows<4, 2>(a, lane);
+        halve_rows<2, 1>(a, lane);
+        a[0] += swap_lanes<1>(a[0]);
+        {
+            const int q = c >> 1;  // the row register this lane ended with: bits 4..1 of the lane
+            if ((c & 1) == 0) dys[8 * (q >> 2) + 4 * h + (q & 3)] = a[0];
+        }
+        wave_lds_order();
+        const float res = live ? dys[c] + b3 - tg : 0.0f;
         const float dy = res * inv_n2;
-        dys[t] = dy;
-        xs[t * 4 + 0] = x0;
-        xs[t * 4 + 1] = x1;
-        xs[t * 4 + 2] = x2;
-        // dz2 = dy * w3 * gelu'(z2); dh1 = W2^T dz2; dz1 = dh1 * gelu'(z1)
-        float dh1[kH];
+        if (h == 0) {
+            loss += (double)res * (double)res;
+            gb3 += dy;
+        }
+        wave_lds_order();
+        if (h == 0) dys[c] = dy;
+        wave_lds_order();
+        // dz2 = dy * w3 * gelu'(z2) (lane = output unit), and the weight gradient
+        // over the tile's rows: h1 read back with lane = first-layer unit
+        f32x16 dz2[2];
 #pragma unroll
-        for (int i = 0; i < kH; ++i) dh1[i] = 0.0f;
-        for (int j = 0; j < kH; ++j) {
-            const float dz2 = dy * w[kOffW3 + j] * gelu_grad(z2s[t * kPad + j]);
-            dz2s[t * kPad + j] = dz2;
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 d = *reinterpret_cast<const f32x4 *>(&dy_half[8 * q]);
 #pragma unroll
-            for (int i = 0; i < kH; ++i) dh1[i] = fmaf(w[kOffW2 + j * kH + i], dz2, dh1[i]);
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const float v = d[j] * w3[t] * z2[t][4 * q + j];
+                    dz2[t][4 * q + j] = v;
+                    gb2[t] += v;
+                    gw3[t] = fmaf(d[j], h2[t][4 * q + j], gw3[t]);
+                }
         }
 #pragma unroll
-        for (int i = 0; i < kH; ++i) {
-            const float z1 = fmaf(w[kOffW1 + 3 * i + 2], x2,
-                                  fmaf(w[kOffW1 + 3 * i + 1], x1, fmaf(w[kOffW1 + 3 * i], x0, w[kOffB1 + i])));
-            dz1s[t * kPad + i] = dh1[i] * gelu_grad(z1);
-        }
-        __syncthreads();
-        // parameter-owner accumulation over the pass's rows, in row order
-        for (int q = 0; q < kBwdRows; ++q) {
-            const float dz2 = dz2s[q * kPad + jw];
+        for (int q = 0; q < 16; ++q) {
+            const int row = (8 * (q >> 2) + (q & 3)) * kPitch;
+            const float ha = by_unit[row], hb = by_unit[row + 32];
 #pragma unroll
-            for (int c = 0; c < 32; ++c) gW2[c] = fmaf(dz2, h1s[q * kPad + i0 + c], gW2[c]);
+            for (int t = 0; t < 2; ++t) {
+                gW2[t][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(dz2[t][q], ha, gW2[t][0], 0, 0, 0);
+                gW2[t][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(dz2[t][q], hb, gW2[t][1], 0, 0, 0);
+            }
+            if (q & 1) __builtin_amdgcn_sched_barrier(0);
         }
-        if (t < kH) {
-            for (int q = 0; q < kBwdRows; ++q) {
-                const float dyq = dys[q];
-                gw3 = fmaf(dyq, gelu(z2s[q * kPad + t]), gw3);
-                gb2 += dz2s[q * kPad + t];
-                const float dz1 = dz1s[q * kPad + t];
-                gW1a = fmaf(dz1, xs[q * 4 + 0], gW1a);
-                gW1b = fmaf(dz1, xs[q * 4 + 1], gW1b);
-                gW1c = fmaf(dz1, xs[q * 4 + 2], gW1c);
-                gb1 += dz1;
-                if (t == 0) gb3 += dyq;
+        wave_lds_order();  // h1 is read; dz2 takes its place
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int row = (8 * (q >> 2) + (q & 3)) * kPitch;
+            by_unit[row] = dz2[0][q];
+            by_unit[row + 32] = dz2[1][q];
+        }
+        wave_lds_order();
+        // dh1 (lane = row, registers = first-layer units)
+        f32x16 dh1[2] = {};
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                constexpr int kHalf = 32 * kPitch;
+                const int u = 32 * t + 8 * q;
+                const f32x4 dv = *reinterpret_cast<const f32x4 *>(&by_row[u]);
+                const f32x4 wa = *reinterpret_cast<const f32x4 *>(&wi[u]);
+                const f32x4 wc = *reinterpret_cast<const f32x4 *>(&wi[kHalf + u]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    dh1[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wa[j], dv[j], dh1[0], 0, 0, 0);
+                    dh1[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(wc[j], dv[j], dh1[1], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        wave_lds_order();  // dz2 is read; dz1 = dh1 * gelu'(z1) takes its place
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = dh1[t][4 * q + j] * dg1[16 * t + 4 * q + j];
+                *reinterpret_cast<f32x4 *>(&by_row[32 * t + 8 * q]) = v;
+            }
+        wave_lds_order();
+        // first-layer gradients (lane = first-layer unit)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int row = 8 * (q >> 2) + (q & 3);
+            const f32x4 xv = *reinterpret_cast<const f32x4 *>(&x_half[row * 4]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float d = by_unit[row * kPitch + 32 * t];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gW1[t][k] = fmaf(d, xv[k], gW1[t][k]);
             }
         }
+    }
+
+    // the workgroup's sums, in a fixed order: waves w + s into waves w for s = 4, 2, 1
+    float v[kBwdRegs];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[32 * t + 16 * u + q] = gW2[t][u][q];
+        v[64 + t] = gw3[t];
+        v[66 + t] = gb2[t];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[68 + 4 * t + k] = gW1[t][k];
+    }
+    v[76] = gb3;
+    for (int d = 32; d >= 1; d >>= 1) loss += __shfl_down(loss, d, 64);
+    if (lane == 0) lred[w] = loss;
+    __syncthreads();  // every wave is done with its tile
+    float *sums = reinterpret_cast<float *>(smem);
+#pragma unroll 1
+    for (int s = kBwdWaves / 2; s >= 1; s >>= 1) {
+        if (w >= s && w < 2 * s)
+#pragma unroll
+            for (int q = 0; q < kBwdRegs; ++q) sums[((w - s) * kBwdRegs + q) * kWave + lane] = v[q];
+        __syncthreads();
+        if (w < s)
+#pragma unroll
+            for (int q = 0; q < kBwdRegs; ++q) v[q] += sums[(w * kBwdRegs + q) * kWave + lane];
         __syncthreads();
     }
+    if (w != 0) return;
     float *pg = part_grad + (int64_t)blockIdx.x * kNParam;
 #pragma unroll
-    for (int c = 0; c < 32; ++c) pg[kOffW2 + jw * kH + i0 + c] = gW2[c];
-    if (t < kH) {
-        pg[kOffW3 + t] = gw3;
-        pg[kOffB2 + t] = gb2;
-        pg[kOffW1 + 3 * t + 0] = gW1a;
-        pg[kOffW1 + 3 * t + 1] = gW1b;
-        pg[kOffW1 + 3 * t + 2] = gW1c;
-        pg[kOffB1 + t] = gb1;
-    }
-    if (t == 0) pg[kOffB3] = gb3;
-    // loss: fixed-order sum over the workgroup's threads
-    __shared__ double lred[kBwdThreads];
-    lred[t] = loss;
-    __syncthreads();
-    if (t == 0) {
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                pg[kOffW2 + (32 * t + 8 * (q >> 2) + 4 * h + (q & 3)) * kH + 32 * u + c] = v[32 * t + 16 * u + q];
+    // the halves hold the sums over their own rows
+#pragma unroll
+    for (int q = 64; q < kBwdRegs; ++q) v[q] += __shfl_xor(v[q], 32, 64);
+    if (h == 0)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            pg[kOffW3 + 32 * t + c] = v[64 + t];
+            pg[kOffB2 + 32 * t + c] = v[66 + t];
+            for (int k = 0; k < 3; ++k) pg[kOffW1 + 3 * (32 * t + c) + k] = v[68 + 4 * t + k];
+            pg[kOffB1 + 32 * t + c] = v[71 + 4 * t];
+        }
+    float b = v[76];
+    for (int d = 16; d >= 1; d >>= 1) b += __shfl_xor(b, d, 32);
+    if (lane == 0) {
+        pg[kOffB3] = b;
         double s = 0.0;
-        for (int q = 0; q < kBwdThreads; ++q) s += lred[q];
+        for (int x = 0; x < kBwdWaves; ++x) s += lred[x];
         part_loss[blockIdx.x] = s;
     }
 }
 
-__global__ void k_grad_reduce(const float *__restrict__ part_grad, const double *__restrict__ part_loss, int grid,
-                              int64_t n, float *__restrict__ grad, double *__restrict__ loss_out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kNParam) {
-        double s = 0.0;
-        for (int b = 0; b < grid; ++b) s += (double)part_grad[(int64_t)b * kNParam + i];
-        grad[i] = (float)s;
+// Adds the workgroups' partials (FP64): kRedParams parameters per workgroup,
+// kRedLanes threads per parameter taking every kRedLanes-th partial, then those
+// sums in order. One thread per parameter over all 256 partials took 75 us.
+constexpr int kRedParams = 32, kRedLanes = 8, kRedBatch = 8;
+__global__ __launch_bounds__(kRedParams *kRedLanes) void k_grad_reduce(const float *__restrict__ part_grad,
+                                                                       const double *__restrict__ part_loss, int grid,
+                                                                       int64_t n, float *__restrict__ grad,
+                                                                       double *__restrict__ loss_out) {
+    __shared__ double red[kRedLanes][kRedParams];
+    const int p = threadIdx.x % kRedParams, g = threadIdx.x / kRedParams;
+    const int i = blockIdx.x * kRedParams + p, ii = i < kNParam ? i : kNParam - 1;
+    double s = 0.0;
+    for (int b0 = g; b0 < grid; b0 += kRedLanes * kRedBatch) {
+        float x[kRedBatch];
+#pragma unroll
+        for (int u = 0; u < kRedBatch; ++u) {
+            const int b = b0 + u * kRedLanes;
+            x[u] = part_grad[(int64_t)(b < grid ? b : b0) * kNParam + ii];
+        }
+#pragma unroll
+        for (int u = 0; u < kRedBatch; ++u)
+            if (b0 + u * kRedLanes < grid) s += (double)x[u];
     }
-    if (i == 0) {
-        double s = 0.0;
-        for (int b = 0; b < grid; ++b) s += part_loss[b];
-        loss_out[0] = s / (double)n;
+    red[g][p] = s;
+    __syncthreads();
+    if (g == 0 && i < kNParam) {
+        double t = 0.0;
+        for (int k = 0; k < kRedLanes; ++k) t += red[k][p];
+        grad[i] = (float)t;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+        double t = 0.0;
+        for (int b = threadIdx.x; b < grid; b += kWave) t += part_loss[b];
+        for (int d = 32; d >= 1; d >>= 1) t += __shfl_down(t, d, 64);
+        if (threadIdx.x == 0) loss_out[0] = t / (double)n;
     }
 }
 
 size_t mlp_grad_ws_bytes() { return align_up((size_t)kBwdGrid * kNParam * 4, 256) + (size_t)kBwdGrid * 8 + 256; }
-
-static size_t bwd_lds_bytes() {
-    return (size_t)(((kNParam + 3 + 3) & ~3) + kBwdRows * 4 + kBwdRows + 4 * kBwdRows * kPad) * sizeof(float);
-}
 
 static unsigned forward_grid(int64_t n) {
     int64_t g = ceil_div(ceil_div(n, 16), kFwdThreads / 64);
@@ -380,9 +612,12 @@ cagra_status launch_mlp_grad(const float *feats, const float *target, int64_t n,
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_mlp_backward)) return a_;
     float *pg = (float *)ws;
     double *pl = (double *)((char *)ws + align_up((size_t)kBwdGrid * kNParam * 4, 256));
-    k_mlp_backward<<<kBwdGrid, kBwdThreads, bwd_lds_bytes(), st>>>(feats, target, n, wb, norm, pg, pl);
+    const int64_t tiles = ceil_div(n, kBwdRows);
+    const int grid = (int)(tiles < kBwdGrid ? tiles : kBwdGrid);
+    k_mlp_backward<<<grid, kBwdThreads, sizeof(BwdLds), st>>>(feats, target, n, wb, norm, pg, pl);
     CAGRA_LAUNCH_CHECK();
-    k_grad_reduce<<<(unsigned)ceil_div(kNParam, 256), 256, 0, st>>>(pg, pl, kBwdGrid, n, grad, loss);
+    k_grad_reduce<<<(unsigned)ceil_div(kNParam, kRedParams), kRedParams * kRedLanes, 0, st>>>(pg, pl, grid, n, grad,
+                                                                                            loss);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
