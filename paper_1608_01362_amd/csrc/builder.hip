@@ -2,7 +2,11 @@
 //
 // The CSC row of a destination v lists its sources in ascending order, so the
 // in-edges of v that fall in one segment (source / N) form a contiguous run.
-// Every run is one row (s, v) of subgraph s. The builder
+// Every run is one row (s, v) of subgraph s. The builder brings rows and edges
+// into segment-major order (segdirect.hip, a counting and a scattering pass),
+// then builds the merge block index (Section 3.3) and the gather tile table.
+//
+// More than kDirectMaxSegments segments go through two stable sorts instead:
 //   1. flags run starts and labels every edge with its run and destination
 //      (two device-wide scans),
 //   2. stable-sorts the runs by segment id (the runs arrive in (v, s) order;
@@ -13,8 +17,7 @@
 //      with the stable digit passes of segsort.hip, whose tile-local ranking in
 //      LDS keeps the writes coalesced where a direct scatter of runs and edges
 //      writes a few bytes per cache line,
-//   3. writes the rows and their offsets from the sorted runs,
-//   4. builds the merge block index (Section 3.3) and the gather tile table.
+//   3. writes the rows and their offsets from the sorted runs.
 // Everything is integer work; the result is unique and bit-identical run to run.
 #include <limits.h>
 
@@ -22,6 +25,7 @@
 
 #include "common.h"
 #include "radix.h"
+#include "segdirect.h"
 
 namespace cagra {
 
@@ -220,46 +224,6 @@ __device__ __forceinline__ int64_t clamp_edge(int64_t e, int64_t E) { return e <
 // segment than its predecessor's.
 __device__ __forceinline__ bool run_start(int64_t e, int32_t m, int32_t u, int32_t u_prev, int32_t N) {
     return e == 0 || m != 0 || (u / N) != (u_prev / N);
-}
-
-// Query pass: per-segment edge counts and the number of runs (rows).
-__global__ __launch_bounds__(kBThreads) void k_count(const int32_t *__restrict__ src,
-                                                     const int32_t *__restrict__ mark, int64_t E, int32_t N,
-                                                     int32_t k, int use_lds, int32_t *__restrict__ seg_edges,
-                                                     unsigned long long *runs) {
-    extern __shared__ int32_t hist[];
-    if (use_lds) {
-        for (int s = threadIdx.x; s < k; s += blockDim.x) hist[s] = 0;
-        __syncthreads();
-    }
-    unsigned long long nr = 0;
-    const int64_t stride = (int64_t)gridDim.x * kBThreads * kBItems;
-    for (int64_t e0 = (int64_t)blockIdx.x * kBThreads * kBItems + threadIdx.x; e0 < E; e0 += stride) {
-        int32_t m[kBItems], u[kBItems], up[kBItems];
-#pragma unroll
-        for (int j = 0; j < kBItems; ++j) {
-            const int64_t ec = clamp_edge(e0 + j * kBThreads, E);
-            m[j] = mark[ec];
-            u[j] = src[ec];
-            up[j] = src[ec > 0 ? ec - 1 : 0];
-        }
-#pragma unroll
-        for (int j = 0; j < kBItems; ++j) {
-            const int64_t e = e0 + j * kBThreads;
-            if (e >= E) break;
-            const int32_t s = u[j] / N;
-            if (use_lds) atomicAdd(&hist[s], 1);
-            else atomicAdd(&seg_edges[s], 1);
-            nr += run_start(e, m[j], u[j], up[j], N) ? 1 : 0;
-        }
-    }
-    for (int d = 32; d >= 1; d >>= 1) nr += __shfl_down(nr, d, 64);
-    if ((threadIdx.x & 63) == 0 && nr) atomicAdd(runs, nr);
-    if (use_lds) {
-        __syncthreads();
-        for (int s = threadIdx.x; s < k; s += blockDim.x)
-            if (hist[s]) atomicAdd(&seg_edges[s], hist[s]);
-    }
 }
 
 __global__ __launch_bounds__(kBThreads) void k_flags(const int32_t *__restrict__ src,
@@ -478,9 +442,9 @@ static int nbits_for(int32_t k) {
 size_t query_workspace_bytes(int32_t V, int64_t E, int32_t N) {
     int64_t k = ceil_div(V, N);
     ArenaSize a;
-    a.take<int32_t>(E);                  // mark
-    a.take<int32_t>(k);                  // per-segment edges
-    a.take<unsigned long long>(1);       // run count
+    a.take<int32_t>(edge_groups(E) + 1);  // first row of each edge group
+    a.take<int32_t>(k);                   // per-segment edges
+    a.take<unsigned long long>(1);        // run count
     return a.used + 256;
 }
 
@@ -502,8 +466,15 @@ static cagra_status sort_temps(int64_t E, int64_t Q, int32_t k, bool w16, SortTe
 //   flag (runincl)     -> sorted edge keys
 //   run_first          -> sorted run keys
 //   run_seg + run_dst  -> sorted run values
+// (k > kDirectMaxSegments; build_direct needs its count matrices only).
 static size_t build_layout(int64_t E, int64_t Q, int32_t k, int32_t nb, int wbytes, const SortTemps &t) {
     ArenaSize a;
+    if (k <= kDirectMaxSegments) {
+        a.take<int32_t>(k + 1);  // tile counts
+        const int64_t most = (int64_t)nb + 1 > (int64_t)k + 1 ? (int64_t)nb + 1 : (int64_t)k + 1;
+        const size_t scan = scan_ws_bytes(most), direct = E > 0 ? direct_ws_bytes(E, k) : 0;
+        return align_up(a.used, 256) + (scan > direct ? scan : direct) + 256;
+    }
     a.take<char>(4 * E + 512);            // mark / dstp1; then edge keys (+ 16-bit edge words)
     a.take<int32_t>(E);                   // flags / runincl; then sorted edge keys
     a.take<int32_t>(Q + 1);               // run_first; then sorted run keys
@@ -520,36 +491,26 @@ static size_t build_layout(int64_t E, int64_t Q, int32_t k, int32_t nb, int wbyt
     return a.used + scan_ws_bytes(mx) + 256;
 }
 
-static cagra_status allow_big_lds_impl();
-static cagra_status allow_big_lds() { return allow_big_lds_impl(); }
-
 cagra_status query_segments(const cagra_graph *g, cagra_segments *seg, void *ws, size_t ws_bytes, hipStream_t st) {
     const int32_t V = g->V, N = seg->N;
     const int64_t E = g->E;
     const int32_t k = (int32_t)ceil_div(V, N);
     Arena ar{(char *)ws, ws_bytes, 0};
-    int32_t *mark = ar.take<int32_t>(E);
+    int32_t *rows = ar.take<int32_t>(edge_groups(E) + 1);
     int32_t *seg_edges = ar.take<int32_t>(k);
     unsigned long long *runs = ar.take<unsigned long long>(1);
-    if (!mark || !seg_edges || !runs) return fail(CAGRA_E_BUFFER, "query workspace smaller than %zu bytes",
+    if (!rows || !seg_edges || !runs) return fail(CAGRA_E_BUFFER, "query workspace smaller than %zu bytes",
                                                   query_workspace_bytes(V, E, N));
     int64_t Q = 0;
     std::vector<int32_t> host_edges(k, 0);
     if (E > 0) {
-        if (cagra_status a = allow_big_lds()) return a;
-        k_fill_i32<<<grid_for(E, 256), 256, 0, st>>>(mark, E, 0);
-        CAGRA_LAUNCH_CHECK();
         k_fill_i32<<<grid_for(k, 256), 256, 0, st>>>(seg_edges, k, 0);
         CAGRA_LAUNCH_CHECK();
-        CAGRA_HIP_CHECK(hipMemsetAsync(runs, 0, sizeof(unsigned long long), st));
-        k_mark_rows<<<grid_for(V, 256), 256, 0, st>>>(g->in_offsets, V, mark);
+        k_fill_i32<<<1, 64, 0, st>>>(reinterpret_cast<int32_t *>(runs), 2, 0);
         CAGRA_LAUNCH_CHECK();
-        int use_lds = k <= 16384 ? 1 : 0;
-        unsigned grid = grid_for(E, kBThreads * kBItems * 8);
-        if (grid > 4096) grid = 4096;
-        k_count<<<grid, kBThreads, use_lds ? k * sizeof(int32_t) : 0, st>>>(g->in_sources, mark, E, N, k, use_lds,
-                                                                      seg_edges, runs);
-        CAGRA_LAUNCH_CHECK();
+        cagra_status s;
+        if ((s = launch_group_rows(g->in_offsets, V, E, rows, st)) != CAGRA_OK) return s;
+        if ((s = launch_count_runs(g, N, k, rows, seg_edges, runs, st)) != CAGRA_OK) return s;
         unsigned long long hr = 0;
         CAGRA_HIP_CHECK(hipMemcpyAsync(&hr, runs, sizeof(hr), hipMemcpyDeviceToHost, st));
         CAGRA_HIP_CHECK(hipMemcpyAsync(host_edges.data(), seg_edges, (size_t)k * sizeof(int32_t),
@@ -575,11 +536,6 @@ cagra_status query_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     return CAGRA_OK;
 }
 
-static cagra_status allow_big_lds_impl() {
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_count)) return a_;
-    return CAGRA_OK;
-}
-
 // 5. merge work items per block (needs block_ptr)
 static cagra_status build_block_items(cagra_segments *seg, Arena &ar, hipStream_t st) {
     k_block_items<<<(unsigned)seg->nb, 64, 0, st>>>(seg->block_ptr, seg->k, seg->nb,
@@ -588,15 +544,14 @@ static cagra_status build_block_items(cagra_segments *seg, Arena &ar, hipStream_
     return scan_i32<ScanAdd>(seg->block_items, seg->block_items, (int64_t)seg->nb + 1, false, ar, st);
 }
 
-cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws, size_t ws_bytes, hipStream_t st) {
-    if (cagra_status a = allow_big_lds()) return a;
-    const int32_t V = g->V, N = seg->N, B = seg->B, T = seg->tile_edges, k = seg->k, nb = seg->nb;
+// The sorted form of the reorder, for more segments than build_direct takes:
+// rows, their offsets and the edge words through two stable radix sorts.
+static cagra_status build_sorted(const cagra_graph *g, cagra_segments *seg, Arena &ar, hipStream_t st) {
+    const int32_t V = g->V, N = seg->N, B = seg->B, k = seg->k;
     const int64_t E = g->E, Q = seg->Q;
-    const int32_t ntiles = seg->ntiles;
     const bool w16 = edge16(N);
     SortTemps tmp;
     if (cagra_status e = sort_temps(E, Q, k, w16, tmp)) return e;
-    Arena ar{(char *)ws, ws_bytes, 0};
     char *mreg = ar.take<char>(4 * E + 512);
     int32_t *flag = ar.take<int32_t>(E);
     int32_t *run_first = ar.take<int32_t>(Q + 1);
@@ -604,10 +559,9 @@ cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     uint16_t *rkey = ar.take<uint16_t>(Q);
     unsigned long long *rval = ar.take<unsigned long long>(Q);
     char *eval32 = w16 ? nullptr : ar.take<char>(4 * E);
-    int32_t *tcount = ar.take<int32_t>(k + 1);
     const size_t tmp_bytes = tmp.rows > tmp.edges ? tmp.rows : tmp.edges;
     char *stmp = ar.take<char>((int64_t)tmp_bytes);
-    if (!mreg || !flag || !run_first || !run_sd || !rkey || !rval || (!w16 && !eval32) || !tcount || !stmp)
+    if (!mreg || !flag || !run_first || !run_sd || !rkey || !rval || (!w16 && !eval32) || !stmp)
         return fail(CAGRA_E_BUFFER, "build workspace smaller than %zu bytes", seg->build_workspace_bytes);
     int32_t *mark = reinterpret_cast<int32_t *>(mreg);
     int32_t *run_seg = run_sd, *run_dst = run_sd + Q;
@@ -618,17 +572,6 @@ cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     uint16_t *rkey_s = reinterpret_cast<uint16_t *>(run_first);
     unsigned long long *rval_s = reinterpret_cast<unsigned long long *>(run_sd);
     cagra_status s;
-    if (E == 0) {
-        k_fill_i32<<<grid_for(k + 1, 256), 256, 0, st>>>(seg->seg_row_begin, k + 1, 0);
-        CAGRA_LAUNCH_CHECK();
-        k_fill_i32<<<1, 64, 0, st>>>(seg->row_ptr, 1, 0);
-        CAGRA_LAUNCH_CHECK();
-        k_fill_i32<<<grid_for((int64_t)(nb + 1) * k, 256), 256, 0, st>>>(seg->block_ptr, (int64_t)(nb + 1) * k, 0);
-        CAGRA_LAUNCH_CHECK();
-        k_fill_i32<<<1, 64, 0, st>>>(seg->tile_edge, 1, 0);
-        CAGRA_LAUNCH_CHECK();
-        return build_block_items(seg, ar, st);
-    }
     // 1. run starts, destinations, run ids
     k_fill_i32<<<grid_for(E, 256), 256, 0, st>>>(mark, E, 0);
     CAGRA_LAUNCH_CHECK();
@@ -669,6 +612,38 @@ cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     k_rows_sorted<<<grid_for(Q + 1, 256), 256, 0, st>>>(rval_s, Q, B, seg->row_dst, seg->row_dst_lo, seg->row_ptr);
     CAGRA_LAUNCH_CHECK();
     if ((s = scan_i32<ScanAdd>(seg->row_ptr, seg->row_ptr, Q + 1, false, ar, st)) != CAGRA_OK) return s;
+    return CAGRA_OK;
+}
+
+cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws, size_t ws_bytes, hipStream_t st) {
+    const int32_t B = seg->B, T = seg->tile_edges, k = seg->k, nb = seg->nb;
+    const int64_t E = g->E;
+    const int32_t ntiles = seg->ntiles;
+    cagra_status s;
+    Arena ar{(char *)ws, ws_bytes, 0};
+    int32_t *tcount = ar.take<int32_t>(k + 1);
+    if (!tcount) return fail(CAGRA_E_BUFFER, "build workspace smaller than %zu bytes", seg->build_workspace_bytes);
+    if (E == 0) {
+        k_fill_i32<<<grid_for(k + 1, 256), 256, 0, st>>>(seg->seg_row_begin, k + 1, 0);
+        CAGRA_LAUNCH_CHECK();
+        k_fill_i32<<<1, 64, 0, st>>>(seg->row_ptr, 1, 0);
+        CAGRA_LAUNCH_CHECK();
+        k_fill_i32<<<grid_for((int64_t)(nb + 1) * k, 256), 256, 0, st>>>(seg->block_ptr, (int64_t)(nb + 1) * k, 0);
+        CAGRA_LAUNCH_CHECK();
+        k_fill_i32<<<1, 64, 0, st>>>(seg->tile_edge, 1, 0);
+        CAGRA_LAUNCH_CHECK();
+        return build_block_items(seg, ar, st);
+    }
+    // 1.-3. rows, offsets and edge words in segment-major order
+    if (k <= kDirectMaxSegments) {
+        const size_t at = align_up(ar.used, 256);
+        s = build_direct(g, seg, ar.base + at, ws_bytes - at, st);
+    } else {
+        const size_t mark = ar.used;
+        s = build_sorted(g, seg, ar, st);
+        ar.used = mark;
+    }
+    if (s != CAGRA_OK) return s;
     // 4. merge block index and gather tiles
     k_block_ptr<<<grid_for((int64_t)(nb + 1) * k, 256), 256, 0, st>>>(seg->row_dst, seg->seg_row_begin, k, nb, B,
                                                                        seg->block_ptr);
