@@ -177,7 +177,7 @@ int32_t cagra_edge_word_bytes(int32_t N);
  *   out_degree  device int32[V], written: new out-degrees
  *   hot         device int32[1] or NULL, written: number of clustered vertices
  *   workspace   device memory of cagra_cluster_workspace_bytes(V, E) bytes
- *               (about 16 bytes per edge; the caller owns it)
+ *               (about 4 bytes per edge and 32 per vertex; the caller owns it)
  * Outputs must not alias the inputs. Errors: CAGRA_E_INVALID / _OVERFLOW for
  * bad arguments, CAGRA_E_BUFFER for a missing or small workspace, nothing
  * launched in those cases. Asynchronous on `stream`.

@@ -442,9 +442,8 @@ static int nbits_for(int32_t k) {
 size_t query_workspace_bytes(int32_t V, int64_t E, int32_t N) {
     int64_t k = ceil_div(V, N);
     ArenaSize a;
-    a.take<int32_t>(edge_groups(E) + 1);  // first row of each edge group
-    a.take<int32_t>(k);                   // per-segment edges
-    a.take<unsigned long long>(1);        // run count
+    a.take<int32_t>((int64_t)k + 2);  // run count (64-bit), edges per segment
+    a.take<char>(E > 0 ? (int64_t)row_list_ws_bytes(V, E, kGroupEdges) : 0);
     return a.used + 256;
 }
 
@@ -467,12 +466,12 @@ static cagra_status sort_temps(int64_t E, int64_t Q, int32_t k, bool w16, SortTe
 //   run_first          -> sorted run keys
 //   run_seg + run_dst  -> sorted run values
 // (k > kDirectMaxSegments; build_direct needs its count matrices only).
-static size_t build_layout(int64_t E, int64_t Q, int32_t k, int32_t nb, int wbytes, const SortTemps &t) {
+static size_t build_layout(int32_t V, int64_t E, int64_t Q, int32_t k, int32_t nb, int wbytes, const SortTemps &t) {
     ArenaSize a;
     if (k <= kDirectMaxSegments) {
         a.take<int32_t>(k + 1);  // tile counts
         const int64_t most = (int64_t)nb + 1 > (int64_t)k + 1 ? (int64_t)nb + 1 : (int64_t)k + 1;
-        const size_t scan = scan_ws_bytes(most), direct = E > 0 ? direct_ws_bytes(E, k) : 0;
+        const size_t scan = scan_ws_bytes(most), direct = E > 0 ? direct_ws_bytes(V, E, k) : 0;
         return align_up(a.used, 256) + (scan > direct ? scan : direct) + 256;
     }
     a.take<char>(4 * E + 512);            // mark / dstp1; then edge keys (+ 16-bit edge words)
@@ -496,20 +495,19 @@ cagra_status query_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     const int64_t E = g->E;
     const int32_t k = (int32_t)ceil_div(V, N);
     Arena ar{(char *)ws, ws_bytes, 0};
-    int32_t *rows = ar.take<int32_t>(edge_groups(E) + 1);
-    int32_t *seg_edges = ar.take<int32_t>(k);
-    unsigned long long *runs = ar.take<unsigned long long>(1);
-    if (!rows || !seg_edges || !runs) return fail(CAGRA_E_BUFFER, "query workspace smaller than %zu bytes",
+    int32_t *totals = ar.take<int32_t>((int64_t)k + 2);
+    unsigned long long *runs = reinterpret_cast<unsigned long long *>(totals);
+    int32_t *seg_edges = totals + 2;
+    if (!totals) return fail(CAGRA_E_BUFFER, "query workspace smaller than %zu bytes",
                                                   query_workspace_bytes(V, E, N));
     int64_t Q = 0;
     std::vector<int32_t> host_edges(k, 0);
     if (E > 0) {
-        k_fill_i32<<<grid_for(k, 256), 256, 0, st>>>(seg_edges, k, 0);
-        CAGRA_LAUNCH_CHECK();
-        k_fill_i32<<<1, 64, 0, st>>>(reinterpret_cast<int32_t *>(runs), 2, 0);
+        k_fill_i32<<<grid_for((int64_t)k + 2, 256), 256, 0, st>>>(totals, (int64_t)k + 2, 0);
         CAGRA_LAUNCH_CHECK();
         cagra_status s;
-        if ((s = launch_group_rows(g->in_offsets, V, E, rows, st)) != CAGRA_OK) return s;
+        RowList rows;
+        if ((s = build_row_list(g->in_offsets, V, E, kGroupEdges, ar, &rows, st)) != CAGRA_OK) return s;
         if ((s = launch_count_runs(g, N, k, rows, seg_edges, runs, st)) != CAGRA_OK) return s;
         unsigned long long hr = 0;
         CAGRA_HIP_CHECK(hipMemcpyAsync(&hr, runs, sizeof(hr), hipMemcpyDeviceToHost, st));
@@ -532,7 +530,7 @@ cagra_status query_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
     seg->max_items = (int32_t)items;
     SortTemps t;
     if (cagra_status e = sort_temps(E, Q, k, edge16(N), t)) return e;
-    seg->build_workspace_bytes = build_layout(E, Q, k, seg->nb, edge16(N) ? 2 : 4, t);
+    seg->build_workspace_bytes = build_layout(V, E, Q, k, seg->nb, edge16(N) ? 2 : 4, t);
     return CAGRA_OK;
 }
 

@@ -10,7 +10,7 @@
 //      edge word, and for each run its destination, block offset and first edge
 //      (row_ptr), straight to their places.
 // Both passes take groups of 1,024 consecutive edges per wave. A wave marks the
-// rows that start in its group in LDS, so the row of an edge is the last mark
+// rows that start in its group (from a list of the non-empty rows) in LDS, so the row of an edge is the last mark
 // at or before it, found with ballots; nothing per edge is kept in memory
 // between the passes. Source reads are coalesced; each segment's part of a tile
 // is staged in LDS by output position and leaves as one contiguous run, and
@@ -59,37 +59,112 @@ constexpr int kTileEdges = kSegWaves * kGroupEdges;   // edges ranked and staged
 constexpr int kMaxChunkTiles = 4;
 constexpr int kChunksWanted = 1024;  // below this many chunks a chunk is one tile
 
-int64_t edge_groups(int64_t E) { return ceil_div(E, kGroupEdges); }
+// ---- non-empty rows
 
-// Row v covers the groups whose first edge it holds. Rows of many groups are
-// filled by the whole wave.
-__global__ __launch_bounds__(256) void k_group_rows(const int32_t *__restrict__ off, int32_t V, int64_t groups,
-                                                    int32_t *__restrict__ rows) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int lane = __lane_id();
-    int64_t g0 = 0, g1 = 0;
-    if (v < V) {
-        g0 = ceil_div(off[v], kGroupEdges);
-        g1 = ceil_div(off[v + 1], kGroupEdges);
-        if (g1 > groups) g1 = groups;
+constexpr int kRlThreads = 256;
+constexpr int kRlItems = 8;
+constexpr int kRlRows = kRlThreads * kRlItems;  // rows of a workgroup
+
+__global__ __launch_bounds__(kRlThreads) void k_rows_count(const int32_t *__restrict__ off, int32_t V,
+                                                           int32_t *__restrict__ count) {
+    __shared__ int32_t wsum[kRlThreads / kWave];
+    int32_t n = 0;
+#pragma unroll
+    for (int j = 0; j < kRlItems; ++j) {
+        const int64_t r = (int64_t)blockIdx.x * kRlRows + j * kRlThreads + threadIdx.x;
+        const bool full = r < V && off[r < V ? r + 1 : 0] > off[r < V ? r : 0];
+        n += (int32_t)__builtin_popcountll(ballot(full));
     }
-    const bool many = g1 - g0 > 8;
-    if (!many)
-        for (int64_t g = g0; g < g1; ++g) rows[g] = (int32_t)v;
-    for (uint64_t m = ballot(many); m; m &= m - 1) {
-        const int l = (int)__builtin_ctzll(m);
-        const int32_t a = __builtin_amdgcn_readlane((int32_t)g0, l), b = __builtin_amdgcn_readlane((int32_t)g1, l);
-        const int32_t row = __builtin_amdgcn_readlane((int32_t)v, l);
-        for (int32_t g = a + lane; g < b; g += kWave) rows[g] = row;
+    if (__lane_id() == 0) wsum[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int i = 0; i < kRlThreads / kWave; ++i) t += wsum[i];
+        const bool one = gridDim.x == 1;  // a single block is its own scan
+        count[blockIdx.x] = one ? 0 : t;
+        if (blockIdx.x == gridDim.x - 1) count[gridDim.x] = one ? t : 0;
     }
-    if (v == 0) rows[groups] = V - 1;
 }
 
-cagra_status launch_group_rows(const int32_t *in_offsets, int32_t V, int64_t E, int32_t *rows, hipStream_t st) {
-    k_group_rows<<<(unsigned)ceil_div(V, 256), 256, 0, st>>>(in_offsets, V, edge_groups(E), rows);
+__global__ __launch_bounds__(kRlThreads) void k_rows_list(const int32_t *__restrict__ off, int32_t V, int64_t units,
+                                                          int32_t unit, RowList list) {
+    __shared__ int32_t cnt[kRlItems][kRlThreads / kWave];
+    const int lane = __lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int32_t a[kRlItems], b[kRlItems];
+    uint64_t m[kRlItems];
+#pragma unroll
+    for (int j = 0; j < kRlItems; ++j) {
+        const int64_t r = (int64_t)blockIdx.x * kRlRows + j * kRlThreads + threadIdx.x;
+        a[j] = off[r < V ? r : V];
+        b[j] = off[r < V ? r + 1 : V];
+        m[j] = ballot(b[j] > a[j]);
+        if (lane == 0) cnt[j][w] = (int32_t)__builtin_popcountll(m[j]);
+    }
+    __syncthreads();
+    int32_t at = list.count[blockIdx.x];
+#pragma unroll
+    for (int j = 0; j < kRlItems; ++j) {
+        int32_t i = at;
+        for (int x = 0; x < kRlThreads / kWave; ++x) {
+            if (x < w) i += cnt[j][x];
+            at += cnt[j][x];
+        }
+        i += (int32_t)__builtin_popcountll(m[j] & lanemask_lt());
+        const bool full = b[j] > a[j];
+        const int64_t r = (int64_t)blockIdx.x * kRlRows + j * kRlThreads + threadIdx.x;
+        int64_t u0 = 0, u1 = 0;  // units whose first edge the row holds
+        if (full) {
+            list.row[i] = (int32_t)r;
+            list.start[i] = a[j];
+            u0 = ceil_div(a[j], unit);
+            u1 = ceil_div(b[j], unit);
+            if (u1 > units) u1 = units;
+        }
+        const bool many = u1 - u0 > 8;
+        if (!many)
+            for (int64_t u = u0; u < u1; ++u) list.first[u] = i;
+        for (uint64_t mm = ballot(many); mm; mm &= mm - 1) {  // rows of many units are filled by the wave
+            const int l = (int)__builtin_ctzll(mm);
+            const int32_t f = __builtin_amdgcn_readlane((int32_t)u0, l), e = __builtin_amdgcn_readlane((int32_t)u1, l);
+            const int32_t at_l = __builtin_amdgcn_readlane(i, l);
+            for (int32_t u = f + lane; u < e; u += kWave) list.first[u] = at_l;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) list.first[units] = list.count[gridDim.x] - 1;
+}
+
+size_t row_list_ws_bytes(int32_t V, int64_t E, int32_t unit) {
+    ArenaSize a;
+    a.take<int32_t>(V < E ? V : E);
+    a.take<int32_t>(V < E ? V : E);
+    a.take<int32_t>(ceil_div(E, unit) + 1);
+    a.take<int32_t>(ceil_div(V, kRlRows) + 1);
+    return a.used + scan_add_ws_bytes(ceil_div(V, kRlRows) + 1) + 512;
+}
+
+cagra_status build_row_list(const int32_t *offsets, int32_t V, int64_t E, int32_t unit, Arena &ar, RowList *list,
+                            hipStream_t st) {
+    const int64_t blocks = ceil_div(V, kRlRows);
+    list->row = ar.take<int32_t>(V < E ? V : E);  // at most one row per edge
+    list->start = ar.take<int32_t>(V < E ? V : E);
+    list->first = ar.take<int32_t>(ceil_div(E, unit) + 1);
+    list->count = ar.take<int32_t>(blocks + 1);
+    if (!list->row || !list->start || !list->first || !list->count)
+        return fail(CAGRA_E_BUFFER, "workspace too small (row list)");
+    k_rows_count<<<(unsigned)blocks, kRlThreads, 0, st>>>(offsets, V, list->count);
+    CAGRA_LAUNCH_CHECK();
+    if (blocks > 1) {
+        const size_t at = align_up(ar.used, 256);  // the scan's temporaries are free again afterwards
+        if (at > ar.cap) return fail(CAGRA_E_BUFFER, "workspace too small (row list)");
+        if (cagra_status s = scan_add_exclusive(list->count, list->count, blocks + 1, ar.base + at, ar.cap - at, st))
+            return s;
+    }
+    k_rows_list<<<(unsigned)blocks, kRlThreads, 0, st>>>(offsets, V, ceil_div(E, unit), unit, *list);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
+
+// ---- passes over the edges
 
 // Orders one wave's LDS accesses (lanes read what other lanes of it wrote).
 __device__ __forceinline__ void wave_lds_order() {
@@ -120,20 +195,18 @@ __device__ __forceinline__ void load_group(const int32_t *__restrict__ src, int6
 }
 
 // marks[i] = 1 + the row that starts at the group's edge i, 0 where none does.
-// The rows between the group's first row and the next group's are looked at.
-__device__ __forceinline__ void mark_rows(const int32_t *__restrict__ off, const int32_t *__restrict__ rows, int64_t g,
-                                          int32_t *marks) {
+__device__ __forceinline__ void mark_rows(const RowList &list, int64_t g, int32_t *marks) {
     const int lane = __lane_id();
     const int64_t base = g * kGroupEdges;
-    const int32_t r0 = rows[g], r1 = rows[g + 1];
+    const int32_t i0 = list.first[g], i1 = list.first[g + 1];
     wave_lds_order();
 #pragma unroll
     for (int j = 0; j < kSteps; ++j) marks[j * kWave + lane] = 0;
     wave_lds_order();
-    for (int32_t rb = r0; rb <= r1; rb += kWave) {  // uniform
-        const int32_t r = rb + lane < r1 ? rb + lane : r1;
-        const int64_t a = (int64_t)off[r] - base;
-        if (rb + lane <= r1 && off[r + 1] - base > a && a >= 0 && a < kGroupEdges) marks[a] = r + 1;
+    for (int32_t ib = i0; ib <= i1; ib += kWave) {  // uniform; at most 17 rounds
+        const int32_t i = ib + lane < i1 ? ib + lane : i1;
+        const int64_t a = (int64_t)list.start[i] - base;
+        if (ib + lane <= i1 && a >= 0 && a < kGroupEdges) marks[a] = list.row[i] + 1;
     }
     wave_lds_order();
 }
@@ -150,9 +223,8 @@ __device__ __forceinline__ bool run_begins(int32_t mark, int32_t s, int32_t &las
 // Edges and runs per segment of a chunk, one LDS atomic per run and step:
 // edges << 16 | runs (a chunk has at most 32,768 of either).
 __global__ __launch_bounds__(kSegThreads) void k_seg_count(const int32_t *__restrict__ src,
-                                                           const int32_t *__restrict__ off,
-                                                           const int32_t *__restrict__ rows, int64_t E, FastDiv div,
-                                                           int32_t k, int32_t chunks, int32_t chunk_groups,
+                                                           RowList list, int64_t E, FastDiv div, int32_t k,
+                                                           int32_t chunks, int32_t chunk_groups,
                                                            int32_t *__restrict__ edge_counts,
                                                            int32_t *__restrict__ run_counts) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -168,7 +240,7 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_count(const int32_t *__rest
         if (g >= groups) break;
         int32_t u[kSteps], before;
         load_group(src, E, g, u, before);
-        mark_rows(off, rows, g, marks);
+        mark_rows(list, g, marks);
         int32_t last = quotient(div, before);
         const int32_t n = group_size(E, g);
 #pragma unroll
@@ -193,9 +265,8 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_count(const int32_t *__rest
 
 // The query's totals: edges per segment (LDS histogram when it fits) and runs.
 __global__ __launch_bounds__(kSegThreads) void k_count_runs(const int32_t *__restrict__ src,
-                                                            const int32_t *__restrict__ off,
-                                                            const int32_t *__restrict__ rows, int64_t E, FastDiv div,
-                                                            int32_t k, int use_lds, int32_t *__restrict__ seg_edges,
+                                                            RowList list, int64_t E, FastDiv div, int32_t k,
+                                                            int use_lds, int32_t *__restrict__ seg_edges,
                                                             unsigned long long *__restrict__ runs) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
@@ -209,7 +280,7 @@ __global__ __launch_bounds__(kSegThreads) void k_count_runs(const int32_t *__res
     for (int64_t g = (int64_t)blockIdx.x * kSegWaves + w; g < groups; g += (int64_t)gridDim.x * kSegWaves) {
         int32_t u[kSteps], before;
         load_group(src, E, g, u, before);
-        mark_rows(off, rows, g, marks);
+        mark_rows(list, g, marks);
         int32_t last = quotient(div, before);
         const int32_t n = group_size(E, g);
 #pragma unroll
@@ -234,15 +305,15 @@ __global__ __launch_bounds__(kSegThreads) void k_count_runs(const int32_t *__res
     }
 }
 
-cagra_status launch_count_runs(const cagra_graph *g, int32_t N, int32_t k, const int32_t *rows, int32_t *seg_edges,
+cagra_status launch_count_runs(const cagra_graph *g, int32_t N, int32_t k, const RowList &rows, int32_t *seg_edges,
                                unsigned long long *runs, hipStream_t st) {
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_count_runs)) return a_;
     const int use_lds = k <= 16384 ? 1 : 0;
-    int64_t grid = ceil_div(edge_groups(g->E), kSegWaves);
+    int64_t grid = ceil_div(ceil_div(g->E, kGroupEdges), kSegWaves);
     if (grid > 2048) grid = 2048;  // a workgroup adds its histogram once
     const size_t lds = kTileEdges * sizeof(int32_t) + (use_lds ? (size_t)k * sizeof(int32_t) : 0);
-    k_count_runs<<<(unsigned)grid, kSegThreads, lds, st>>>(g->in_sources, g->in_offsets, rows, g->E, fast_div(N), k,
-                                                           use_lds, seg_edges, runs);
+    k_count_runs<<<(unsigned)grid, kSegThreads, lds, st>>>(g->in_sources, rows, g->E, fast_div(N), k, use_lds,
+                                                           seg_edges, runs);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -299,8 +370,7 @@ static size_t scatter_lds(int32_t k) {
 
 template <typename W, int KBITS>
 __global__ __launch_bounds__(kSegThreads, 4) void k_seg_scatter(
-    const int32_t *__restrict__ src, const int32_t *__restrict__ off, const int32_t *__restrict__ rows, int64_t E,
-    FastDiv div, int32_t N, int32_t k, int32_t chunks, int32_t chunk_tiles,
+    const int32_t *__restrict__ src, RowList list, int64_t E, FastDiv div, int32_t N, int32_t k, int32_t chunks, int32_t chunk_tiles,
     const int32_t *__restrict__ edge_base, const int32_t *__restrict__ run_base, FastDiv bdiv, int32_t B,
     W *__restrict__ edge_src, int32_t *__restrict__ row_ptr, int32_t *__restrict__ row_dst,
     uint16_t *__restrict__ row_dst_lo) {
@@ -344,8 +414,8 @@ __global__ __launch_bounds__(kSegThreads, 4) void k_seg_scatter(
             int32_t before;
             int32_t u[kSteps];
             load_group(src, E, g, u, before);
-            int32_t row1 = rows[g] + 1;  // 1 + the row of the edge before the step's first mark
-            mark_rows(off, rows, g, marks);
+            int32_t row1 = list.row[list.first[g]] + 1;  // 1 + the row of the edge before the step's first mark
+            mark_rows(list, g, marks);
             int32_t last = quotient(div, before);
             // kPart steps at a time: the first lane of each segment in a step
             // adds the step's edges and runs of that segment to the wave's count
@@ -489,22 +559,22 @@ static int32_t chunk_tiles_for(int64_t E) {
     return (int32_t)(t < 1 ? 1 : (t > kMaxChunkTiles ? kMaxChunkTiles : t));
 }
 
-size_t direct_ws_bytes(int64_t E, int32_t k) {
+size_t direct_ws_bytes(int32_t V, int64_t E, int32_t k) {
     const int64_t chunks = ceil_div(E, (int64_t)chunk_tiles_for(E) * kTileEdges);
     ArenaSize a;
-    a.take<int32_t>(edge_groups(E) + 1);
+    a.take<char>((int64_t)row_list_ws_bytes(V, E, kGroupEdges));
     a.take<int32_t>(chunks * k);
     a.take<int32_t>(chunks * k);
     return a.used + scan_add_ws_bytes(chunks * k) + 512;
 }
 
 template <typename W, int KBITS>
-static cagra_status launch_scatter_b(const cagra_graph *g, const cagra_segments *seg, const int32_t *rows,
+static cagra_status launch_scatter_b(const cagra_graph *g, const cagra_segments *seg, const RowList &rows,
                                      int32_t chunks, int32_t chunk_tiles, const int32_t *edge_base,
                                      const int32_t *run_base, hipStream_t st) {
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_seg_scatter<W, KBITS>)) return a_;
     k_seg_scatter<W, KBITS><<<(unsigned)chunks, kSegThreads, scatter_lds(seg->k), st>>>(
-        g->in_sources, g->in_offsets, rows, g->E, fast_div(seg->N), seg->N, seg->k, chunks, chunk_tiles, edge_base,
+        g->in_sources, rows, g->E, fast_div(seg->N), seg->N, seg->k, chunks, chunk_tiles, edge_base,
         run_base, fast_div(seg->B), seg->B, static_cast<W *>(seg->edge_src), seg->row_ptr, seg->row_dst,
         seg->row_dst_lo);
     CAGRA_LAUNCH_CHECK();
@@ -514,7 +584,7 @@ static cagra_status launch_scatter_b(const cagra_graph *g, const cagra_segments 
 // The segment ids' bits are compared one ballot each, unrolled; the width is
 // rounded up to one of a few.
 template <typename W>
-static cagra_status launch_scatter(const cagra_graph *g, const cagra_segments *seg, const int32_t *rows,
+static cagra_status launch_scatter(const cagra_graph *g, const cagra_segments *seg, const RowList &rows,
                                    int32_t chunks, int32_t chunk_tiles, const int32_t *edge_base,
                                    const int32_t *run_base, hipStream_t st) {
     static_assert(kDirectMaxSegments <= 1 << 11, "widest segment id");
@@ -531,16 +601,16 @@ cagra_status build_direct(const cagra_graph *g, const cagra_segments *seg, void 
     const int64_t chunks = ceil_div(E, (int64_t)tiles * kTileEdges), n = chunks * k;
     if (n > INT32_MAX) return fail(CAGRA_E_OVERFLOW, "segment count matrix too large");
     Arena ar{(char *)ws, ws_bytes, 0};
-    int32_t *rows = ar.take<int32_t>(edge_groups(E) + 1);
+    RowList rows;
+    cagra_status s;
+    if ((s = build_row_list(g->in_offsets, g->V, E, kGroupEdges, ar, &rows, st)) != CAGRA_OK) return s;
     int32_t *ce = ar.take<int32_t>(n), *cr = ar.take<int32_t>(n);
-    if (!rows || !ce || !cr) return fail(CAGRA_E_BUFFER, "build workspace too small (segment counts)");
+    if (!ce || !cr) return fail(CAGRA_E_BUFFER, "build workspace too small (segment counts)");
     char *tmp = ar.base + align_up(ar.used, 256);
     const size_t tmp_bytes = ws_bytes - align_up(ar.used, 256);
-    cagra_status s;
-    if ((s = launch_group_rows(g->in_offsets, g->V, E, rows, st)) != CAGRA_OK) return s;
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_seg_count)) return a_;
     k_seg_count<<<(unsigned)chunks, kSegThreads, kTileEdges * 4 + (size_t)k * 4, st>>>(
-        g->in_sources, g->in_offsets, rows, E, fast_div(seg->N), k, (int32_t)chunks, tiles * kSegWaves, ce, cr);
+        g->in_sources, rows, E, fast_div(seg->N), k, (int32_t)chunks, tiles * kSegWaves, ce, cr);
     CAGRA_LAUNCH_CHECK();
     if ((s = scan_add_exclusive(ce, ce, n, tmp, tmp_bytes, st)) != CAGRA_OK) return s;
     if ((s = scan_add_exclusive(cr, cr, n, tmp, tmp_bytes, st)) != CAGRA_OK) return s;

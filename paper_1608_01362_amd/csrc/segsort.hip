@@ -2,8 +2,7 @@
 // step of the Section 3.1 preprocessing, where the rows and the edges,
 // produced in destination order, are regrouped by the segment of their
 // sources while keeping destination order inside a segment (16-bit keys), and
-// the vertex order and edge relabelling of the Section 5 clustering (32- and
-// 64-bit keys, the latter without values).
+// the vertex order of the Section 5 clustering (32-bit keys).
 //
 // Least-significant-digit radix passes over digits of at most 8 bits. One
 // pass: every tile of kSortTile pairs counts its digits (k_sort_count), one
@@ -14,8 +13,6 @@
 // the waves) and writes each digit's run of the tile contiguously. The passes
 // are stable, so the last one leaves the pairs ordered by key and, for equal
 // keys, in input order.
-#include <type_traits>
-
 #include "radix.h"
 
 namespace cagra {
@@ -23,7 +20,6 @@ namespace cagra {
 constexpr int kSortThreads = 512;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
-static_assert(kSortTile == kRadixTile, "a tile is the unit of the published digit counts");
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kMaxDigitBits = 8;
 constexpr int kMaxDigits = 1 << kMaxDigitBits;
@@ -32,7 +28,8 @@ static_assert(kMaxDigits <= kSortThreads && kMaxDigits % 64 == 0, "digit tables 
 
 static int sort_passes(int bits) { return bits <= 0 ? 0 : (bits + kMaxDigitBits - 1) / kMaxDigitBits; }
 
-int sort_digit_bits(int bits) {
+// Digit width of every pass for keys below 2^bits.
+static int sort_digit_bits(int bits) {
     if (bits < 1) bits = 1;
     const int passes = sort_passes(bits);
     return (bits + passes - 1) / passes;
@@ -81,15 +78,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_count(const K *__restrict
 // over the digits orders the waves, and the pairs are placed in LDS by digit
 // and written out so that each digit's run of the tile lands contiguously at
 // offsets[digit * ntiles + tile].
-// With kLow the pass writes only (int32)(key & low_mask) to low_out.
-template <typename K, typename V, bool kLow = false>
+template <typename K, typename V>
 __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restrict__ kin, const V *__restrict__ vin,
                                                                int64_t n, int shift, int dbits, int32_t ntiles,
                                                                const int32_t *__restrict__ offsets,
-                                                               K *__restrict__ kout, V *__restrict__ vout,
-                                                               int32_t *__restrict__ low_out, K low_mask) {
-    constexpr bool kVals = !std::is_same<V, NoValue>::value;
-    using VS = typename std::conditional<kVals, V, char>::type;  // stored value type
+                                                               K *__restrict__ kout, V *__restrict__ vout) {
     constexpr int kWaveItems = kSortItems * 64;
     // The ranking's lane masks (per wave and digit, cleared again by each
     // digit's first lane) and, after them, the tile's keys in digit order share
@@ -99,7 +92,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
     __shared__ __attribute__((aligned(16))) unsigned char area[kKeyBytes > kMatchBytes ? kKeyBytes : kMatchBytes];
     K *sk = reinterpret_cast<K *>(area);
     unsigned long long *match = reinterpret_cast<unsigned long long *>(area);
-    __shared__ VS sv[kVals ? kSortTile : 1];
+    __shared__ V sv[kSortTile];
     // per-wave digit counts; after the scan, the first local slot of each wave's pairs of a digit
     __shared__ int32_t wbase[kSortWaves][kMaxDigits];
     __shared__ int32_t gofs[kMaxDigits];  // output index of a digit's pair = gofs[digit] + local slot
@@ -113,7 +106,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
     const int cnt = (int)(n - base < kSortTile ? n - base : kSortTile);
 
     K key[kSortItems];
-    VS val[kSortItems];
+    V val[kSortItems];
     int dig[kSortItems];
     int rank[kSortItems];
     // unconditional loads (lanes past the end read the tile's first pair), all
@@ -123,7 +116,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
         const int p = w * kWaveItems + j * 64 + lane;
         const int64_t i = base + (p < cnt ? p : 0);
         key[j] = kin[i];
-        if constexpr (kVals) val[j] = vin[i];
+        val[j] = vin[i];
     }
 #pragma unroll
     for (int j = 0; j < kSortItems; ++j) {
@@ -213,7 +206,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
         if (dig[j] < ndig) {
             const int32_t pos = wbase[w][dig[j]] + rank[j];
             sk[pos] = key[j];
-            if constexpr (kVals) sv[pos] = val[j];
+            sv[pos] = val[j];
         }
     }
     __syncthreads();
@@ -224,12 +217,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const K *__restri
         const K kk = sk[p];
         const int d = (int)((kk >> shift) & (K)mask);
         const int64_t g = (int64_t)gofs[d] + p;
-        if constexpr (kLow) {
-            low_out[g] = (int32_t)(kk & low_mask);
-        } else {
-            kout[g] = kk;
-            if constexpr (kVals) vout[g] = sv[p];
-        }
+        kout[g] = kk;
+        vout[g] = sv[p];
     }
 }
 
@@ -251,8 +240,7 @@ size_t seg_sort_ws_bytes(int64_t n, int bits, int value_bytes) { return sort_ws_
 template <typename K, typename V>
 cagra_status radix_sort_stable(const K *keys_in, const V *vals_in, K *keys_out, V *vals_out, int64_t n, int bits,
                                void *ws, size_t ws_bytes, hipStream_t st) {
-    constexpr bool kVals = !std::is_same<V, NoValue>::value;
-    constexpr int kValBytes = kVals ? (int)sizeof(V) : 0;
+    constexpr int kValBytes = (int)sizeof(V);
     if (n <= 0) return CAGRA_OK;
     if (bits < 1) bits = 1;
     if (bits > (int)(8 * sizeof(K))) return fail(CAGRA_E_CAPACITY, "sort keys wider than the key type");
@@ -265,7 +253,7 @@ cagra_status radix_sort_stable(const K *keys_in, const V *vals_in, K *keys_out, 
     const int32_t ntiles = (int32_t)ntiles64;
     Arena ar{(char *)ws, ws_bytes, 0};
     K *ktmp = reinterpret_cast<K *>(ar.take<char>(n * (int64_t)sizeof(K)));
-    V *vtmp = kVals ? reinterpret_cast<V *>(ar.take<char>(n * (int64_t)kValBytes)) : nullptr;
+    V *vtmp = reinterpret_cast<V *>(ar.take<char>(n * (int64_t)kValBytes));
     int32_t *counts = ar.take<int32_t>(((int64_t)1 << dbits) * ntiles);
     char *scan_ws = ar.base + align_up(ar.used, 256);
     const size_t scan_bytes = ws_bytes - align_up(ar.used, 256);
@@ -283,66 +271,10 @@ cagra_status radix_sort_stable(const K *keys_in, const V *vals_in, K *keys_out, 
         if (cagra_status s = scan_add_exclusive(counts, counts, ((int64_t)1 << dbits) * ntiles, scan_ws, scan_bytes,
                                                 st))
             return s;
-        k_sort_scatter<K, V><<<ntiles, kSortThreads, 0, st>>>(ks, vs, n, shift, dbits, ntiles, counts, kd, vd,
-                                                              nullptr, (K)0);
+        k_sort_scatter<K, V><<<ntiles, kSortThreads, 0, st>>>(ks, vs, n, shift, dbits, ntiles, counts, kd, vd);
         CAGRA_LAUNCH_CHECK();
         ks = kd;
         vs = vd;
-    }
-    return CAGRA_OK;
-}
-
-size_t sort_low32_ws_bytes(int64_t n, int bits) {
-    const int passes = sort_passes(bits < 1 ? 1 : bits);
-    if (passes == 0 || n <= 0) return 256;
-    const int64_t ncounts = ((int64_t)1 << sort_digit_bits(bits)) * ceil_div(n, kSortTile);
-    ArenaSize a;
-    a.take<int32_t>(ncounts);
-    return a.used + scan_add_ws_bytes(ncounts) + 512;
-}
-
-cagra_status radix_sort_low32(unsigned long long *keys, unsigned long long *tmp, const int32_t *pass0_counts,
-                              int32_t *low_out, int64_t n, int bits, int low_bits, void *ws, size_t ws_bytes,
-                              hipStream_t st) {
-    using K = unsigned long long;
-    if (n <= 0) return CAGRA_OK;
-    if (bits < 1) bits = 1;
-    if (bits > 64) return fail(CAGRA_E_CAPACITY, "sort keys wider than 64 bits");
-    if (low_bits < 1 || low_bits > 31) return fail(CAGRA_E_INVALID, "low_bits must be in [1, 31]");
-    const int passes = sort_passes(bits);
-    const int dbits = sort_digit_bits(bits);
-    if (ws_bytes < sort_low32_ws_bytes(n, bits)) return fail(CAGRA_E_BUFFER, "workspace too small (sort counts)");
-    const int64_t ntiles64 = ceil_div(n, kSortTile);
-    if (ntiles64 * ((int64_t)1 << dbits) > INT32_MAX) return fail(CAGRA_E_OVERFLOW, "sort too large");
-    const int32_t ntiles = (int32_t)ntiles64;
-    const int64_t ncounts = ((int64_t)1 << dbits) * ntiles;
-    Arena ar{(char *)ws, ws_bytes, 0};
-    int32_t *counts = ar.take<int32_t>(ncounts);
-    char *scan_ws = ar.base + align_up(ar.used, 256);
-    const size_t scan_bytes = ws_bytes - align_up(ar.used, 256);
-    const K low_mask = ((K)1 << low_bits) - 1;
-    const K *ks = keys;
-    for (int p = 0; p < passes; ++p) {
-        const bool last = p == passes - 1;
-        K *kd = (p & 1) ? keys : tmp;  // keys -> tmp -> keys -> ...
-        const int shift = p * dbits;
-        const int32_t *cin = counts;
-        if (p == 0 && pass0_counts) {
-            cin = pass0_counts;
-        } else {
-            k_sort_count<K><<<ntiles, kSortThreads, 0, st>>>(ks, n, shift, dbits, ntiles, counts);
-            CAGRA_LAUNCH_CHECK();
-        }
-        if (cagra_status s = scan_add_exclusive(cin, counts, ncounts, scan_ws, scan_bytes, st)) return s;
-        if (last) {
-            k_sort_scatter<K, NoValue, true><<<ntiles, kSortThreads, 0, st>>>(
-                ks, nullptr, n, shift, dbits, ntiles, counts, nullptr, nullptr, low_out, low_mask);
-        } else {
-            k_sort_scatter<K, NoValue><<<ntiles, kSortThreads, 0, st>>>(ks, nullptr, n, shift, dbits, ntiles, counts,
-                                                                        kd, nullptr, nullptr, (K)0);
-        }
-        CAGRA_LAUNCH_CHECK();
-        ks = kd;
     }
     return CAGRA_OK;
 }
@@ -363,8 +295,5 @@ template cagra_status seg_sort_pairs<unsigned long long>(const uint16_t *, const
                                                          hipStream_t);
 template cagra_status radix_sort_stable<uint32_t, int32_t>(const uint32_t *, const int32_t *, uint32_t *, int32_t *,
                                                            int64_t, int, void *, size_t, hipStream_t);
-template cagra_status radix_sort_stable<unsigned long long, NoValue>(const unsigned long long *, const NoValue *,
-                                                                     unsigned long long *, NoValue *, int64_t, int,
-                                                                     void *, size_t, hipStream_t);
 
 }  // namespace cagra
