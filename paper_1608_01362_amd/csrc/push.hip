@@ -23,8 +23,8 @@
 //
 // Pieces: a subgraph with E_s edges is cut into ceil(E_s / cap) runs of its
 // tiles (at most one per tile); cap is twice the mean subgraph size, capped so
-// that a small graph still yields about 1024 pieces. The plan is rebuilt by
-// one small kernel at the start of every call, so the workspace holds no
+// that a graph of few subgraphs still yields enough pieces to fill the chip. The plan is rebuilt by
+// one workgroup of the expand in every call, so the workspace holds no
 // state between calls.
 #include <math.h>
 
@@ -44,8 +44,9 @@ constexpr int kPushChunk = kWave * kPushEPT;
 constexpr int kPushStages = 4;                // chunk buffers of edge words per wave
 static_assert(kPushStages % 2 == 0, "the two value sets alternate with the chunk index inside one ring pass");
 constexpr int kPlanThreads = 1024;
-constexpr int kUpdSpan = 4096;                // vertices per update workgroup
 constexpr int kUpdThreads = 256;
+constexpr int kUpdItems = 4;                  // vertices per thread whose loads are in flight together
+constexpr int kUpdRound = kUpdThreads * kUpdItems;
 // expand items per XCD group (R-MAT 25 push iteration: 4 -> 2.814, 8 -> 2.790,
 // 16 -> 2.783 ms; fewer block boundaries cross XCDs)
 constexpr int32_t kExpandGroup = 16;
@@ -92,15 +93,23 @@ __device__ __forceinline__ PieceRange pieces_of(const int32_t *__restrict__ tile
     return r;
 }
 
-// One workgroup: pfirst[s] = first piece of subgraph s (pfirst[k] = piece
-// count), and per piece its first tile and subgraph; piece_tile[count] =
-// ntiles closes the last piece. Subgraphs without tiles get no piece.
-__global__ __launch_bounds__(kPlanThreads) void k_push_plan(const int32_t *__restrict__ tile_seg,
-                                                            const int32_t *__restrict__ tile_edge, int32_t ntiles,
-                                                            int32_t k, int64_t cap, int32_t *__restrict__ pfirst,
-                                                            int32_t *__restrict__ piece_tile,
-                                                            int32_t *__restrict__ piece_seg) {
-    __shared__ int32_t tmp[kPlanThreads / kWave];
+// The plan's inputs and outputs: pfirst[s] = first piece of subgraph s
+// (pfirst[k] = piece count), and per piece its first tile and subgraph;
+// piece_tile[count] = ntiles closes the last piece. Subgraphs without tiles get
+// no piece.
+struct PushPlan {
+    const int32_t *tile_seg, *tile_edge;
+    int32_t ntiles, k;
+    int64_t cap;
+    int32_t *pfirst, *piece_tile, *piece_seg;
+};
+
+// Makes the plan; the whole 1024-thread workgroup calls it.
+__device__ void push_plan(const PushPlan &P, int32_t *tmp /* kPlanThreads / kWave */) {
+    const int32_t *tile_seg = P.tile_seg, *tile_edge = P.tile_edge;
+    const int32_t ntiles = P.ntiles, k = P.k;
+    const int64_t cap = P.cap;
+    int32_t *pfirst = P.pfirst, *piece_tile = P.piece_tile, *piece_seg = P.piece_seg;
     const int32_t per = (k + kPlanThreads - 1) / kPlanThreads;
     const int32_t lo = threadIdx.x * per, hi = min(lo + per, k);
     int32_t sum = 0;
@@ -132,18 +141,32 @@ __global__ __launch_bounds__(kPlanThreads) void k_push_plan(const int32_t *__res
     }
 }
 
+// The plan alone, for graphs without edges (no expand launch to carry it).
+__global__ __launch_bounds__(kPlanThreads) void k_push_plan(PushPlan plan) {
+    __shared__ int32_t tmp[kPlanThreads / kWave];
+    push_plan(plan, tmp);
+}
+
 // ------------------------------------------------------------------ expand
 
 // vals[i] = x[row_dst[i]] for the rows of source block b, item j of its S
 // items (the block's rows flattened over subgraphs, cut into S equal parts).
+// The last workgroup makes the scatter's plan meanwhile: on its own it was a
+// launch of one workgroup, 10 us of search latency per iteration.
 template <bool WIDE>
 __global__ __launch_bounds__(kMergeThreads) void k_push_expand(const uint16_t *__restrict__ row_dst_lo,
                                                                const int32_t *__restrict__ block_ptr,
                                                                const int32_t *__restrict__ block_items,
                                                                const uint32_t *__restrict__ x, int32_t V, int32_t k,
-                                                               int32_t B, int32_t nb, uint32_t *__restrict__ vals) {
+                                                               int32_t B, int32_t nb, uint32_t *__restrict__ vals,
+                                                               PushPlan plan) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int32_t tmp[16];
+    static_assert(kPlanThreads == kMergeThreads, "the plan runs on a workgroup of the expand");
+    if (blockIdx.x == gridDim.x - 1) {  // uniform
+        push_plan(plan, tmp);
+        return;
+    }
     const int32_t total = block_items[nb];
     if ((int32_t)blockIdx.x >= total) return;  // the grid is the bound max_items
     // neighbouring blocks share the cache lines at the ends of their row ranges:
@@ -399,58 +422,111 @@ __global__ __launch_bounds__(kPushThreads) void k_push_scatter(
 
 // ------------------------------------------------------------------ update
 
+// An update workgroup covers `span` vertices, kUpdRound at a time. A vertex's
+// slots are one dependent load each, so a thread takes kUpdItems vertices
+// together: one vertex at a time, 1,024 workgroups, took 97 us for 4 M vertices
+// with about five slots each (230 MB), this form 54 us, and 20 us with the one or
+// two slots that push_piece_cap leaves.
+
+// Combine of the pieces' slots of kUpdItems vertices: v[j] of segment-local
+// index at[j] over pieces [p0[j], p1[j]).
+template <typename T, class F>
+__device__ __forceinline__ void fold_slots(const T *__restrict__ slots, int32_t N, const int32_t (&p0)[kUpdItems],
+                                           const int32_t (&p1)[kUpdItems], const int32_t (&at)[kUpdItems],
+                                           T (&acc)[kUpdItems], F combine) {
+    int32_t most = 0;
+#pragma unroll
+    for (int j = 0; j < kUpdItems; ++j) most = max(most, p1[j] - p0[j]);
+    for (int32_t q = 0; q < most; q += 2) {
+        T x[2][kUpdItems];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < kUpdItems; ++j) {  // pieces past the vertex's last read its first again, unused
+                const int32_t p = p0[j] + q + u;
+                x[u][j] = p0[j] < p1[j] ? slots[(int64_t)(p < p1[j] ? p : p0[j]) * N + at[j]] : T(0);
+            }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < kUpdItems; ++j) acc[j] = p0[j] + q + u < p1[j] ? combine(acc[j], x[u][j]) : acc[j];
+    }
+}
+
 __global__ __launch_bounds__(kUpdThreads) void k_push_pr_update(
     const unsigned long long *__restrict__ slots, const int32_t *__restrict__ pfirst, int32_t V, int32_t N,
-    const float *__restrict__ rank_in, const int32_t *__restrict__ outdeg, const double *__restrict__ scalars_in,
-    double damping, float *__restrict__ rank_out, float *__restrict__ contrib_out, double *__restrict__ blk) {
-    __shared__ double red[kUpdThreads / kWave];
+    int32_t span, const float *__restrict__ rank_in, const int32_t *__restrict__ outdeg,
+    const double *__restrict__ scalars_in, double damping, float *__restrict__ rank_out,
+    float *__restrict__ contrib_out, double *__restrict__ blk) {
+    __shared__ double red[4 * kUpdThreads / kWave];
     const double dd = damping;
     const double base = (1.0 - dd) / (double)V + dd * scalars_in[0] / (double)V;
-    const int64_t lo = (int64_t)blockIdx.x * kUpdSpan;
-    const int64_t hi = lo + kUpdSpan < V ? lo + kUpdSpan : V;
-    double dang = 0.0, res = 0.0, mass = 0.0;
-    for (int64_t v = lo + threadIdx.x; v < hi; v += kUpdThreads) {
-        const int32_t s = (int32_t)(v / N);
-        const int64_t i = v - (int64_t)s * N;
-        unsigned long long a = 0ull;
-        for (int32_t p = pfirst[s]; p < pfirst[s + 1]; ++p) a += slots[(int64_t)p * N + i];
-        const double sum = (double)(long long)a * kFixInv;
-        const float r = (float)(base + dd * sum);
-        rank_out[v] = r;
-        const int32_t od = outdeg[v];
-        contrib_out[v] = od > 0 ? r / (float)od : 0.0f;
-        if (od == 0) dang += (double)r;
-        res += fabs((double)r - (double)rank_in[v]);
-        mass += (double)r;
+    const int64_t lo = (int64_t)blockIdx.x * span;
+    const int64_t hi = lo + span < V ? lo + span : V;
+    double part[4] = {0.0, 0.0, 0.0, 0.0};  // dangling mass, L1 residual, mass
+    for (int64_t v0 = lo + threadIdx.x; v0 < hi; v0 += kUpdRound) {
+        int32_t p0[kUpdItems], p1[kUpdItems], at[kUpdItems], od[kUpdItems];
+        float rin[kUpdItems];
+        unsigned long long a[kUpdItems];
+#pragma unroll
+        for (int j = 0; j < kUpdItems; ++j) {  // vertices past the span read its first again, unused
+            const int32_t v = (int32_t)(v0 + j * kUpdThreads < hi ? v0 + j * kUpdThreads : v0);
+            const int32_t s = v / N;
+            at[j] = v - s * N;
+            p0[j] = pfirst[s];
+            p1[j] = pfirst[s + 1];
+            od[j] = outdeg[v];
+            rin[j] = rank_in[v];
+            a[j] = 0ull;
+        }
+        fold_slots(slots, N, p0, p1, at, a, [](unsigned long long x, unsigned long long y) { return x + y; });
+#pragma unroll
+        for (int j = 0; j < kUpdItems; ++j) {
+            const int64_t v = v0 + j * kUpdThreads;
+            if (v >= hi) break;
+            const float r = (float)(base + dd * ((double)(long long)a[j] * kFixInv));
+            rank_out[v] = r;
+            contrib_out[v] = od[j] > 0 ? r / (float)od[j] : 0.0f;
+            if (od[j] == 0) part[0] += (double)r;
+            part[1] += fabs((double)r - (double)rin[j]);
+            part[2] += (double)r;
+        }
     }
-    dang = block_sum_f64<kUpdThreads>(dang, red);
-    res = block_sum_f64<kUpdThreads>(res, red);
-    mass = block_sum_f64<kUpdThreads>(mass, red);
-    if (threadIdx.x == 0) {
-        blk[(int64_t)blockIdx.x * 4 + 0] = dang;
-        blk[(int64_t)blockIdx.x * 4 + 1] = res;
-        blk[(int64_t)blockIdx.x * 4 + 2] = mass;
-        blk[(int64_t)blockIdx.x * 4 + 3] = 0.0;
-    }
+    block_sum4_f64<kUpdThreads>(part, red);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 4; ++c) blk[(int64_t)blockIdx.x * 4 + c] = part[c];
 }
 
 __global__ __launch_bounds__(kUpdThreads) void k_push_lp_update(const int32_t *__restrict__ slots,
                                                                 const int32_t *__restrict__ pfirst, int32_t V,
-                                                                int32_t N, const int32_t *__restrict__ labels_in,
+                                                                int32_t N, int32_t span,
+                                                                const int32_t *__restrict__ labels_in,
                                                                 int32_t *__restrict__ labels_out,
                                                                 int32_t *__restrict__ blk) {
     __shared__ int32_t red[kUpdThreads / kWave];
-    const int64_t lo = (int64_t)blockIdx.x * kUpdSpan;
-    const int64_t hi = lo + kUpdSpan < V ? lo + kUpdSpan : V;
+    const int64_t lo = (int64_t)blockIdx.x * span;
+    const int64_t hi = lo + span < V ? lo + span : V;
     int32_t changed = 0;
-    for (int64_t v = lo + threadIdx.x; v < hi; v += kUpdThreads) {
-        const int32_t s = (int32_t)(v / N);
-        const int64_t i = v - (int64_t)s * N;
-        const int32_t old = labels_in[v];
-        int32_t m = old;
-        for (int32_t p = pfirst[s]; p < pfirst[s + 1]; ++p) m = min(m, slots[(int64_t)p * N + i]);
-        labels_out[v] = m;
-        changed += m != old ? 1 : 0;
+    for (int64_t v0 = lo + threadIdx.x; v0 < hi; v0 += kUpdRound) {
+        int32_t p0[kUpdItems], p1[kUpdItems], at[kUpdItems], old[kUpdItems], m[kUpdItems];
+#pragma unroll
+        for (int j = 0; j < kUpdItems; ++j) {  // vertices past the span read its first again, unused
+            const int32_t v = (int32_t)(v0 + j * kUpdThreads < hi ? v0 + j * kUpdThreads : v0);
+            const int32_t s = v / N;
+            at[j] = v - s * N;
+            p0[j] = pfirst[s];
+            p1[j] = pfirst[s + 1];
+            old[j] = labels_in[v];
+            m[j] = old[j];
+        }
+        fold_slots(slots, N, p0, p1, at, m, [](int32_t x, int32_t y) { return min(x, y); });
+#pragma unroll
+        for (int j = 0; j < kUpdItems; ++j) {
+            const int64_t v = v0 + j * kUpdThreads;
+            if (v >= hi) break;
+            labels_out[v] = m[j];
+            changed += m[j] != old[j] ? 1 : 0;
+        }
     }
     for (int d = 32; d >= 1; d >>= 1) changed += __shfl_down(changed, d, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = changed;
@@ -464,15 +540,27 @@ __global__ __launch_bounds__(kUpdThreads) void k_push_lp_update(const int32_t *_
 
 // ------------------------------------------------------------------ host side
 
+// Edges per piece. Every piece is a workgroup and leaves a slot of 8 N bytes, so
+// pieces beyond what the chip runs at once cost slot traffic and give no
+// parallelism: about three quarters of the resident workgroups are asked for
+// (each subgraph rounds its share up). One workgroup fills a CU's LDS when
+// N > 10,240, two its waves otherwise. Step time, us, with E / 1024 and E / 192
+// edges per piece (N = 20,480): V = 4 M 254 and 184, V = 1 M 120 and 88;
+// N = 10,000, V = 2 M, E / 1024, / 384, / 192: 112, 99, 111.
+constexpr int kChipCus = 256;
 int64_t push_piece_cap(const cagra_segments *seg) {
+    const int resident = kChipCus * ((size_t)seg->N * 16 <= CAGRA_LDS_BYTES ? 2 : 1);
     int64_t cap = ceil_div(2 * seg->E, seg->k);
-    const int64_t fill = ceil_div(seg->E, 1024);
+    const int64_t fill = ceil_div(seg->E, resident * 3 / 4);
     if (fill < cap) cap = fill;
     if (cap < 4096) cap = 4096;
     return cap;
 }
 int64_t push_max_pieces(const cagra_segments *seg) { return (int64_t)seg->k + ceil_div(seg->E, push_piece_cap(seg)); }
-int32_t push_update_blocks(int32_t V) { return (int32_t)ceil_div(V, kUpdSpan); }
+// Vertices per update workgroup: one round of its threads, more on large graphs
+// so that the reduction of the workgroups' sums stays short.
+static int32_t push_update_span(int32_t V) { return V > (1 << 23) ? 4 * kUpdRound : kUpdRound; }
+int32_t push_update_blocks(int32_t V) { return (int32_t)ceil_div(V, push_update_span(V)); }
 
 // LDS of the expand kernel: staged block values and the block's range starts
 // and prefix (plus the static scan scratch).
@@ -535,22 +623,24 @@ static cagra_status launch_scatter(const cagra_segments *seg, const void *vals, 
 template <class PO>
 static cagra_status push_edges(const cagra_segments *seg, const void *x, void *vals, const PushWs &ws,
                                hipStream_t st) {
-    k_push_plan<<<1, kPlanThreads, 0, st>>>(seg->tile_seg, seg->tile_edge, seg->ntiles, seg->k, push_piece_cap(seg),
-                                           ws.pfirst, ws.piece_tile, ws.piece_seg);
-    CAGRA_LAUNCH_CHECK();
+    const PushPlan plan = {seg->tile_seg, seg->tile_edge, seg->ntiles, seg->k,      push_piece_cap(seg),
+                           ws.pfirst,     ws.piece_tile,  ws.piece_seg};
     if (seg->Q > 0) {
         const size_t lds = push_expand_lds_bytes(seg->B, seg->k);
         const bool wide = seg->Q < (int64_t)kWave * seg->k * seg->nb;
         if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand<true>)) return a_;
         if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand<false>)) return a_;
         if (wide)
-            k_push_expand<true><<<seg->max_items, kMergeThreads, lds, st>>>(
+            k_push_expand<true><<<seg->max_items + 1, kMergeThreads, lds, st>>>(
                 seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
-                seg->B, seg->nb, static_cast<uint32_t *>(vals));
+                seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
         else
-            k_push_expand<false><<<seg->max_items, kMergeThreads, lds, st>>>(
+            k_push_expand<false><<<seg->max_items + 1, kMergeThreads, lds, st>>>(
                 seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
-                seg->B, seg->nb, static_cast<uint32_t *>(vals));
+                seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
+        CAGRA_LAUNCH_CHECK();
+    } else {
+        k_push_plan<<<1, kPlanThreads, 0, st>>>(plan);
         CAGRA_LAUNCH_CHECK();
     }
     return launch_scatter<PO>(seg, vals, ws, st);
@@ -564,8 +654,9 @@ cagra_status launch_pr_push(const cagra_graph *g, const cagra_segments *seg, dou
     if (cagra_status s = push_edges<PushSum>(seg, contrib_in, vals, ws, st)) return s;
     const int32_t nblk = push_update_blocks(seg->V);
     k_push_pr_update<<<nblk, kUpdThreads, 0, st>>>(static_cast<const unsigned long long *>(ws.slots), ws.pfirst,
-                                                   seg->V, seg->N, rank_in, g->out_degree, scalars_in, damping,
-                                                   rank_out, contrib_out, static_cast<double *>(ws.blk));
+                                                   seg->V, seg->N, push_update_span(seg->V), rank_in,
+                                                   g->out_degree, scalars_in, damping, rank_out, contrib_out,
+                                                   static_cast<double *>(ws.blk));
     CAGRA_LAUNCH_CHECK();
     return launch_reduce4(static_cast<const double *>(ws.blk), nblk, scalars_out, scalars_in, st);
 }
@@ -577,7 +668,7 @@ cagra_status launch_lp_push(const cagra_segments *seg, const int32_t *labels_in,
     if (cagra_status s = push_edges<PushMin>(seg, labels_in, vals, ws, st)) return s;
     const int32_t nblk = push_update_blocks(seg->V);
     k_push_lp_update<<<nblk, kUpdThreads, 0, st>>>(static_cast<const int32_t *>(ws.slots), ws.pfirst, seg->V, seg->N,
-                                                   labels_in, labels_out, static_cast<int32_t *>(ws.blk));
+                                                   push_update_span(seg->V), labels_in, labels_out, static_cast<int32_t *>(ws.blk));
     CAGRA_LAUNCH_CHECK();
     return launch_reduce_i32(static_cast<const int32_t *>(ws.blk), nblk, changed_out, st);
 }
