@@ -626,7 +626,7 @@ cagra_status cagra_ppr_solve(const cagra_graph *g, const cagra_segments *seg, co
  * vectors of all graphs live in shared pools, graph i's at the running offset
  * of the earlier graphs' V (rank, contrib) and Q (partial). Persistent
  * workgroups stride over the global tile and merge-block lists, so each
- * iteration of all graphs is three kernel launches without host
+ * iteration of all graphs is two kernel launches without host
  * synchronization (capturable into one HIP graph).
  */
 typedef struct {

@@ -72,6 +72,10 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
                              int32_t contrib_type,
                              const float *rank_in, const double *scalars_in, const float *partial, float *rank_out,
                              void *contrib_out, double *scalars_out, void *ws, hipStream_t st);
+cagra_status launch_pagerank_iter(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
+                                  int32_t contrib_type, const float *rank_in, const void *contrib_in,
+                                  const double *scalars_in, float *partial, float *rank_out, void *contrib_out,
+                                  double *scalars_out, void *ws, hipStream_t st);
 cagra_status launch_merge_lp(const cagra_segments *seg, const int32_t *labels_in, const int32_t *partial,
                              int32_t *labels_out, int32_t *changed_out, void *ws, hipStream_t st);
 
@@ -431,9 +435,8 @@ cagra_status cagra_pagerank_iter(const cagra_graph *g, const cagra_segments *seg
                                  partial, rank_out, contrib_out, scalars_out)) != CAGRA_OK)
         return s;
     if ((s = check_pagerank(g, seg, damping, contrib_type, workspace_bytes, workspace)) != CAGRA_OK) return s;
-    if ((s = launch_gather(seg, CAGRA_SUM_F32, contrib_type, contrib_in, partial, stream)) != CAGRA_OK) return s;
-    return launch_merge_pr(g, seg, damping, restart_vertex, contrib_type, rank_in, scalars_in, partial, rank_out,
-                           contrib_out, scalars_out, workspace, stream);
+    return launch_pagerank_iter(g, seg, damping, restart_vertex, contrib_type, rank_in, contrib_in, scalars_in, partial,
+                                rank_out, contrib_out, scalars_out, workspace, stream);
 }
 
 // Reads the four FP64 scalars of one iteration back to the host (synchronizes).
@@ -480,9 +483,8 @@ struct PageRankSolveOps {
             ++at.iters;
             return CAGRA_OK;
         }
-        if ((s = launch_gather(seg, CAGRA_SUM_F32, at.ct, contrib[c], partial, st)) != CAGRA_OK) return s;
-        if ((s = launch_merge_pr(g, seg, p->damping, p->restart_vertex, at.ct, rank[c], sc[c], partial, rank[1 - c],
-                                 contrib[1 - c], sc[1 - c], ws, st)) != CAGRA_OK)
+        if ((s = launch_pagerank_iter(g, seg, p->damping, p->restart_vertex, at.ct, rank[c], contrib[c], sc[c], partial,
+                                      rank[1 - c], contrib[1 - c], sc[1 - c], ws, st)) != CAGRA_OK)
             return s;
         at.cur = 1 - c;
         ++at.iters;

@@ -336,9 +336,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(
     const W *__restrict__ edge_src, int64_t E, int64_t Q, const int32_t *__restrict__ tile_edge,
     const int32_t *__restrict__ tile_seg, const int32_t *__restrict__ span_row, const VT *__restrict__ values,
     int32_t V, int32_t N, int32_t ntiles, typename Op::T *__restrict__ partial,
-    const uint32_t *__restrict__ seg_active) {
+    const uint32_t *__restrict__ seg_active, unsigned long long *__restrict__ clear) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     (void)E;
+    // the counter of the merge that follows on the stream (null: none)
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
     gather_tile<Op, VT, STAGED, W, DEPTH>(edge_src, Q, tile_edge, tile_seg, span_row, values, V, N,
                                           xcd_remap(blockIdx.x, ntiles), partial, smem, seg_active);
 }
@@ -346,8 +348,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(
 // Persistent form over many graphs: workgroups stride over a global tile list.
 __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc *__restrict__ desc,
                                                                  const int32_t *__restrict__ tile_graph,
-                                                                 int64_t total_tiles, int parity) {
+                                                                 int64_t total_tiles, int parity,
+                                                                 unsigned long long *__restrict__ tickets, int32_t ngraphs) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // the counters of the merge that follows on the stream
+    if (blockIdx.x == 0)
+        for (int32_t i = threadIdx.x; i < ngraphs; i += kGatherThreads) tickets[i] = 0ull;
     for (int64_t gt = blockIdx.x; gt < total_tiles; gt += gridDim.x) {
         __syncthreads();  // LDS reuse across tiles
         const int gi = tile_graph[gt];
@@ -359,18 +365,18 @@ __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc
 }
 
 cagra_status launch_multi_gather(const MultiDesc *desc, const int32_t *tile_graph, int64_t total_tiles, int parity,
-                                 int grid, hipStream_t st) {
+                                 unsigned long long *tickets, int32_t ngraphs, int grid, hipStream_t st) {
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_multi_gather)) return a_;
     if (total_tiles == 0) return CAGRA_OK;
-    k_multi_gather<<<grid, kGatherThreads, kStageBytes + CAGRA_STAGE_BYTES, st>>>(desc, tile_graph, total_tiles,
-                                                                                   parity);
+    k_multi_gather<<<grid, kGatherThreads, kStageBytes + CAGRA_STAGE_BYTES, st>>>(
+        desc, tile_graph, total_tiles, parity, tickets, ngraphs);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
 
 template <class Op, typename VT, bool STAGED, typename W>
 static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values, typename Op::T *partial,
-                                    const uint32_t *seg_active, hipStream_t st) {
+                                    const uint32_t *seg_active, unsigned long long *clear, hipStream_t st) {
     if (seg->ntiles == 0) return CAGRA_OK;
     auto kern = k_gather<Op, VT, STAGED, W, kStagesDefault>;
     if constexpr (STAGED && sizeof(W) == 2)
@@ -379,7 +385,7 @@ static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values,
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
     kern<<<seg->ntiles, kGatherThreads, lds, st>>>(static_cast<const W *>(seg->edge_src), seg->E, seg->Q,
                                                   seg->tile_edge, seg->tile_seg, seg->tile_span_row, values, seg->V,
-                                                  seg->N, seg->ntiles, partial, seg_active);
+                                                  seg->N, seg->ntiles, partial, seg_active, clear);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -388,15 +394,15 @@ static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values,
 // words; larger staged ones (BF16 values) and all unstaged ones use 32-bit words.
 template <class Op, typename VT, bool STAGED>
 static cagra_status launch_gather_t(const cagra_segments *seg, const VT *values, typename Op::T *partial,
-                                    const uint32_t *seg_active, hipStream_t st) {
+                                    const uint32_t *seg_active, unsigned long long *clear, hipStream_t st) {
     if constexpr (STAGED) {
-        if (edge16(seg->N)) return launch_gather_w<Op, VT, true, uint16_t>(seg, values, partial, seg_active, st);
+        if (edge16(seg->N)) return launch_gather_w<Op, VT, true, uint16_t>(seg, values, partial, seg_active, clear, st);
         if constexpr (sizeof(VT) == 2)
-            return launch_gather_w<Op, VT, true, uint32_t>(seg, values, partial, seg_active, st);
+            return launch_gather_w<Op, VT, true, uint32_t>(seg, values, partial, seg_active, clear, st);
         return fail(CAGRA_E_INVALID, "internal: staged segment of %d vertices with 32-bit edge words", seg->N);
     } else {
         if (edge16(seg->N)) return fail(CAGRA_E_INVALID, "internal: unstaged segment of %d vertices", seg->N);
-        return launch_gather_w<Op, VT, false, uint32_t>(seg, values, partial, seg_active, st);
+        return launch_gather_w<Op, VT, false, uint32_t>(seg, values, partial, seg_active, clear, st);
     }
 }
 
@@ -406,27 +412,45 @@ bool gather_staged(int32_t N, int32_t value_type) {
     return (size_t)N * bytes <= CAGRA_STAGE_BYTES;
 }
 
-cagra_status launch_gather_active(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
-                                  void *partial, const uint32_t *seg_active, hipStream_t st) {
+static cagra_status launch_gather_any(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
+                                      void *partial, const uint32_t *seg_active, unsigned long long *clear, hipStream_t st) {
     const bool staged = gather_staged(seg->N, value_type);
     if (op == CAGRA_SUM_F32 && value_type == CAGRA_F32) {
-        return staged ? launch_gather_t<OpSum, float, true>(seg, (const float *)values, (float *)partial, seg_active, st)
-                      : launch_gather_t<OpSum, float, false>(seg, (const float *)values, (float *)partial, seg_active, st);
+        return staged ? launch_gather_t<OpSum, float, true>(seg, (const float *)values, (float *)partial, seg_active,
+                                                        clear, st)
+                      : launch_gather_t<OpSum, float, false>(seg, (const float *)values, (float *)partial, seg_active,
+                                                        clear, st);
     }
     if (op == CAGRA_SUM_F32 && value_type == CAGRA_BF16) {
-        return staged ? launch_gather_t<OpSum, uint16_t, true>(seg, (const uint16_t *)values, (float *)partial, seg_active, st)
-                      : launch_gather_t<OpSum, uint16_t, false>(seg, (const uint16_t *)values, (float *)partial, seg_active, st);
+        return staged ? launch_gather_t<OpSum, uint16_t, true>(seg, (const uint16_t *)values, (float *)partial, seg_active,
+                                                        clear, st)
+                      : launch_gather_t<OpSum, uint16_t, false>(seg, (const uint16_t *)values, (float *)partial, seg_active,
+                                                        clear, st);
     }
     if (op == CAGRA_MIN_I32 && value_type == CAGRA_I32) {
-        return staged ? launch_gather_t<OpMin, int32_t, true>(seg, (const int32_t *)values, (int32_t *)partial, seg_active, st)
-                      : launch_gather_t<OpMin, int32_t, false>(seg, (const int32_t *)values, (int32_t *)partial, seg_active, st);
+        return staged ? launch_gather_t<OpMin, int32_t, true>(seg, (const int32_t *)values, (int32_t *)partial, seg_active,
+                                                        clear, st)
+                      : launch_gather_t<OpMin, int32_t, false>(seg, (const int32_t *)values, (int32_t *)partial, seg_active,
+                                                        clear, st);
     }
     return fail(CAGRA_E_INVALID, "unsupported gather op %d / value type %d", op, value_type);
 }
 
+cagra_status launch_gather_active(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
+                                  void *partial, const uint32_t *seg_active, hipStream_t st) {
+    return launch_gather_any(seg, op, value_type, values, partial, seg_active, nullptr, st);
+}
+
 cagra_status launch_gather(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
                            void *partial, hipStream_t st) {
-    return launch_gather_active(seg, op, value_type, values, partial, nullptr, st);
+    return launch_gather_any(seg, op, value_type, values, partial, nullptr, nullptr, st);
+}
+
+// The gather of an iteration: also sets *clear to 0 for the merge that follows
+// on the stream. Needs ntiles > 0.
+cagra_status launch_gather_clear(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
+                                 void *partial, unsigned long long *clear, hipStream_t st) {
+    return launch_gather_any(seg, op, value_type, values, partial, nullptr, clear, st);
 }
 
 }  // namespace cagra

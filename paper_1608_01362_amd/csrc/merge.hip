@@ -24,10 +24,17 @@
 
 namespace cagra {
 
+cagra_status launch_gather(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
+                           void *partial, hipStream_t st);
+cagra_status launch_gather_clear(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
+                                 void *partial, unsigned long long *clear, hipStream_t st);
+
 // Dynamic LDS of the fused merges; kFusedStaticLds covers their static arrays.
 constexpr size_t kFusedStaticLds = 256;
+// At least what the last block's sums need (reduce4_rows).
 size_t merge_fused_lds_bytes(int32_t B, int32_t k, int acc_bytes) {
-    return align_up((size_t)B * acc_bytes, 16) + (size_t)(2 * (int64_t)k + 2) * sizeof(int32_t) + 64;
+    const size_t n = align_up((size_t)B * acc_bytes, 16) + (size_t)(2 * (int64_t)k + 2) * sizeof(int32_t) + 64;
+    return n < 192 ? 192 : n;
 }
 size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes) {
     return merge_fused_lds_bytes(B, k, acc_bytes) + kFusedStaticLds;
@@ -339,6 +346,90 @@ __device__ __forceinline__ void stream_block(const uint16_t *__restrict__ dlo, c
     }
 }
 
+// ---- sums over the workgroups, taken by the last one to finish
+//
+// A reduction of the blocks' FP64 partial sums as a launch of its own costs 3 us
+// and a launch gap per iteration, a seventh of a small graph's. Where there are
+// few blocks they instead count themselves off and the last one adds the partials, in the same
+// fixed order. The partials are exchanged (not stored) at device scope, and a
+// workgroup counts itself off after its exchanges have returned, so every
+// partial is in place at the point all XCDs share before its count is; the last
+// workgroup reads them there, past its own L2.
+constexpr int kReduceThreads = 256;
+
+// Writes a partial sum for the last workgroup to read; returns when it is in place.
+__device__ __forceinline__ void publish4(double *blk_out, const double (&v)[4]) {
+    unsigned long long old[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        old[c] = __hip_atomic_exchange(reinterpret_cast<unsigned long long *>(blk_out + c),
+                                       (unsigned long long)__double_as_longlong(v[c]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) asm volatile("" ::"v"(old[c]) : "memory");  // the exchanges have returned
+}
+
+// out[c] = sum of n rows of 4 partials by the workgroup's first kReduceThreads
+// threads, in an order that depends on n alone; carry[3] is added to out[3].
+// SHARED: rows published by running workgroups. BATCH: rows per thread loaded
+// together (the order of the sum is the same). red: 4 * kReduceThreads / 64
+// doubles of LDS. The whole workgroup calls it.
+template <bool SHARED, int BATCH = 4>
+__device__ __forceinline__ void reduce4_rows(const double *__restrict__ blk, int32_t n, double *__restrict__ out,
+                                             const double *__restrict__ carry, double *red) {
+    auto row = [&](int64_t i) -> double {
+        if constexpr (SHARED)
+            return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long *>(blk + i),
+                                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        else return blk[i];
+    };
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    if (threadIdx.x < kReduceThreads) {
+        int32_t j = threadIdx.x;
+        if constexpr (BATCH > 1)
+            for (; j + (BATCH - 1) * kReduceThreads < n; j += BATCH * kReduceThreads) {
+                double x[BATCH][4];
+#pragma unroll
+                for (int r = 0; r < BATCH; ++r)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[r][c] = row((int64_t)(j + r * kReduceThreads) * 4 + c);
+#pragma unroll
+                for (int r = 0; r < BATCH; ++r)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) a[c] += x[r][c];
+            }
+        for (; j < n; j += kReduceThreads) {
+            double x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = row((int64_t)j * 4 + c);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] += x[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            for (int d = 32; d >= 1; d >>= 1) a[c] += __shfl_down(a[c], d, 64);
+        if ((threadIdx.x & 63) == 0)
+            for (int c = 0; c < 4; ++c) red[c * (kReduceThreads / 64) + (threadIdx.x >> 6)] = a[c];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int c = threadIdx.x;
+        double t = 0.0;
+        for (int i = 0; i < kReduceThreads / 64; ++i) t += red[c * (kReduceThreads / 64) + i];
+        out[c] = c == 3 && carry ? t + carry[3] : t;
+    }
+}
+
+// Counts a finished workgroup off; true (in every thread) for the last of n.
+// flag: an int of LDS. Called after publish4 by the same thread.
+__device__ __forceinline__ bool last_of(unsigned long long *ticket, int32_t n, int32_t *flag) {
+    if (threadIdx.x == 0)
+        *flag = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                (unsigned long long)(n - 1);
+    __syncthreads();
+    return *flag != 0;
+}
+
 constexpr int kEpiBatch = 8;  // vertices per thread whose loads are in flight together
 
 // PageRank vertex update of block b from its exact sums acc (LDS, int64 fixed
@@ -398,13 +489,66 @@ __device__ __forceinline__ void pr_epilogue(const unsigned long long *acc, int32
     }
 }
 
+template <int EPI>
+__device__ __forceinline__ void load_vertices(const float *__restrict__ rank_in, const int32_t *__restrict__ outdeg,
+                                              int64_t vb, int32_t nv, int i0, float (&rin)[EPI], int32_t (&odv)[EPI]) {
+#pragma unroll
+    for (int u = 0; u < EPI; ++u) {
+        const int i = i0 + u * kMergeThreads;
+        rin[u] = i < nv ? rank_in[vb + i] : 0.0f;
+        odv[u] = i < nv ? outdeg[vb + i] : 0;
+    }
+}
+
+// The same for the blocks of a small graph, alone on their CUs: the inputs of
+// their first kMergeThreads * EPI vertices (rin, odv, loaded before the buffer
+// entries) and the dangling mass are at hand, which takes one round trip to
+// memory out of the chain, and the sums go to the last block (publish4).
+template <bool BF16OUT, int EPI>
+__device__ __forceinline__ void pr_epilogue_small(const unsigned long long *acc, int32_t V, int64_t vb, int32_t nv,
+                                                  const float *__restrict__ rank_in,
+                                                  const int32_t *__restrict__ outdeg, double dangling, double damping,
+                                                  int32_t seed, float *__restrict__ rank_out,
+                                                  void *__restrict__ contrib_out, double *__restrict__ blk_out,
+                                                  double am, double *red, float (&rin)[EPI], int32_t (&odv)[EPI]) {
+    const double dd = damping;
+    const double base = seed < 0 ? (1.0 - dd) / (double)V + dd * dangling / (double)V : 0.0;
+    const double sbase = (1.0 - dd) + dd * dangling;
+    double dang = 0.0, res = 0.0, mass = 0.0;
+    for (int i0 = threadIdx.x; i0 < nv; i0 += kMergeThreads * EPI) {
+        if (i0 >= kMergeThreads * EPI) load_vertices<EPI>(rank_in, outdeg, vb, nv, i0, rin, odv);
+#pragma unroll
+        for (int u = 0; u < EPI; ++u) {
+            const int i = i0 + u * kMergeThreads;
+            if (i >= nv) break;
+            const int64_t v = vb + i;
+            const double sum = (double)(long long)acc[i] * kFixInv;
+            const float r = (float)((v == seed ? sbase : base) + dd * sum);
+            rank_out[v] = r;
+            const int32_t od = odv[u];
+            const float c = od > 0 ? r / (float)od : 0.0f;
+            if (BF16OUT) reinterpret_cast<uint16_t *>(contrib_out)[v] = f32_to_bf16(c);
+            else reinterpret_cast<float *>(contrib_out)[v] = c;
+            if (od == 0) dang += (double)r;
+            res += fabs((double)r - (double)rin[u]);
+            mass += (double)r;
+        }
+    }
+    double v4[4] = {dang, res, mass, am};
+    block_sum4_f64<kMergeThreads>(v4, red);
+    if (threadIdx.x == 0) {
+        v4[3] = range_flag(v4[3]);
+        publish4(blk_out, v4);
+    }
+}
+
 // Item j of the S items of block b: the block's entries (flattened over
 // subgraphs) [P*j/S, P*(j+1)/S). With S == 1 the item is the whole block and
 // the vertex update follows at once. Otherwise the item stores its exact int64
 // sums in its own slot of the workspace and the absolute sum of its buffer
 // values in *item_abs, and k_merge_pr_finish adds the S slots of the block
 // (exactly, so the split does not change any result) and applies the update.
-template <bool BF16OUT, bool WIDE, int EPI = kEpiBatch>
+template <bool BF16OUT, bool WIDE, int EPI = kEpiBatch, bool SMALL = false>
 __device__ __forceinline__ void merge_pr_block(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const float *__restrict__ partial, int32_t V, int32_t k, int32_t B, int b, int32_t j, int32_t S,
@@ -420,6 +564,13 @@ __device__ __forceinline__ void merge_pr_block(
 
     const int64_t vb = (int64_t)b * B;
     const int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);
+    [[maybe_unused]] float rin[EPI];
+    [[maybe_unused]] int32_t odv[EPI];
+    [[maybe_unused]] double dangling;
+    if constexpr (SMALL) {
+        load_vertices<EPI>(rank_in, outdeg, vb, nv, threadIdx.x, rin, odv);
+        dangling = scalars_in[0];
+    }
     for (int i = threadIdx.x; i < nv; i += kMergeThreads) acc[i] = 0ull;
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
     const int32_t F0 = (int32_t)((int64_t)P * j / S), F1 = (int32_t)((int64_t)P * (j + 1) / S);
@@ -435,8 +586,12 @@ __device__ __forceinline__ void merge_pr_block(
         if (threadIdx.x == 0) *item_abs = tot;
         return;
     }
-    pr_epilogue<BF16OUT, EPI>(acc, V, vb, nv, rank_in, outdeg, scalars_in, damping, seed, rank_out, contrib_out,
-                              blk_out, (double)am, red);
+    if constexpr (SMALL)
+        pr_epilogue_small<BF16OUT, EPI>(acc, V, vb, nv, rank_in, outdeg, dangling, damping, seed, rank_out,
+                                        contrib_out, blk_out, (double)am, red, rin, odv);
+    else
+        pr_epilogue<BF16OUT, EPI>(acc, V, vb, nv, rank_in, outdeg, scalars_in, damping, seed, rank_out, contrib_out,
+                                  blk_out, (double)am, red);
 }
 
 // Slot of item j of a split block b whose first item is items_b: 2*(items_b - b)
@@ -478,6 +633,24 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_pr(
     double *ia = S > 1 ? item_abs + block_items[b] + j : nullptr;
     merge_pr_block<BF16OUT, WIDE>(row_dst_lo, block_ptr, partial, V, k, B, b, j, S, rank_in, outdeg, scalars_in,
                                   damping, seed, rank_out, contrib_out, blk + (int64_t)b * 4, slot, ia, smem);
+}
+
+// The merge of a small graph: every block is one work item, and the last block
+// to finish adds the blocks' sums (the accumulators' LDS is free by then).
+template <bool BF16OUT, bool WIDE>
+__global__ __launch_bounds__(kMergeThreads) void k_merge_pr_small(
+    const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr, const float *__restrict__ partial,
+    int32_t V, int32_t k, int32_t B, int32_t nb, const float *__restrict__ rank_in,
+    const int32_t *__restrict__ outdeg, const double *scalars_in, double damping, int32_t seed,
+    float *__restrict__ rank_out, void *__restrict__ contrib_out, double *__restrict__ blk,
+    unsigned long long *__restrict__ ticket, double *scalars_out) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int b = xcd_remap(blockIdx.x, nb);
+    merge_pr_block<BF16OUT, WIDE, kEpiBatch, true>(row_dst_lo, block_ptr, partial, V, k, B, b, 0, 1, rank_in, outdeg,
+                                                   scalars_in, damping, seed, rank_out, contrib_out,
+                                                   blk + (int64_t)b * 4, nullptr, nullptr, smem);
+    if (last_of(ticket, nb, reinterpret_cast<int32_t *>(smem)))
+        reduce4_rows<true>(blk, nb, scalars_out, scalars_in, reinterpret_cast<double *>(smem) + 1);
 }
 
 // Sum of the item slots of each split block, written into its first slot.
@@ -573,21 +746,30 @@ cagra_status launch_merge_sum_fixed24(const cagra_segments *seg, const float *pa
 }
 
 // Persistent form over many graphs: workgroups stride over a global block list.
-__global__ __launch_bounds__(kMergeThreads) void k_multi_merge(const MultiDesc *__restrict__ desc,
-                                                               const int32_t *__restrict__ block_graph,
-                                                               int64_t total_blocks, int parity, double damping,
-                                                               double *__restrict__ blk) {
+__global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_multi_merge(
+    const MultiDesc *__restrict__ desc, const int32_t *__restrict__ block_graph, int64_t total_blocks, int parity,
+    double damping, double *__restrict__ blk, unsigned long long *__restrict__ tickets) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     for (int64_t gb = blockIdx.x; gb < total_blocks; gb += gridDim.x) {
         __syncthreads();  // LDS reuse across blocks
         const int gi = block_graph[gb];
         const MultiDesc &d = desc[gi];
-        // one vertex per pass in the update keeps this kernel within 64 VGPRs
-        // (two workgroups per CU)
-        merge_pr_block<false, false, 1>(d.row_dst_lo, d.block_ptr, d.partial, d.V, d.k, d.B,
-                                        (int)(gb - d.block_base), 0, 1, d.rank[parity], d.out_degree,
-                                        d.scalars[parity], damping, -1, d.rank[1 - parity], d.contrib[1 - parity],
-                                        blk + gb * 4, nullptr, nullptr, smem);
+        // kept within 64 VGPRs (two workgroups per CU): at 66 one fitted, and the
+        // merge of 48 graphs took 22.5 us and its sums 4.6 us more; now 21.4 us
+        // with the sums
+        merge_pr_block<false, false, 4, true>(d.row_dst_lo, d.block_ptr, d.partial, d.V, d.k, d.B,
+                                              (int)(gb - d.block_base), 0, 1, d.rank[parity], d.out_degree,
+                                              d.scalars[parity], damping, -1, d.rank[1 - parity],
+                                              d.contrib[1 - parity], blk + gb * 4, nullptr, nullptr, smem);
+        if (!tickets) continue;
+        // the last block of a graph adds that graph's sums (its descriptor is
+        // read again rather than held in registers over the merge)
+        int gr = gi;
+        asm volatile("" : "+s"(gr));
+        const MultiDesc &e = desc[gr];
+        if (last_of(tickets + gr, e.nb, reinterpret_cast<int32_t *>(smem)))
+            reduce4_rows<true, 1>(blk + e.block_base * 4, e.nb, e.scalars[1 - parity], e.scalars[parity],
+                                  reinterpret_cast<double *>(smem) + 1);
     }
 }
 
@@ -623,17 +805,12 @@ __global__ __launch_bounds__(256) void k_multi_start(const MultiDesc *__restrict
 
 // Per graph: fixed-order sum of its blocks' partials into scalars[parity]. With
 // carry, the range count [3] also adds the previous step's (scalars[1 - parity]).
-__global__ __launch_bounds__(256) void k_multi_reduce(const MultiDesc *__restrict__ desc,
-                                                      const double *__restrict__ blk, int parity, int carry) {
-    __shared__ double red[4];
+__global__ __launch_bounds__(kReduceThreads) void k_multi_reduce(const MultiDesc *__restrict__ desc,
+                                                                 const double *__restrict__ blk, int parity,
+                                                                 int carry) {
+    __shared__ double red[4 * kReduceThreads / 64];
     const MultiDesc &d = desc[blockIdx.x];
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int32_t j = threadIdx.x; j < d.nb; j += 256)
-        for (int c = 0; c < 4; ++c) a[c] += blk[(d.block_base + j) * 4 + c];
-    for (int c = 0; c < 4; ++c) {
-        double t = block_sum_f64<256>(a[c], red);
-        if (threadIdx.x == 0) d.scalars[parity][c] = c == 3 && carry ? t + d.scalars[1 - parity][3] : t;
-    }
+    reduce4_rows<false>(blk + d.block_base * 4, d.nb, d.scalars[parity], carry ? d.scalars[1 - parity] : nullptr, red);
 }
 
 cagra_status launch_multi_start(const MultiDesc *desc, const int32_t *block_graph, int64_t total_blocks,
@@ -641,19 +818,20 @@ cagra_status launch_multi_start(const MultiDesc *desc, const int32_t *block_grap
     if (total_blocks == 0) return CAGRA_OK;
     k_multi_start<<<grid, 256, 0, st>>>(desc, block_graph, total_blocks, blk);
     CAGRA_LAUNCH_CHECK();
-    k_multi_reduce<<<ngraphs, 256, 0, st>>>(desc, blk, 0, 0);
+    k_multi_reduce<<<ngraphs, kReduceThreads, 0, st>>>(desc, blk, 0, 0);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
 
 cagra_status launch_multi_merge(const MultiDesc *desc, const int32_t *block_graph, int64_t total_blocks,
-                                int32_t ngraphs, int parity, double damping, double *blk, size_t lds, int grid,
-                                hipStream_t st) {
+                                int32_t ngraphs, int parity, double damping, double *blk, unsigned long long *tickets,
+                                size_t lds, int grid, hipStream_t st) {
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_multi_merge)) return a_;
     if (total_blocks == 0) return CAGRA_OK;
-    k_multi_merge<<<grid, kMergeThreads, lds, st>>>(desc, block_graph, total_blocks, parity, damping, blk);
+    k_multi_merge<<<grid, kMergeThreads, lds, st>>>(desc, block_graph, total_blocks, parity, damping, blk, tickets);
     CAGRA_LAUNCH_CHECK();
-    k_multi_reduce<<<ngraphs, 256, 0, st>>>(desc, blk, 1 - parity, 1);
+    if (tickets) return CAGRA_OK;
+    k_multi_reduce<<<ngraphs, kReduceThreads, 0, st>>>(desc, blk, 1 - parity, 1);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -760,29 +938,11 @@ __global__ __launch_bounds__(kInitThreads) void k_pr_init(const float *__restric
 
 // Fixed-order FP64 reduction of n rows of 4 partial sums. With carry non-null,
 // out[3] also adds carry[3] (the range count accumulates over iterations).
-__global__ __launch_bounds__(256) void k_reduce4(const double *__restrict__ blk, int32_t n,
-                                                 double *__restrict__ out, const double *__restrict__ carry) {
-    __shared__ double red[4];
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    // four rows per thread and pass, loaded before they are added (same order)
-    int32_t j = threadIdx.x;
-    for (; j + 3 * 256 < n; j += 4 * 256) {
-        double x[4][4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) x[r][c] = blk[(int64_t)(j + r * 256) * 4 + c];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] += x[r][c];
-    }
-    for (; j < n; j += 256)
-        for (int c = 0; c < 4; ++c) a[c] += blk[(int64_t)j * 4 + c];
-    for (int c = 0; c < 4; ++c) {
-        double t = block_sum_f64<256>(a[c], red);
-        if (threadIdx.x == 0) out[c] = c == 3 && carry ? t + carry[3] : t;
-    }
+__global__ __launch_bounds__(kReduceThreads) void k_reduce4(const double *__restrict__ blk, int32_t n,
+                                                            double *__restrict__ out,
+                                                            const double *__restrict__ carry) {
+    __shared__ double red[4 * kReduceThreads / 64];
+    reduce4_rows<false>(blk, n, out, carry, red);
 }
 
 __global__ __launch_bounds__(256) void k_reduce_i32(const int32_t *__restrict__ blk, int32_t n,
@@ -798,7 +958,7 @@ __global__ __launch_bounds__(256) void k_reduce_i32(const int32_t *__restrict__ 
 
 // Fixed-order reductions of per-block partial sums (also used by the push path).
 cagra_status launch_reduce4(const double *blk, int32_t n, double *out, const double *carry, hipStream_t st) {
-    k_reduce4<<<1, 256, 0, st>>>(blk, n, out, carry);
+    k_reduce4<<<1, kReduceThreads, 0, st>>>(blk, n, out, carry);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -829,10 +989,13 @@ cagra_status launch_pr_init(const cagra_graph *g, int32_t contrib_type, const fl
     if (contrib_type == CAGRA_BF16) k_pr_init<true><<<nblk, kInitThreads, 0, st>>>(rank, g->out_degree, g->V, contrib_out, blk);
     else k_pr_init<false><<<nblk, kInitThreads, 0, st>>>(rank, g->out_degree, g->V, contrib_out, blk);
     CAGRA_LAUNCH_CHECK();
-    k_reduce4<<<1, 256, 0, st>>>(blk, nblk, scalars_out, nullptr);
+    k_reduce4<<<1, kReduceThreads, 0, st>>>(blk, nblk, scalars_out, nullptr);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
+
+// Mean entries per (subgraph, block) range below one 64-entry step: wide walk.
+static bool wide_ranges(const cagra_segments *seg) { return seg->Q < (int64_t)kWave * seg->k * seg->nb; }
 
 template <bool BF16OUT, bool WIDE>
 static cagra_status launch_merge_pr_t(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
@@ -864,7 +1027,7 @@ static cagra_status launch_merge_pr_t(const cagra_graph *g, const cagra_segments
             contrib_out, blk, slots, item_abs, seg->max_items);
         CAGRA_LAUNCH_CHECK();
     }
-    k_reduce4<<<1, 256, 0, st>>>(blk, seg->nb, scalars_out, scalars_in);
+    k_reduce4<<<1, kReduceThreads, 0, st>>>(blk, seg->nb, scalars_out, scalars_in);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -873,8 +1036,7 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
                              int32_t contrib_type,
                              const float *rank_in, const double *scalars_in, const float *partial, float *rank_out,
                              void *contrib_out, double *scalars_out, void *ws, hipStream_t st) {
-    // mean entries per (subgraph, block) range below one 64-entry step: wide walk
-    const bool wide = seg->Q < (int64_t)kWave * seg->k * seg->nb;
+    const bool wide = wide_ranges(seg);
     if (contrib_type == CAGRA_BF16)
         return wide ? launch_merge_pr_t<true, true>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out,
                                                     contrib_out, scalars_out, ws, st)
@@ -884,6 +1046,55 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
                                                  scalars_out, ws, st)
                 : launch_merge_pr_t<false, false>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out,
                                                   contrib_out, scalars_out, ws, st);
+}
+
+// Most blocks whose sums the last one takes. Each block then ends with two
+// round trips to memory and an atomic on one address (about 40 ns each, one
+// after the other), against a launch of about 3 us plus its gap: 20 iterations
+// of a 4,096-vertex graph took 331 us with the reduction launch and 298 us
+// without; replayed from a captured graph the two are level up to 64 blocks,
+// and with 256 (1,024) blocks of 1,024 vertices the launch is 8% faster.
+// A small graph's merge is a chain of round trips to memory: with the vertex
+// inputs loaded at its end it takes 10.4 us, loaded first 9.9 us (the pass 287).
+constexpr int32_t kOwnSumBlocks = 64;
+
+template <bool BF16OUT, bool WIDE>
+static cagra_status launch_merge_pr_small_t(const cagra_graph *g, const cagra_segments *seg, double damping,
+                                            int32_t seed, const float *rank_in, const double *scalars_in,
+                                            const float *partial, float *rank_out, void *contrib_out,
+                                            double *scalars_out, void *ws, unsigned long long *ticket,
+                                            hipStream_t st) {
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr_small<BF16OUT, WIDE>)) return a_;
+    k_merge_pr_small<BF16OUT, WIDE><<<seg->nb, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
+        seg->row_dst_lo, seg->block_ptr, partial, seg->V, seg->k, seg->B, seg->nb, rank_in, g->out_degree, scalars_in,
+        damping, seed, rank_out, contrib_out, reinterpret_cast<double *>(ws), ticket, scalars_out);
+    CAGRA_LAUNCH_CHECK();
+    return CAGRA_OK;
+}
+
+// One PageRank iteration. The merge's last block also takes the FP64 sums when
+// the graph is small, every block is one work item and the gather runs before
+// it and clears the counter (in the workspace's tail, behind the slots);
+// otherwise they are a launch of their own. Both give the same bits.
+cagra_status launch_pagerank_iter(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
+                                  int32_t contrib_type, const float *rank_in, const void *contrib_in,
+                                  const double *scalars_in, float *partial, float *rank_out, void *contrib_out,
+                                  double *scalars_out, void *ws, hipStream_t st) {
+    cagra_status s;
+    if (seg->ntiles == 0 || seg->max_items != seg->nb || seg->nb > kOwnSumBlocks) {
+        if ((s = launch_gather(seg, CAGRA_SUM_F32, contrib_type, contrib_in, partial, st)) != CAGRA_OK) return s;
+        return launch_merge_pr(g, seg, damping, seed, contrib_type, rank_in, scalars_in, partial, rank_out,
+                               contrib_out, scalars_out, ws, st);
+    }
+    unsigned long long *ticket = reinterpret_cast<unsigned long long *>(
+        static_cast<char *>(ws) + ws_blk_bytes(seg->V, seg->nb) + ws_item_bytes(seg) + ws_slot_bytes(seg));
+    if ((s = launch_gather_clear(seg, CAGRA_SUM_F32, contrib_type, contrib_in, partial, ticket, st)) != CAGRA_OK)
+        return s;
+    const bool wide = wide_ranges(seg);
+    auto f = contrib_type == CAGRA_BF16
+                 ? (wide ? launch_merge_pr_small_t<true, true> : launch_merge_pr_small_t<true, false>)
+                 : (wide ? launch_merge_pr_small_t<false, true> : launch_merge_pr_small_t<false, false>);
+    return f(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out, contrib_out, scalars_out, ws, ticket, st);
 }
 
 cagra_status launch_merge_lp(const cagra_segments *seg, const int32_t *labels_in, const int32_t *partial,

@@ -1,6 +1,6 @@
 // Many independent graphs in one launch per kernel: per-graph descriptors in
 // device memory, global tile and merge-block lists, and persistent workgroups
-// striding over them. A PageRank iteration of every graph is three kernel
+// striding over them. A PageRank iteration of every graph is two kernel
 // launches with no host synchronization, so a whole run can be captured into
 // one HIP graph.
 #include <vector>
@@ -13,14 +13,20 @@ cagra_status fail(cagra_status st, const char *fmt, ...);
 size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes);
 size_t merge_fused_lds_bytes(int32_t B, int32_t k, int acc_bytes);
 cagra_status launch_multi_gather(const MultiDesc *desc, const int32_t *tile_graph, int64_t total_tiles, int parity,
-                                 int grid, hipStream_t st);
+                                 unsigned long long *tickets, int32_t ngraphs, int grid, hipStream_t st);
 cagra_status launch_multi_merge(const MultiDesc *desc, const int32_t *block_graph, int64_t total_blocks,
-                                int32_t ngraphs, int parity, double damping, double *blk, size_t lds, int grid,
-                                hipStream_t st);
+                                int32_t ngraphs, int parity, double damping, double *blk, unsigned long long *tickets,
+                                size_t lds, int grid, hipStream_t st);
 cagra_status launch_multi_start(const MultiDesc *desc, const int32_t *block_graph, int64_t total_blocks,
                                 int32_t ngraphs, double *blk, int grid, hipStream_t st);
 
 static size_t desc_area(int32_t ngraphs) { return align_up((size_t)ngraphs * sizeof(MultiDesc), 256); }
+
+constexpr int64_t kMaxGrid = 1 << 20;
+
+// The plan: descriptors, the graph of every tile and of every block, and a
+// counter per graph for the blocks of a step.
+static size_t list_area(int64_t tiles, int64_t blocks) { return align_up((size_t)(tiles + blocks) * sizeof(int32_t), 8); }
 
 static cagra_status check_multi_member(const cagra_graph *g, const cagra_segments *s, int i) {
     if (!g || !s) return fail(CAGRA_E_INVALID, "graph/segments %d is NULL", i);
@@ -70,7 +76,7 @@ cagra_status cagra_multi_query(int32_t ngraphs, const cagra_graph *graphs, const
     m->total_blocks = Bk;
     m->max_k = max_k;
     m->max_B = max_B;
-    m->desc_bytes = desc_area(ngraphs) + (size_t)(T + Bk + 2) * sizeof(int32_t) + 256;
+    m->desc_bytes = desc_area(ngraphs) + list_area(T, Bk) + (size_t)ngraphs * sizeof(unsigned long long) + 256;
     return CAGRA_OK;
 }
 
@@ -127,11 +133,10 @@ cagra_status cagra_multi_setup(cagra_multi *m, const cagra_graph *graphs, const 
     }
     CAGRA_HIP_CHECK(hipMemcpyAsync(m->desc, host.data(), m->desc_bytes, hipMemcpyHostToDevice, stream));
     CAGRA_HIP_CHECK(hipStreamSynchronize(stream));  // the host staging copy goes out of scope
-    int dev = 0, cus = 0;
-    CAGRA_HIP_CHECK(hipGetDevice(&dev));
-    CAGRA_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    m->grid_gather = cus;      // one 160 KB-LDS workgroup per CU
-    m->grid_merge = 2 * cus;
+    // a workgroup per tile and per block, dispatched as the earlier ones end;
+    // past the bound they stride
+    m->grid_gather = (int32_t)(m->total_tiles < 1 ? 1 : m->total_tiles < kMaxGrid ? m->total_tiles : kMaxGrid);
+    m->grid_merge = (int32_t)(m->total_blocks < kMaxGrid ? m->total_blocks : kMaxGrid);
     return CAGRA_OK;
 }
 
@@ -159,9 +164,15 @@ cagra_status cagra_multi_pagerank_step(const cagra_multi *m, int32_t parity, dou
     const int32_t *tile_graph =
         reinterpret_cast<const int32_t *>((const unsigned char *)m->desc + desc_area(m->ngraphs));
     const int32_t *block_graph = tile_graph + m->total_tiles;
-    if ((s = launch_multi_gather(d, tile_graph, m->total_tiles, parity, m->grid_gather, stream)) != CAGRA_OK)
+    // cleared by the gather; without one the sums are a launch of their own
+    unsigned long long *tickets =
+        m->total_tiles > 0 ? reinterpret_cast<unsigned long long *>((unsigned char *)m->desc + desc_area(m->ngraphs) +
+                                                                    list_area(m->total_tiles, m->total_blocks))
+                           : nullptr;
+    if ((s = launch_multi_gather(d, tile_graph, m->total_tiles, parity, tickets, m->ngraphs, m->grid_gather,
+                                 stream)) != CAGRA_OK)
         return s;
-    return launch_multi_merge(d, block_graph, m->total_blocks, m->ngraphs, parity, damping, m->blk,
+    return launch_multi_merge(d, block_graph, m->total_blocks, m->ngraphs, parity, damping, m->blk, tickets,
                               merge_fused_lds_bytes(m->max_B, m->max_k, 8), m->grid_merge, stream);
 }
 

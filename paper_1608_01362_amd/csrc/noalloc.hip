@@ -11,12 +11,10 @@ namespace cagra {
 size_t ws_blk_bytes(int32_t V, int32_t nb);
 size_t ws_item_bytes(const cagra_segments *seg);
 size_t ws_slot_bytes(const cagra_segments *seg);
-cagra_status launch_gather(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
-                           void *partial, hipStream_t st);
-cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
-                             int32_t contrib_type, const float *rank_in, const double *scalars_in,
-                             const float *partial, float *rank_out, void *contrib_out, double *scalars_out, void *ws,
-                             hipStream_t st);
+cagra_status launch_pagerank_iter(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
+                                  int32_t contrib_type, const float *rank_in, const void *contrib_in,
+                                  const double *scalars_in, float *partial, float *rank_out, void *contrib_out,
+                                  double *scalars_out, void *ws, hipStream_t st);
 cagra_status check_pagerank_args(const cagra_graph *g, const cagra_segments *seg, double damping,
                                  int32_t restart_vertex, int32_t contrib_type, const void *rank_in,
                                  const void *contrib_in, const void *scalars_in, const void *partial,
@@ -75,9 +73,8 @@ cagra_status cagra_pagerank_iter_noalloc(const cagra_graph *g, const cagra_segme
                     need, (size_t)CAGRA_NOALLOC_SCRATCH_BYTES);
     void *ws = nullptr;
     if ((s = scratch_address(&ws)) != CAGRA_OK) return s;
-    if ((s = launch_gather(seg, CAGRA_SUM_F32, contrib_type, contrib_in, partial, stream)) != CAGRA_OK) return s;
-    return launch_merge_pr(g, seg, damping, restart_vertex, contrib_type, rank_in, scalars_in, partial, rank_out,
-                           contrib_out, scalars_out, ws, stream);
+    return launch_pagerank_iter(g, seg, damping, restart_vertex, contrib_type, rank_in, contrib_in, scalars_in, partial,
+                                rank_out, contrib_out, scalars_out, ws, stream);
 }
 
 }  // extern "C"
