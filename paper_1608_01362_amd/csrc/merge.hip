@@ -297,15 +297,16 @@ __device__ __forceinline__ unsigned long long fix24(float x) {
 
 // Streams block b's buffer entries (the ranges of all subgraphs, flattened).
 // Each wave takes a contiguous share and walks it in windows of 64 entries,
-// kUnroll windows per pass so that many loads are in flight. With long ranges
-// (WIDE = false) the wave steps over each window's range starts together
-// (window_index); with short ranges each lane searches forward from the
-// previous window's subgraph. apply(d, x) updates the LDS accumulator of
-// block offset d. The loads keep the default cache policy: the cache line at
-// each end of a (subgraph, block) range is shared with the neighbouring
-// block, which is merged at the same time on the same XCD and finds the line
-// in L2.
-template <typename PT, bool WIDE, class Apply>
+// kUnroll windows per pass so that many loads are in flight (RangeWalk). Only
+// the last pass of a share tests its lanes. The entries of a graph whose buffer
+// is past the caches come at the card's read rate (R-MAT 25: 840 us for 3.9 GB
+// in place of 856); with the buffer in the caches the walk's own instructions,
+// 35 per window before and 20 now, are what is left: 38 -> 33 us for 3 M vertices.
+// apply(d, x) updates the LDS accumulator of block offset d. The loads keep the
+// default cache policy: the cache line at each end of a (subgraph, block) range
+// is shared with the neighbouring block, which is merged at the same time on
+// the same XCD and finds the line in L2.
+template <typename PT, class Apply>
 __device__ __forceinline__ void stream_block(const uint16_t *__restrict__ dlo, const PT *__restrict__ partial,
                                              const int32_t *ofs, const int32_t *pre, int32_t k, int32_t F0,
                                              int32_t F1, Apply apply) {
@@ -313,37 +314,43 @@ __device__ __forceinline__ void stream_block(const uint16_t *__restrict__ dlo, c
     const int32_t share = ((((F1 - F0) + 15) / 16) + 63) & ~63;
     const int32_t fa = min(F0 + w * share, F1), fb = min(fa + share, F1);
     if (fa >= fb) return;  // uniform over the wave
-    int32_t sw = __builtin_amdgcn_readfirstlane(run_of(pre, k, fa));
-    int32_t i_safe = __builtin_amdgcn_readfirstlane(ofs[sw]) + fa;  // an entry of the share, for idle lanes
-    for (int32_t f0 = fa; f0 < fb; f0 += kWave * kUnroll) {
-        int32_t d[kUnroll];
+    RangeWalk walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
+    int32_t f0 = fa;
+    for (; f0 + kWave * kUnroll <= fb; f0 += kWave * kUnroll) {
+        uint16_t d[kUnroll];
         PT x[kUnroll];
-        int32_t sl = WIDE ? run_of(pre, k, f0) : 0;
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int32_t fs = f0 + u * kWave;
-            const int32_t f = fs + lane;
-            const bool valid = f < fb;
-            int32_t i;
-            if (WIDE) {
-                const int32_t ff = valid ? f : f0;
-                sl = advance<true>(pre, k, sl, ff);
-                i = ofs[sl] + ff;
-            } else if (fs < fb) {  // uniform
-                const int32_t ii = window_index(ofs, pre, sw, fs, min(fs + kWave - 1, fb - 1), f);
-                i_safe = __builtin_amdgcn_readfirstlane(ii);  // lane 0's entry is in the share
-                i = valid ? ii : i_safe;
-            } else {
-                i = i_safe;  // a window past the share: loads of an entry already read, results dropped
-            }
-            const int32_t dd = (int32_t)dlo[i];
+            const uint32_t i = (uint32_t)walk.index(fs + kWave - 1, fs + lane);
+            d[u] = dlo[i];
             x[u] = partial[i];
-            d[u] = valid ? dd : -1;
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            if (d[u] >= 0) apply(d[u], x[u]);
+        for (int u = 0; u < kUnroll; ++u) apply((int32_t)d[u], x[u]);
     }
+    if (f0 >= fb) return;
+    int32_t d[kUnroll];
+    PT x[kUnroll];
+    int32_t i_safe = 0;  // an entry of the share, for idle lanes
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int32_t fs = f0 + u * kWave;
+        const int32_t f = fs + lane;
+        const bool valid = f < fb;
+        int32_t i = i_safe;  // a window past the share: loads of an entry already read, results dropped
+        if (fs < fb) {       // uniform, and so for u = 0
+            const int32_t ii = walk.index(min(fs + kWave - 1, fb - 1), f);
+            i_safe = __builtin_amdgcn_readfirstlane(ii);  // lane 0's entry is in the share
+            i = valid ? ii : i_safe;
+        }
+        const int32_t dd = (int32_t)dlo[i];
+        x[u] = partial[i];
+        d[u] = valid ? dd : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+        if (d[u] >= 0) apply(d[u], x[u]);
 }
 
 // ---- sums over the workgroups, taken by the last one to finish
@@ -548,7 +555,7 @@ __device__ __forceinline__ void pr_epilogue_small(const unsigned long long *acc,
 // sums in its own slot of the workspace and the absolute sum of its buffer
 // values in *item_abs, and k_merge_pr_finish adds the S slots of the block
 // (exactly, so the split does not change any result) and applies the update.
-template <bool BF16OUT, bool WIDE, int EPI = kEpiBatch, bool SMALL = false>
+template <bool BF16OUT, int EPI = kEpiBatch, bool SMALL = false>
 __device__ __forceinline__ void merge_pr_block(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const float *__restrict__ partial, int32_t V, int32_t k, int32_t B, int b, int32_t j, int32_t S,
@@ -575,8 +582,8 @@ __device__ __forceinline__ void merge_pr_block(
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
     const int32_t F0 = (int32_t)((int64_t)P * j / S), F1 = (int32_t)((int64_t)P * (j + 1) / S);
     float am = 0.0f;  // this thread's share of the absolute buffer mass (range check)
-    stream_block<float, WIDE>(row_dst_lo, partial, ofs, pre, k, F0, F1, [&](int32_t d, float x) {
-        atomicAdd(&acc[d], fix56(x));
+    stream_block<float>(row_dst_lo, partial, ofs, pre, k, F0, F1, [&](int32_t d, float x) {
+        atomicAdd(&acc[d], fix56_wave(x));
         am += fabsf(x);
     });
     __syncthreads();
@@ -604,7 +611,7 @@ __device__ __forceinline__ int64_t split_slot(int32_t items_b, int32_t b, int32_
 
 constexpr int32_t kItemGroup = 4;  // work items per XCD group (1, 2, 4 and 16 time alike; contiguous is slower)
 
-template <bool BF16OUT, bool WIDE>
+template <bool BF16OUT>
 __global__ __launch_bounds__(kMergeThreads) void k_merge_pr(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const int32_t *__restrict__ block_items, const float *__restrict__ partial, int32_t V, int32_t k, int32_t B,
@@ -631,13 +638,13 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_pr(
     const int32_t b = ip.b, j = ip.j, S = ip.S;
     unsigned long long *slot = S > 1 ? slots + split_slot(block_items[b], b, j) * B : nullptr;
     double *ia = S > 1 ? item_abs + block_items[b] + j : nullptr;
-    merge_pr_block<BF16OUT, WIDE>(row_dst_lo, block_ptr, partial, V, k, B, b, j, S, rank_in, outdeg, scalars_in,
+    merge_pr_block<BF16OUT>(row_dst_lo, block_ptr, partial, V, k, B, b, j, S, rank_in, outdeg, scalars_in,
                                   damping, seed, rank_out, contrib_out, blk + (int64_t)b * 4, slot, ia, smem);
 }
 
 // The merge of a small graph: every block is one work item, and the last block
 // to finish adds the blocks' sums (the accumulators' LDS is free by then).
-template <bool BF16OUT, bool WIDE>
+template <bool BF16OUT>
 __global__ __launch_bounds__(kMergeThreads) void k_merge_pr_small(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr, const float *__restrict__ partial,
     int32_t V, int32_t k, int32_t B, int32_t nb, const float *__restrict__ rank_in,
@@ -646,7 +653,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_pr_small(
     unsigned long long *__restrict__ ticket, double *scalars_out) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int b = xcd_remap(blockIdx.x, nb);
-    merge_pr_block<BF16OUT, WIDE, kEpiBatch, true>(row_dst_lo, block_ptr, partial, V, k, B, b, 0, 1, rank_in, outdeg,
+    merge_pr_block<BF16OUT, kEpiBatch, true>(row_dst_lo, block_ptr, partial, V, k, B, b, 0, 1, rank_in, outdeg,
                                                    scalars_in, damping, seed, rank_out, contrib_out,
                                                    blk + (int64_t)b * 4, nullptr, nullptr, smem);
     if (last_of(ticket, nb, reinterpret_cast<int32_t *>(smem)))
@@ -728,7 +735,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_sum_fixed24(
     const int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);
     for (int i = threadIdx.x; i < nv; i += kMergeThreads) acc[i] = 0ull;
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
-    stream_block<float, false>(row_dst_lo, partial, ofs, pre, k, 0, P,
+    stream_block<float>(row_dst_lo, partial, ofs, pre, k, 0, P,
                                [&](int32_t d, float x) { atomicAdd(&acc[d], fix24(x)); });
     __syncthreads();
     for (int i = threadIdx.x; i < nv; i += kMergeThreads)
@@ -757,7 +764,7 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8
         // kept within 64 VGPRs (two workgroups per CU): at 66 one fitted, and the
         // merge of 48 graphs took 22.5 us and its sums 4.6 us more; now 21.4 us
         // with the sums
-        merge_pr_block<false, false, 4, true>(d.row_dst_lo, d.block_ptr, d.partial, d.V, d.k, d.B,
+        merge_pr_block<false, 4, true>(d.row_dst_lo, d.block_ptr, d.partial, d.V, d.k, d.B,
                                               (int)(gb - d.block_base), 0, 1, d.rank[parity], d.out_degree,
                                               d.scalars[parity], damping, -1, d.rank[1 - parity],
                                               d.contrib[1 - parity], blk + gb * 4, nullptr, nullptr, smem);
@@ -866,7 +873,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_lp(
         }
     }
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
-    stream_block<int32_t, false>(row_dst_lo, partial, ofs, pre, k, 0, P,
+    stream_block<int32_t>(row_dst_lo, partial, ofs, pre, k, 0, P,
                           [&](int32_t d, int32_t x) { atomicMin(&acc[d], x); });
     __syncthreads();
     int32_t changed = 0;
@@ -994,22 +1001,19 @@ cagra_status launch_pr_init(const cagra_graph *g, int32_t contrib_type, const fl
     return CAGRA_OK;
 }
 
-// Mean entries per (subgraph, block) range below one 64-entry step: wide walk.
-static bool wide_ranges(const cagra_segments *seg) { return seg->Q < (int64_t)kWave * seg->k * seg->nb; }
-
-template <bool BF16OUT, bool WIDE>
+template <bool BF16OUT>
 static cagra_status launch_merge_pr_t(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
                                       const float *rank_in, const double *scalars_in, const float *partial,
                                       float *rank_out, void *contrib_out, double *scalars_out, void *ws,
                                       hipStream_t st) {
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr<BF16OUT, WIDE>)) return a_;
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr<BF16OUT>)) return a_;
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr_finish<BF16OUT>)) return a_;
     double *blk = reinterpret_cast<double *>(ws);
     double *item_abs = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + ws_blk_bytes(seg->V, seg->nb));
     unsigned long long *slots = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ws) +
                                                                        ws_blk_bytes(seg->V, seg->nb) +
                                                                        ws_item_bytes(seg));
-    k_merge_pr<BF16OUT, WIDE><<<seg->max_items, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
+    k_merge_pr<BF16OUT><<<seg->max_items, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
         seg->row_dst_lo, seg->block_ptr, seg->block_items, partial, seg->V, seg->k, seg->B, seg->nb, rank_in,
         g->out_degree, scalars_in, damping, seed, rank_out, contrib_out, blk, slots, item_abs,
         seg->max_items == seg->nb ? 1 : 0);
@@ -1036,16 +1040,8 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
                              int32_t contrib_type,
                              const float *rank_in, const double *scalars_in, const float *partial, float *rank_out,
                              void *contrib_out, double *scalars_out, void *ws, hipStream_t st) {
-    const bool wide = wide_ranges(seg);
-    if (contrib_type == CAGRA_BF16)
-        return wide ? launch_merge_pr_t<true, true>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out,
-                                                    contrib_out, scalars_out, ws, st)
-                    : launch_merge_pr_t<true, false>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out,
-                                                     contrib_out, scalars_out, ws, st);
-    return wide ? launch_merge_pr_t<false, true>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out, contrib_out,
-                                                 scalars_out, ws, st)
-                : launch_merge_pr_t<false, false>(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out,
-                                                  contrib_out, scalars_out, ws, st);
+    auto f = contrib_type == CAGRA_BF16 ? launch_merge_pr_t<true> : launch_merge_pr_t<false>;
+    return f(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out, contrib_out, scalars_out, ws, st);
 }
 
 // Most blocks whose sums the last one takes. Each block then ends with two
@@ -1058,14 +1054,14 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
 // inputs loaded at its end it takes 10.4 us, loaded first 9.9 us (the pass 287).
 constexpr int32_t kOwnSumBlocks = 64;
 
-template <bool BF16OUT, bool WIDE>
+template <bool BF16OUT>
 static cagra_status launch_merge_pr_small_t(const cagra_graph *g, const cagra_segments *seg, double damping,
                                             int32_t seed, const float *rank_in, const double *scalars_in,
                                             const float *partial, float *rank_out, void *contrib_out,
                                             double *scalars_out, void *ws, unsigned long long *ticket,
                                             hipStream_t st) {
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr_small<BF16OUT, WIDE>)) return a_;
-    k_merge_pr_small<BF16OUT, WIDE><<<seg->nb, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr_small<BF16OUT>)) return a_;
+    k_merge_pr_small<BF16OUT><<<seg->nb, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
         seg->row_dst_lo, seg->block_ptr, partial, seg->V, seg->k, seg->B, seg->nb, rank_in, g->out_degree, scalars_in,
         damping, seed, rank_out, contrib_out, reinterpret_cast<double *>(ws), ticket, scalars_out);
     CAGRA_LAUNCH_CHECK();
@@ -1090,10 +1086,7 @@ cagra_status launch_pagerank_iter(const cagra_graph *g, const cagra_segments *se
         static_cast<char *>(ws) + ws_blk_bytes(seg->V, seg->nb) + ws_item_bytes(seg) + ws_slot_bytes(seg));
     if ((s = launch_gather_clear(seg, CAGRA_SUM_F32, contrib_type, contrib_in, partial, ticket, st)) != CAGRA_OK)
         return s;
-    const bool wide = wide_ranges(seg);
-    auto f = contrib_type == CAGRA_BF16
-                 ? (wide ? launch_merge_pr_small_t<true, true> : launch_merge_pr_small_t<true, false>)
-                 : (wide ? launch_merge_pr_small_t<false, true> : launch_merge_pr_small_t<false, false>);
+    auto f = contrib_type == CAGRA_BF16 ? launch_merge_pr_small_t<true> : launch_merge_pr_small_t<false>;
     return f(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out, contrib_out, scalars_out, ws, ticket, st);
 }
 

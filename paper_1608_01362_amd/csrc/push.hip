@@ -153,7 +153,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_push_plan(PushPlan plan) {
 // items (the block's rows flattened over subgraphs, cut into S equal parts).
 // The last workgroup makes the scatter's plan meanwhile: on its own it was a
 // launch of one workgroup, 10 us of search latency per iteration.
-template <bool WIDE>
 __global__ __launch_bounds__(kMergeThreads) void k_push_expand(const uint16_t *__restrict__ row_dst_lo,
                                                                const int32_t *__restrict__ block_ptr,
                                                                const int32_t *__restrict__ block_items,
@@ -199,35 +198,41 @@ __global__ __launch_bounds__(kMergeThreads) void k_push_expand(const uint16_t *_
     const int32_t share = ((((F1 - F0) + 15) / 16) + 63) & ~63;
     const int32_t fa = min(F0 + w * share, F1), fb = min(fa + share, F1);
     if (fa >= fb) return;  // uniform over the wave
-    int32_t sw = __builtin_amdgcn_readfirstlane(run_of(pre, k, fa));
-    int32_t i_safe = __builtin_amdgcn_readfirstlane(ofs[sw]) + fa;
-    for (int32_t f0 = fa; f0 < fb; f0 += kWave * kExpandUnroll) {
-        int32_t idx[kExpandUnroll], d[kExpandUnroll];
-        int32_t sl = WIDE ? run_of(pre, k, f0) : 0;
+    RangeWalk walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
+    int32_t f0 = fa;
+    for (; f0 + kWave * kExpandUnroll <= fb; f0 += kWave * kExpandUnroll) {
+        uint32_t idx[kExpandUnroll];
+        uint16_t d[kExpandUnroll];
 #pragma unroll
         for (int u = 0; u < kExpandUnroll; ++u) {
             const int32_t fs = f0 + u * kWave;
-            const int32_t f = fs + lane;
-            const bool valid = f < fb;
-            int32_t i;
-            if (WIDE) {
-                const int32_t ff = valid ? f : f0;
-                sl = advance<true>(pre, k, sl, ff);
-                i = ofs[sl] + ff;
-            } else if (fs < fb) {  // uniform
-                const int32_t ii = window_index(ofs, pre, sw, fs, min(fs + kWave - 1, fb - 1), f);
-                i_safe = __builtin_amdgcn_readfirstlane(ii);
-                i = valid ? ii : i_safe;
-            } else {
-                i = i_safe;
-            }
-            d[u] = (int32_t)row_dst_lo[i];
-            idx[u] = valid ? i : -1;
+            idx[u] = (uint32_t)walk.index(fs + kWave - 1, fs + lane);
+            d[u] = row_dst_lo[idx[u]];
         }
 #pragma unroll
-        for (int u = 0; u < kExpandUnroll; ++u)
-            if (idx[u] >= 0) vals[idx[u]] = xs[d[u]];
+        for (int u = 0; u < kExpandUnroll; ++u) vals[idx[u]] = xs[d[u]];
     }
+    if (f0 >= fb) return;
+    // the last pass tests its lanes
+    int32_t idx[kExpandUnroll], d[kExpandUnroll];
+    int32_t i_safe = 0;
+#pragma unroll
+    for (int u = 0; u < kExpandUnroll; ++u) {
+        const int32_t fs = f0 + u * kWave;
+        const int32_t f = fs + lane;
+        const bool valid = f < fb;
+        int32_t i = i_safe;
+        if (fs < fb) {  // uniform, and so for u = 0
+            const int32_t ii = walk.index(min(fs + kWave - 1, fb - 1), f);
+            i_safe = __builtin_amdgcn_readfirstlane(ii);
+            i = valid ? ii : i_safe;
+        }
+        d[u] = (int32_t)row_dst_lo[i];
+        idx[u] = valid ? i : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kExpandUnroll; ++u)
+        if (idx[u] >= 0) vals[idx[u]] = xs[d[u]];
 }
 
 // ------------------------------------------------------------------ scatter
@@ -627,17 +632,10 @@ static cagra_status push_edges(const cagra_segments *seg, const void *x, void *v
                            ws.pfirst,     ws.piece_tile,  ws.piece_seg};
     if (seg->Q > 0) {
         const size_t lds = push_expand_lds_bytes(seg->B, seg->k);
-        const bool wide = seg->Q < (int64_t)kWave * seg->k * seg->nb;
-        if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand<true>)) return a_;
-        if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand<false>)) return a_;
-        if (wide)
-            k_push_expand<true><<<seg->max_items + 1, kMergeThreads, lds, st>>>(
-                seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
-                seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
-        else
-            k_push_expand<false><<<seg->max_items + 1, kMergeThreads, lds, st>>>(
-                seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
-                seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
+        if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand)) return a_;
+        k_push_expand<<<seg->max_items + 1, kMergeThreads, lds, st>>>(
+            seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
+            seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
         CAGRA_LAUNCH_CHECK();
     } else {
         k_push_plan<<<1, kPlanThreads, 0, st>>>(plan);
