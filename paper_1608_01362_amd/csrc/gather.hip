@@ -235,18 +235,30 @@ __device__ __forceinline__ void load_chunk(v4i (&r)[kLoads<W>], __amdgpu_buffer_
 constexpr int kStagesDeep = 8;
 constexpr int kStagesDefault = 4;
 constexpr int32_t kDeepTileEdges = 131072;  // tiles at least this long take kStagesDeep
+constexpr int64_t kSplitEdges = 49152;      // shorter tiles stay whole (split_plan)
+constexpr int kXcds = 8, kXcdCus = 32;
 
-template <class Op, typename VT, bool STAGED, typename W, int DEPTH>
+// Tile t; with SPLIT, part `part` of nparts (1, 2, 4, 8 or 16) of its spans.
+// Wave w takes span part * per + w: the first `per` waves produce their rows,
+// and the others read on only as far as the first row start of the spans that
+// follow, whose heads complete the part's last row. The heads are summed as
+// in the whole tile, so the result does not depend on the split.
+template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool SPLIT>
 __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int64_t Q,
                                             const int32_t *__restrict__ tile_edge,
                                             const int32_t *__restrict__ tile_seg,
                                             const int32_t *__restrict__ span_row, const VT *__restrict__ values,
-                                            int32_t V, int32_t N, int t, typename Op::T *__restrict__ partial,
-                                            unsigned char *smem, const uint32_t *__restrict__ seg_active) {
+                                            int32_t V, int32_t N, int t, int part, int nparts,
+                                            typename Op::T *__restrict__ partial, unsigned char *smem,
+                                            const uint32_t *__restrict__ seg_active) {
     using T = typename Op::T;
     VT *seg_vals = reinterpret_cast<VT *>(smem + kStageBytes);
     const int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
     if (e0 >= e1) return;  // empty tile (uniform over the workgroup)
+    if (SPLIT && nparts > 1 && e1 - e0 < kSplitEdges) {  // uniform: not worth it
+        if (part > 0) return;
+        nparts = 1;
+    }
     const int32_t s = tile_seg[t];
     // an inactive segment (no source in the frontier) contributes nothing: its
     // rows are skipped here and by the merge
@@ -262,12 +274,15 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
 
     // wave index as a scalar, so that everything derived from it stays in SGPRs
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int per = SPLIT ? kGatherWaves / nparts : kGatherWaves;
+    const int sp = SPLIT ? part * per + w : w;
+    const bool head_only = SPLIT && w >= per;
     const int64_t sl = (e1 - e0 + kGatherWaves - 1) / kGatherWaves;
-    int64_t w0 = e0 + w * sl;
-    if (w0 > e1) w0 = e1;
+    int64_t w0 = e0 + sp * sl;
+    if (w0 > e1 || (SPLIT && sp >= kGatherWaves)) w0 = e1;
     int64_t w1 = w0 + sl;
     if (w1 > e1) w1 = e1;
-    const int32_t row0 = span_row[(int64_t)t * kGatherWaves + w];
+    const int32_t row0 = span_row[(int64_t)t * kGatherWaves + (SPLIT ? min(sp, kGatherWaves - 1) : w)];
 
     // Buffer descriptors: loads past the share read zero, and stores to rows
     // outside [row0, Q) are dropped, so the loop needs no bounds branches.
@@ -279,7 +294,7 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
         (void *)(edge_src + ebase), 0, (int32_t)align_up((size_t)(w1 - ebase) * kWB, 4), kBufFlags);
     int64_t rows_left = Q - row0;
     if (rows_left > (1 << 28)) rows_left = 1 << 28;
-    if (rows_left < 0) rows_left = 0;
+    if (rows_left < 0 || head_only) rows_left = 0;
     const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(partial + row0), 0, (int32_t)(rows_left * (int64_t)sizeof(T)), kBufFlags);
 
@@ -293,9 +308,11 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
 #pragma unroll
     for (int c = 0; c < kSt - 1; ++c) load_chunk<W>(R[c], ein, (uint32_t)(c * kChunk * kWB) + lane_off);
     for (int64_t cc = 0; cc < len; cc += kSt * kChunk) {
+        if (SPLIT && head_only && S.nflags > 0) break;
 #pragma unroll
         for (int c = 0; c < kSt; ++c) {
             if (cc + c * kChunk >= len) break;  // uniform: len and cc are wave-wide
+            if (SPLIT && head_only && S.nflags > 0) break;  // uniform
             load_chunk<W>(R[(c + kSt - 1) % kSt], ein,
                           (uint32_t)((cc + (c + kSt - 1) * kChunk) * kWB) + lane_off);
             const int32_t rel0 = (int32_t)(ebase + cc + c * kChunk - w0);
@@ -309,17 +326,17 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
     // complete rows that continue into later waves' shares, in wave order
     __syncthreads();  // all waves are done with the staged values
     WaveFix<T> *fix = reinterpret_cast<WaveFix<T> *>(smem);
-    if (lane == 0) {
+    if (lane == 0 && (!SPLIT || sp < kGatherWaves)) {
         WaveFix<T> f;
         f.has = S.nflags > 0;
         f.head = f.has ? S.head : S.carry;
         f.last = S.carry;
         f.row = row0 + S.nflags - 1;
-        fix[w] = f;
+        fix[sp] = f;
     }
     __syncthreads();
-    if (threadIdx.x < kGatherWaves) {
-        const int ww = threadIdx.x;
+    if (threadIdx.x < per) {
+        const int ww = SPLIT ? part * per + (int)threadIdx.x : (int)threadIdx.x;
         if (fix[ww].has) {
             T tot = fix[ww].last;
             for (int x = ww + 1; x < kGatherWaves; ++x) {
@@ -331,25 +348,48 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
     }
 }
 
-template <class Op, typename VT, bool STAGED, typename W, int DEPTH>
+// SPLIT: how the tiles of each XCD (a contiguous range, as xcd_remap) map to its
+// workgroups: the first `whole` workgroups take a tile each, the others 1 / parts
+// of one of the tiles left.
+struct SplitPlan {
+    int32_t whole, parts;
+};
+
+template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool SPLIT>
 __global__ __launch_bounds__(kGatherThreads) void k_gather(
     const W *__restrict__ edge_src, int64_t E, int64_t Q, const int32_t *__restrict__ tile_edge,
     const int32_t *__restrict__ tile_seg, const int32_t *__restrict__ span_row, const VT *__restrict__ values,
     int32_t V, int32_t N, int32_t ntiles, typename Op::T *__restrict__ partial,
-    const uint32_t *__restrict__ seg_active, unsigned long long *__restrict__ clear) {
+    const uint32_t *__restrict__ seg_active, unsigned long long *__restrict__ clear, SplitPlan plan) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     (void)E;
     // the counter of the merge that follows on the stream (null: none)
     if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
-    gather_tile<Op, VT, STAGED, W, DEPTH>(edge_src, Q, tile_edge, tile_seg, span_row, values, V, N,
-                                          xcd_remap(blockIdx.x, ntiles), partial, smem, seg_active);
+    int t = 0, part = 0, parts = 1;
+    if constexpr (SPLIT) {
+        const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+        const int q = ntiles / kXcds, r = ntiles % kXcds;
+        int m = i;
+        if (i >= plan.whole) {
+            parts = plan.parts;
+            m = plan.whole + (i - plan.whole) / parts;
+            part = (i - plan.whole) % parts;
+        }
+        if (m >= q + (x < r ? 1 : 0)) return;  // uniform
+        t = x * q + min(x, r) + m;
+    } else {
+        t = xcd_remap(blockIdx.x, ntiles);
+    }
+    gather_tile<Op, VT, STAGED, W, DEPTH, SPLIT>(edge_src, Q, tile_edge, tile_seg, span_row, values, V, N, t, part,
+                                                 parts, partial, smem, seg_active);
 }
 
-// Persistent form over many graphs: workgroups stride over a global tile list.
+// Over many graphs: workgroups stride over a global tile list.
 __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc *__restrict__ desc,
                                                                  const int32_t *__restrict__ tile_graph,
                                                                  int64_t total_tiles, int parity,
-                                                                 unsigned long long *__restrict__ tickets, int32_t ngraphs) {
+                                                                 unsigned long long *__restrict__ tickets,
+                                                                 int32_t ngraphs) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // the counters of the merge that follows on the stream
     if (blockIdx.x == 0)
@@ -358,10 +398,26 @@ __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc
         __syncthreads();  // LDS reuse across tiles
         const int gi = tile_graph[gt];
         const MultiDesc &d = desc[gi];
-        gather_tile<OpSum, float, true, uint16_t, kStagesDefault>(static_cast<const uint16_t *>(d.edge_src), d.Q, d.tile_edge, d.tile_seg, d.tile_span_row,
-                                        d.contrib[parity], d.V, d.N, (int)(gt - d.tile_base), d.partial, smem,
-                                        nullptr);
+        gather_tile<OpSum, float, true, uint16_t, kStagesDefault, false>(
+            static_cast<const uint16_t *>(d.edge_src), d.Q, d.tile_edge, d.tile_seg, d.tile_span_row, d.contrib[parity],
+            d.V, d.N, (int)(gt - d.tile_base), 0, 1, d.partial, smem, nullptr);
     }
+}
+
+// Tiles are long (they amortize a segment's staging), so a launch is a few rounds
+// of one or two workgroups per CU, and the last round is often nearly empty; a
+// small graph is one such round. If it leaves at least half of the CUs idle, its
+// tiles are cut into as many parts as there are CUs for. R-MAT, 262,144-edge
+// tiles: 2 to 17 tiles 36-38 -> 24-27 us, 70 tiles 42 -> 34, 294 tiles 90 -> 79;
+// 65,536-edge tiles: 8 to 65 tiles 12.8-13.8 -> 10-12. Tiles of 32,768 edges lose
+// (9.6 -> 10.6 us), as does one more round after many (4,442 tiles: 0.3%).
+constexpr int kSplitRounds = 4;         // after more whole rounds the last one is too
+static SplitPlan split_plan(int64_t n, int slots) {  // n: tiles, slots: workgroups at a time, per XCD
+    const int64_t left = n % slots;
+    int parts = 1;
+    if (n / slots <= kSplitRounds)
+        while (left > 0 && 2 * parts <= kGatherWaves && left * 2 * parts <= kXcdCus) parts *= 2;
+    return {(int32_t)(n - left), parts};
 }
 
 cagra_status launch_multi_gather(const MultiDesc *desc, const int32_t *tile_graph, int64_t total_tiles, int parity,
@@ -378,14 +434,27 @@ template <class Op, typename VT, bool STAGED, typename W>
 static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values, typename Op::T *partial,
                                     const uint32_t *seg_active, unsigned long long *clear, hipStream_t st) {
     if (seg->ntiles == 0) return CAGRA_OK;
-    auto kern = k_gather<Op, VT, STAGED, W, kStagesDefault>;
-    if constexpr (STAGED && sizeof(W) == 2)
-        if (seg->tile_edges >= kDeepTileEdges) kern = k_gather<Op, VT, STAGED, W, kStagesDeep>;
+    auto kern = k_gather<Op, VT, STAGED, W, kStagesDefault, false>;
     const size_t lds = kStageBytes + (STAGED ? (size_t)seg->N * sizeof(VT) : 0);
+    SplitPlan plan = {seg->ntiles, 1};
+    int grid = seg->ntiles;
+    if constexpr (STAGED) {
+        const bool deep = sizeof(W) == 2 && seg->tile_edges >= kDeepTileEdges;
+        if (seg->tile_edges >= kSplitEdges) {
+            const int64_t n = ceil_div(seg->ntiles, kXcds);
+            plan = split_plan(n, kXcdCus * (!deep && 2 * lds <= CAGRA_LDS_BYTES ? 2 : 1));
+            if (plan.parts > 1) grid = (int)(kXcds * (plan.whole + (n - plan.whole) * plan.parts));
+        }
+        if (plan.parts > 1) kern = k_gather<Op, VT, STAGED, W, kStagesDefault, true>;
+        if constexpr (sizeof(W) == 2)
+            if (deep)
+                kern = plan.parts > 1 ? k_gather<Op, VT, STAGED, W, kStagesDeep, true>
+                                      : k_gather<Op, VT, STAGED, W, kStagesDeep, false>;
+    }
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
-    kern<<<seg->ntiles, kGatherThreads, lds, st>>>(static_cast<const W *>(seg->edge_src), seg->E, seg->Q,
-                                                  seg->tile_edge, seg->tile_seg, seg->tile_span_row, values, seg->V,
-                                                  seg->N, seg->ntiles, partial, seg_active, clear);
+    kern<<<grid, kGatherThreads, lds, st>>>(static_cast<const W *>(seg->edge_src), seg->E, seg->Q, seg->tile_edge,
+                                            seg->tile_seg, seg->tile_span_row, values, seg->V, seg->N, seg->ntiles,
+                                            partial, seg_active, clear, plan);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
