@@ -23,10 +23,10 @@
 //
 // Bytes: 4 E + 4 E (random reads of inv) + 4 E, against the 16 E of each of six
 // or seven passes of the edge-key sort it replaces. Clustering R-MAT 24 / ef 24:
-// 20.5 -> 9.6 ms (light tiles 6.3, pieces 2.1, merges 0.4), R-MAT 25 / ef 32
+// 20.5 -> 9.2 ms (light tiles 5.4, pieces 1.9, merges 0.4), R-MAT 25 / ef 32
 // 59.5 -> 25.3 ms. What bounds it is the lookup of the new ids: one random
 // 4-byte read per edge through L2 and the Infinity Cache, about 65 G/s. Rows of
-// neighbouring ids (a band of width 300) take 2.2 against 2.0 ms, a star of 3 M
+// neighbouring ids (a band of width 300) take 2.1 against 2.0 ms, a star of 3 M
 // edges 0.53 against 0.40 ms (nine merge levels).
 #include "rowsort.h"
 
@@ -45,6 +45,7 @@ constexpr int kLightMax = kRsCap - kRsTile;    // longest light row
 constexpr int kMaxSlot = 96;                   // edges per slot beyond which a slot is spread again
 constexpr int kRefine = 3;                     // times at most, before the tile is sorted
 constexpr int kUnit = 4096;                    // output edges of a merge unit
+constexpr int kShortItems = 10;                // items per thread for tiles of at most 5,120 edges
 constexpr int kCellBits = 6;                   // cells of G per power of two
 constexpr int kCells = (32 - kCellBits) << kCellBits;
 static_assert(kLightMax >= kRsTile, "a longer row is the last one of its tile");
@@ -78,6 +79,7 @@ struct HeavyCount {
     unsigned long long rows_units;  // heavy rows << 32 | merge units
     int32_t levels;                 // most merge levels of a row
     int32_t crowded[2];             // light tiles and pieces left to the second kernel
+    int32_t lengthy;                // light tiles of more than kShortItems edges per thread
     __device__ __forceinline__ int32_t units() const { return (int32_t)(uint32_t)rows_units; }
 };
 
@@ -86,7 +88,7 @@ struct HeavyCount {
 __global__ __launch_bounds__(1024) void k_rs_table(const int32_t *__restrict__ cum,
                                                    const int32_t *__restrict__ outdeg, int32_t V,
                                                    uint32_t *__restrict__ tab, HeavyCount *__restrict__ hc) {
-    if (threadIdx.x == 0) *hc = HeavyCount{0ull, 0, {0, 0}};
+    if (threadIdx.x == 0) *hc = HeavyCount{0ull, 0, {0, 0}, 0};
     constexpr int kPer = (kCells + 1 + 1023) / 1024;
     __shared__ uint32_t wmax[16];
     const double total = (double)cum[V - 1] + (double)outdeg[V - 1];
@@ -163,9 +165,15 @@ __global__ __launch_bounds__(256) void k_rs_units(const int32_t *__restrict__ no
 
 // ---- sorting a tile
 
+// ITEMS: edges per thread, at most. Most light tiles hold about kRsTile edges: with
+// kShortItems three workgroups fit a CU in place of two (registers), and more
+// lookups of new ids are in flight (R-MAT 24 / ef 24: 6.06 -> 5.43 ms; at four
+// workgroups the registers spill, 6.48 ms).
+template <int ITEMS>
 struct SortLds {
-    uint32_t key[kRsCap];                       // row tables before, ids after
-    uint32_t cnt[kRsCap / 2 + 4];               // two 16-bit slot counts (then starts) a word, and the end
+    static constexpr int kItems = ITEMS, kCap = ITEMS * kRsThreads;
+    uint32_t key[kCap];                         // row tables before, ids after
+    uint32_t cnt[kCap / 2 + 4];                 // two 16-bit slot counts (then starts) a word, and the end
     uint32_t tab[kCells + 1];
     unsigned long long starts[kRsCap / kWave];  // row starts of the tile, one bit an edge
     int32_t before[kRsCap / kWave];             // row starts before each 64 edges
@@ -177,31 +185,33 @@ __device__ __forceinline__ uint32_t get16(const uint32_t *a, uint32_t i) {
     return reinterpret_cast<const uint16_t *>(a)[i];
 }
 
-// Counts the tile's edges per slot (slots below kRsCap) and scans the counts:
+// Counts the tile's edges per slot (slots below the cap) and scans the counts:
 // afterwards lo[j] = first place of item j's slot | its edges << 16, and
 // slot[j] holds, above the slot, the edge's turn among those of its slot (as
 // the atomics fell). Returns whether some slot holds more than kMaxSlot edges.
-__device__ __forceinline__ bool count_slots(SortLds &L, uint32_t (&slot)[kRsItems], uint32_t (&lo)[kRsItems],
+template <int ITEMS>
+__device__ __forceinline__ bool count_slots(SortLds<ITEMS> &L, uint32_t (&slot)[ITEMS], uint32_t (&lo)[ITEMS],
                                             int32_t n) {
+    constexpr int kCap = SortLds<ITEMS>::kCap;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     __syncthreads();  // whatever was in the counts is read
 #pragma unroll
-    for (int i = 0; i < kRsCap / 2 / kRsThreads; ++i) L.cnt[i * kRsThreads + tid] = 0u;
+    for (int i = 0; i < kCap / 2 / kRsThreads; ++i) L.cnt[i * kRsThreads + tid] = 0u;
     if (tid == 0) L.most = 0;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         const uint32_t s = slot[j], sh = (s & 1u) * 16u;
         uint32_t had = 0;
         if (j * kRsThreads + tid < n) had = atomicAdd(&L.cnt[s >> 1], 1u << sh);
         slot[j] = s | ((had >> sh) << 16);
     }
     __syncthreads();
-    // exclusive scan, 16 consecutive slots per thread
-    uint32_t c[kRsItems / 2], sum = 0, most = 0;
+    // exclusive scan, ITEMS consecutive slots per thread
+    uint32_t c[ITEMS / 2], sum = 0, most = 0;
 #pragma unroll
-    for (int i = 0; i < kRsItems / 2; ++i) {
-        c[i] = L.cnt[tid * (kRsItems / 2) + i];
+    for (int i = 0; i < ITEMS / 2; ++i) {
+        c[i] = L.cnt[tid * (ITEMS / 2) + i];
         sum += (c[i] & 0xffffu) + (c[i] >> 16);
         most = max(most, max(c[i] & 0xffffu, c[i] >> 16));
     }
@@ -217,15 +227,15 @@ __device__ __forceinline__ bool count_slots(SortLds &L, uint32_t (&slot)[kRsItem
     uint32_t at = incl - sum;
     for (int x = 0; x < w; ++x) at += L.wsum[x];
 #pragma unroll
-    for (int i = 0; i < kRsItems / 2; ++i) {
+    for (int i = 0; i < ITEMS / 2; ++i) {
         const uint32_t a = at, b = at + (c[i] & 0xffffu);
         at = b + (c[i] >> 16);
-        L.cnt[tid * (kRsItems / 2) + i] = a | (b << 16);
+        L.cnt[tid * (ITEMS / 2) + i] = a | (b << 16);
     }
-    if (tid == 0) L.cnt[kRsCap / 2] = (uint32_t)n;  // the end, read for the last slot
+    if (tid == 0) L.cnt[kCap / 2] = (uint32_t)n;  // the end, read for the last slot
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) {  // items past the tile have a slot too; unused
+    for (int j = 0; j < ITEMS; ++j) {  // items past the tile have a slot too; unused
         const uint32_t s = slot[j] & 0xffffu, a = get16(L.cnt, s);
         lo[j] = a | ((get16(L.cnt, s + 1) - a) << 16);
     }
@@ -235,28 +245,30 @@ __device__ __forceinline__ bool count_slots(SortLds &L, uint32_t (&slot)[kRsItem
 // Spreads the slots of more than kMaxSlot edges over their places by linear
 // interpolation between their smallest and largest id; the other slots become
 // their first place. The order of slots stays the order of ids.
-__device__ __forceinline__ void refine_slots(SortLds &L, const uint32_t (&key)[kRsItems], uint32_t (&slot)[kRsItems],
-                                             const uint32_t (&lo)[kRsItems], int32_t n) {
+template <int ITEMS>
+__device__ __forceinline__ void refine_slots(SortLds<ITEMS> &L, const uint32_t (&key)[ITEMS], uint32_t (&slot)[ITEMS],
+                                             const uint32_t (&lo)[ITEMS], int32_t n) {
+    constexpr int kCap = SortLds<ITEMS>::kCap;
     const int tid = threadIdx.x;
-    uint32_t least[kRsItems];
+    uint32_t least[ITEMS];
     auto big = [&](int j) { return j * kRsThreads + tid < n && (lo[j] >> 16) > (uint32_t)kMaxSlot; };
-    for (int i = tid; i < kRsCap; i += kRsThreads) L.key[i] = ~0u;
+    for (int i = tid; i < kCap; i += kRsThreads) L.key[i] = ~0u;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j)
+    for (int j = 0; j < ITEMS; ++j)
         if (big(j)) atomicMin(&L.key[lo[j] & 0xffffu], key[j]);
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) least[j] = big(j) ? L.key[lo[j] & 0xffffu] : 0u;
+    for (int j = 0; j < ITEMS; ++j) least[j] = big(j) ? L.key[lo[j] & 0xffffu] : 0u;
     __syncthreads();
-    for (int i = tid; i < kRsCap; i += kRsThreads) L.key[i] = 0u;
+    for (int i = tid; i < kCap; i += kRsThreads) L.key[i] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j)
+    for (int j = 0; j < ITEMS; ++j)
         if (big(j)) atomicMax(&L.key[lo[j] & 0xffffu], key[j]);
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         // rounding keeps the order; the last place takes what rounds up past it
         const uint32_t a = lo[j] & 0xffffu, m = lo[j] >> 16, span = L.key[a] - least[j];
         const uint32_t at = (uint32_t)((float)(key[j] - least[j]) * ((float)m / ((float)span + 1.0f)));
@@ -267,12 +279,14 @@ __device__ __forceinline__ void refine_slots(SortLds &L, const uint32_t (&key)[k
 
 // Orders the n edges held in (key, slot) across the workgroup (item j of thread
 // t valid when j * kRsThreads + t < n) and writes them to out[0 .. n). Slots
-// below kRsCap. With ANY = false a crowded tile is not written: false comes back.
-template <bool ANY>
-__device__ __forceinline__ bool sort_tile(SortLds &L, const uint32_t (&key)[kRsItems], uint32_t (&slot)[kRsItems],
+// below the cap. With ANY = false a crowded tile is not written: false comes back.
+template <bool ANY, int ITEMS>
+__device__ __forceinline__ bool sort_tile(SortLds<ITEMS> &L, const uint32_t (&key)[ITEMS], uint32_t (&slot)[ITEMS],
                                           int32_t n, int32_t *__restrict__ out) {
+    [[maybe_unused]] constexpr int kCap = SortLds<ITEMS>::kCap;
+    static_assert(!ANY || (kCap & (kCap - 1)) == 0, "the bitonic sort's length");
     const int tid = threadIdx.x;
-    uint32_t lo[kRsItems];
+    uint32_t lo[ITEMS];
     bool crowded = count_slots(L, slot, lo, n);
     if constexpr (ANY) {
 #pragma unroll 1
@@ -285,11 +299,11 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint32_t (&key)[kRsI
     }
     if (!ANY || !crowded) {
 #pragma unroll
-        for (int j = 0; j < kRsItems; ++j)
+        for (int j = 0; j < ITEMS; ++j)
             if (j * kRsThreads + tid < n) L.key[(lo[j] & 0xffffu) + (slot[j] >> 16)] = key[j];
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kRsItems; ++j) {
+        for (int j = 0; j < ITEMS; ++j) {
             const uint32_t a = lo[j] & 0xffffu, m = j * kRsThreads + tid < n ? lo[j] >> 16 : 0u;
             uint32_t less = 0;
             for (uint32_t q = 0; m > 1 && q < m; ++q) less += L.key[a + q] < key[j] ? 1u : 0u;
@@ -297,21 +311,21 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint32_t (&key)[kRsI
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kRsItems; ++j)
+        for (int j = 0; j < ITEMS; ++j)
             if (j * kRsThreads + tid < n) L.key[lo[j]] = key[j];
     } else {
         uint16_t *sl = reinterpret_cast<uint16_t *>(L.cnt);
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kRsItems; ++j) {
+        for (int j = 0; j < ITEMS; ++j) {
             const int i = j * kRsThreads + tid;
             L.key[i] = i < n ? key[j] : ~0u;
             sl[i] = i < n ? (uint16_t)(slot[j] & 0xffffu) : (uint16_t)0xffffu;
         }
-        for (int k = 2; k <= kRsCap; k <<= 1)
+        for (int k = 2; k <= kCap; k <<= 1)
             for (int d = k >> 1; d >= 1; d >>= 1) {
                 __syncthreads();
-                for (int p = tid; p < kRsCap / 2; p += kRsThreads) {
+                for (int p = tid; p < kCap / 2; p += kRsThreads) {
                     const int a = 2 * p - (p & (d - 1)), b = a + d;
                     const uint32_t sa = sl[a], sb = sl[b], ka = L.key[a], kb = L.key[b];
                     const bool after = sa != sb ? sa > sb : ka > kb;
@@ -330,8 +344,11 @@ __device__ __forceinline__ bool sort_tile(SortLds &L, const uint32_t (&key)[kRsI
 }
 
 // Tile t: the light rows that start in output edges [t * kRsTile, (t + 1) * kRsTile).
-template <bool ANY>
-__device__ __forceinline__ bool sort_light(SortLds &L, const int32_t *__restrict__ in_offsets,
+// Returns 0, or why the tile was not written: kCrowded, or kLengthy (more edges
+// than the workgroup takes).
+enum { kSorted, kCrowded, kLengthy };
+template <bool ANY, int ITEMS>
+__device__ __forceinline__ int sort_light(SortLds<ITEMS> &L, const int32_t *__restrict__ in_offsets,
                                            const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
                                            const int32_t *__restrict__ inv, const RowList &list, int64_t E, int32_t t,
                                            int32_t *__restrict__ out) {
@@ -361,7 +378,8 @@ __device__ __forceinline__ bool sort_light(SortLds &L, const int32_t *__restrict
     }
     __syncthreads();
     const int32_t e0 = L.lo, e1 = L.hi;
-    if (e1 == 0) return true;  // uniform: no light row starts here
+    if (e1 == 0) return kSorted;  // uniform: no light row starts here
+    if (ITEMS < kRsItems && e1 - e0 > SortLds<ITEMS>::kCap) return kLengthy;  // uniform
     // the light rows of a tile are consecutive: only the last row that starts in it can be heavy
     if (tid < kWave) {
         constexpr int kPer = kRsCap / kWave / kWave;  // 64-edge words per lane
@@ -383,8 +401,8 @@ __device__ __forceinline__ bool sort_light(SortLds &L, const int32_t *__restrict
             L.before[lane * kPer + i] = at;
             at += c[i];
         }
-        // row tables: old position of output edge e of row o = delta[o] + e; first edge of row o
-        if (lane == 63) reinterpret_cast<uint16_t *>(L.cnt)[at] = (uint16_t)e1;
+        // row tables: old position of the tile's edge e in row o = delta[o] + e; first edge of row o, from e0
+        if (lane == 63) reinterpret_cast<uint16_t *>(L.cnt)[at] = (uint16_t)(e1 - e0);
     }
     __syncthreads();
     int32_t *delta = reinterpret_cast<int32_t *>(L.key);
@@ -394,14 +412,14 @@ __device__ __forceinline__ bool sort_light(SortLds &L, const int32_t *__restrict
         if (len <= kLightMax) {
             const int32_t o = L.before[a >> 6] + (int32_t)__popcll(L.starts[a >> 6] & ((1ull << (a & 63)) - 1ull));
             delta[o] = in_offsets[perm[list.row[i]]] - a;
-            begin[o] = (uint16_t)a;
+            begin[o] = (uint16_t)(a - e0);
         }
     }
     __syncthreads();
     const int32_t n = e1 - e0;
-    uint32_t key[kRsItems], slot[kRsItems];
+    uint32_t key[ITEMS], slot[ITEMS];
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         // items past the tile read its first edge, unused
         const int32_t e = e0 + (j * kRsThreads + tid < n ? j * kRsThreads + tid : 0);
         const int32_t o = L.before[e >> 6] + (int32_t)__popcll(L.starts[e >> 6] & (~0ull >> (63 - (e & 63)))) - 1;
@@ -409,30 +427,53 @@ __device__ __forceinline__ bool sort_light(SortLds &L, const int32_t *__restrict
         key[j] = (uint32_t)in_sources[(int64_t)delta[o] + e];
     }
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) key[j] = (uint32_t)inv[key[j]];
+    for (int j = 0; j < ITEMS; ++j) key[j] = (uint32_t)inv[key[j]];
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j)
+    for (int j = 0; j < ITEMS; ++j)
         slot[j] = (slot[j] & 0xffffu) + __umulhi(slot[j] >> 16, fraction(L.tab, key[j]));
-    return sort_tile<ANY>(L, key, slot, n, out + base + e0);
+    return sort_tile<ANY>(L, key, slot, n, out + base + e0) ? kSorted : kCrowded;
 }
 
-__device__ __forceinline__ void load_table(SortLds &L, const uint32_t *__restrict__ tab) {
+template <int ITEMS>
+__device__ __forceinline__ void load_table(SortLds<ITEMS> &L, const uint32_t *__restrict__ tab) {
     for (int i = threadIdx.x; i <= kCells; i += kRsThreads) L.tab[i] = tab[i];
 }
 
 // One tile per workgroup; the crowded ones are listed for k_rs_light_crowded,
-// whose further passes need twice the registers.
-__global__ __launch_bounds__(kRsThreads, 4) void k_rs_light(
+// whose further passes need twice the registers, and the lengthy ones, whose last
+// rows run far past kRsTile, for k_rs_light_lengthy.
+__global__ __launch_bounds__(kRsThreads, 6) void k_rs_light(
     const int32_t *__restrict__ in_offsets, const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ inv, RowList list, int64_t E, const uint32_t *__restrict__ tab, int32_t tiles,
-    HeavyCount *__restrict__ hc, int32_t *__restrict__ crowded,
+    HeavyCount *__restrict__ hc, int32_t *__restrict__ crowded, int32_t *__restrict__ lengthy,
     int32_t *__restrict__ out) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    SortLds &L = *reinterpret_cast<SortLds *>(smem);
+    auto &L = *reinterpret_cast<SortLds<kShortItems> *>(smem);
     load_table(L, tab);  // ordered by the barriers before its first use
     const int32_t t = xcd_remap(blockIdx.x, tiles);
-    if (!sort_light<false>(L, in_offsets, in_sources, perm, inv, list, E, t, out) && threadIdx.x == 0)
-        crowded[atomicAdd(&hc->crowded[0], 1)] = t;
+    const int r = sort_light<false>(L, in_offsets, in_sources, perm, inv, list, E, t, out);
+    if (threadIdx.x == 0) {
+        if (r == kCrowded) crowded[atomicAdd(&hc->crowded[0], 1)] = t;
+        if (r == kLengthy) lengthy[atomicAdd(&hc->lengthy, 1)] = t;
+    }
+}
+
+__global__ __launch_bounds__(kRsThreads, 4) void k_rs_light_lengthy(
+    const int32_t *__restrict__ in_offsets, const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ inv, RowList list, int64_t E, const uint32_t *__restrict__ tab,
+    HeavyCount *__restrict__ hc, int32_t *__restrict__ crowded, const int32_t *__restrict__ lengthy,
+    int32_t *__restrict__ out) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    auto &L = *reinterpret_cast<SortLds<kRsItems> *>(smem);
+    const int32_t n = hc->lengthy;
+    if ((int32_t)blockIdx.x >= n) return;
+    load_table(L, tab);
+    for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const int32_t t = lengthy[i];
+        if (sort_light<false>(L, in_offsets, in_sources, perm, inv, list, E, t, out) == kCrowded && threadIdx.x == 0)
+            crowded[atomicAdd(&hc->crowded[0], 1)] = t;
+        __syncthreads();  // the next tile reuses the LDS
+    }
 }
 
 __global__ __launch_bounds__(kRsThreads, 2) void k_rs_light_crowded(
@@ -441,7 +482,7 @@ __global__ __launch_bounds__(kRsThreads, 2) void k_rs_light_crowded(
     const HeavyCount *__restrict__ hc, const int32_t *__restrict__ crowded,
     int32_t *__restrict__ out) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    SortLds &L = *reinterpret_cast<SortLds *>(smem);
+    auto &L = *reinterpret_cast<SortLds<kRsItems> *>(smem);
     const int32_t n = hc->crowded[0];
     if ((int32_t)blockIdx.x >= n) return;
     load_table(L, tab);
@@ -453,7 +494,7 @@ __global__ __launch_bounds__(kRsThreads, 2) void k_rs_light_crowded(
 
 // The piece that starts at merge unit u (every other unit of a heavy row).
 template <bool ANY>
-__device__ __forceinline__ bool sort_piece(SortLds &L, const int32_t *__restrict__ in_offsets,
+__device__ __forceinline__ bool sort_piece(SortLds<kRsItems> &L, const int32_t *__restrict__ in_offsets,
                                            const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
                                            const int32_t *__restrict__ inv, const int32_t *__restrict__ noff,
                                            int32_t row, int32_t i, int32_t *__restrict__ out,
@@ -483,7 +524,7 @@ __global__ __launch_bounds__(kRsThreads, 4) void k_rs_pieces(
     const uint32_t *__restrict__ tab, int32_t *__restrict__ crowded, int32_t *__restrict__ out,
     int32_t *__restrict__ tmp) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    SortLds &L = *reinterpret_cast<SortLds *>(smem);
+    auto &L = *reinterpret_cast<SortLds<kRsItems> *>(smem);
     const int32_t units = hc->units();
     if ((int32_t)blockIdx.x >= units) return;
     load_table(L, tab);
@@ -504,7 +545,7 @@ __global__ __launch_bounds__(kRsThreads, 2) void k_rs_pieces_crowded(
     const uint32_t *__restrict__ tab, const int32_t *__restrict__ crowded, int32_t *__restrict__ out,
     int32_t *__restrict__ tmp) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    SortLds &L = *reinterpret_cast<SortLds *>(smem);
+    auto &L = *reinterpret_cast<SortLds<kRsItems> *>(smem);
     const int32_t n = hc->crowded[1];
     if ((int32_t)blockIdx.x >= n) return;
     load_table(L, tab);
@@ -604,7 +645,7 @@ __global__ __launch_bounds__(kMgThreads) void k_rs_merge(const int32_t *__restri
 }
 
 struct RsWs {
-    int32_t *tmp, *hrow, *hunit, *unit_row, *crowded;
+    int32_t *tmp, *hrow, *hunit, *unit_row, *crowded, *lengthy;
     uint32_t *tab;
     HeavyCount *hc;
 };
@@ -621,6 +662,7 @@ static void rs_layout(A &a, int64_t E, RsWs *w) {
     take(w->hunit, heavy);
     take(w->unit_row, units);
     take(w->crowded, tiles > units ? tiles : units);  // tiles, then pieces
+    take(w->lengthy, tiles);
     take(w->tab, kCells + 1);
     take(w->hc, 1);
 }
@@ -638,10 +680,10 @@ cagra_status sort_rows(const int32_t *in_offsets, const int32_t *in_sources, int
     Arena ar{(char *)ws, ws_bytes, 0};
     RsWs w{};
     rs_layout(ar, E, &w);
-    if (!w.tmp || !w.hrow || !w.hunit || !w.unit_row || !w.crowded || !w.tab || !w.hc)
+    if (!w.tmp || !w.hrow || !w.hunit || !w.unit_row || !w.crowded || !w.lengthy || !w.tab || !w.hc)
         return fail(CAGRA_E_BUFFER, "workspace too small (row sort)");
-    for (const void *f : {(const void *)k_rs_light, (const void *)k_rs_light_crowded, (const void *)k_rs_pieces,
-                          (const void *)k_rs_pieces_crowded})
+    for (const void *f : {(const void *)k_rs_light, (const void *)k_rs_light_lengthy, (const void *)k_rs_light_crowded,
+                          (const void *)k_rs_pieces, (const void *)k_rs_pieces_crowded})
         if (cagra_status a_ = ensure_dynamic_lds(f)) return a_;
     const int32_t tiles = (int32_t)ceil_div(E, kRsTile);
     k_rs_table<<<1, 1024, 0, st>>>(cum, outdeg_new, V, w.tab, w.hc);
@@ -650,20 +692,23 @@ cagra_status sort_rows(const int32_t *in_offsets, const int32_t *in_sources, int
     if (cagra_status s = build_row_list(new_off, V, E, kRsTile, ar, &list, st)) return s;
     k_rs_units<<<(unsigned)ceil_div(V, 256), 256, 0, st>>>(new_off, V, w.hc, w.hrow, w.hunit, w.unit_row);
     CAGRA_LAUNCH_CHECK();
-    k_rs_light<<<(unsigned)tiles, kRsThreads, sizeof(SortLds), st>>>(
-        in_offsets, in_sources, perm, inv, list, E, w.tab, tiles, w.hc, w.crowded, out);
+    k_rs_light<<<(unsigned)tiles, kRsThreads, sizeof(SortLds<kShortItems>), st>>>(
+        in_offsets, in_sources, perm, inv, list, E, w.tab, tiles, w.hc, w.crowded, w.lengthy, out);
     CAGRA_LAUNCH_CHECK();
     // grids of resident workgroups that walk lists whose lengths the host does not know
     const int64_t units = E / kUnit + E / (kLightMax + 1) + 1;
     const unsigned grid = (unsigned)(units < 2048 ? units : 2048);
-    k_rs_light_crowded<<<(unsigned)(tiles < 256 ? tiles : 256), kRsThreads, sizeof(SortLds), st>>>(
+    k_rs_light_lengthy<<<(unsigned)(tiles < 2048 ? tiles : 2048), kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
+        in_offsets, in_sources, perm, inv, list, E, w.tab, w.hc, w.crowded, w.lengthy, out);
+    CAGRA_LAUNCH_CHECK();
+    k_rs_light_crowded<<<(unsigned)(tiles < 256 ? tiles : 256), kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
         in_offsets, in_sources, perm, inv, list, E, w.tab, w.hc, w.crowded, out);
     CAGRA_LAUNCH_CHECK();
     if (E <= kLightMax) return CAGRA_OK;  // no heavy row
-    k_rs_pieces<<<grid, kRsThreads, sizeof(SortLds), st>>>(in_offsets, in_sources, perm, inv, new_off, w.hc, w.hrow,
+    k_rs_pieces<<<grid, kRsThreads, sizeof(SortLds<kRsItems>), st>>>(in_offsets, in_sources, perm, inv, new_off, w.hc, w.hrow,
                                                            w.hunit, w.unit_row, w.tab, w.crowded, out, w.tmp);
     CAGRA_LAUNCH_CHECK();
-    k_rs_pieces_crowded<<<grid < 256 ? grid : 256, kRsThreads, sizeof(SortLds), st>>>(
+    k_rs_pieces_crowded<<<grid < 256 ? grid : 256, kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
         in_offsets, in_sources, perm, inv, new_off, w.hc, w.hrow, w.hunit, w.unit_row, w.tab, w.crowded, out, w.tmp);
     CAGRA_LAUNCH_CHECK();
     for (int32_t level = 0; ((int64_t)kRsCap << level) < E; ++level) {
