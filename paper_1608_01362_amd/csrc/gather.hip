@@ -30,42 +30,27 @@ constexpr size_t kStageBytes = (size_t)kGatherWaves * kStageRows * 4;
 
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 
-// Source value fetch: from the staged LDS copy, or from global memory.
-template <typename VT, bool STAGED>
-struct Fetch;
+// Staged value i. The kernels of this file have no static LDS, so their dynamic
+// LDS starts at address 0 and a value's address is a constant plus the word's
+// index bits: one instruction an edge less than an address from a pointer.
+template <typename VT>
+__device__ __forceinline__ VT staged(uint32_t i) {
+    return *(const __attribute__((address_space(3))) VT *)(uint32_t)(kStageBytes + i * sizeof(VT));
+}
+
+// Source values: Raw is what a load leaves in a register (32 bits, so that a load
+// in flight is not touched), value() what enters the sums.
+template <typename VT>
+struct Fetch {
+    using T = VT;
+    using Raw = VT;
+    static __device__ __forceinline__ T value(Raw r) { return r; }
+};
 template <>
-struct Fetch<float, true> {
+struct Fetch<uint16_t> {
     using T = float;
-    static __device__ __forceinline__ float get(const float *lds, const float *, int32_t i) { return lds[i]; }
-};
-template <>
-struct Fetch<float, false> {
-    using T = float;
-    static __device__ __forceinline__ float get(const float *, const float *g, int32_t i) { return g[i]; }
-};
-template <>
-struct Fetch<uint16_t, true> {
-    using T = float;
-    static __device__ __forceinline__ float get(const uint16_t *lds, const uint16_t *, int32_t i) {
-        return bf16_to_f32(lds[i]);
-    }
-};
-template <>
-struct Fetch<uint16_t, false> {
-    using T = float;
-    static __device__ __forceinline__ float get(const uint16_t *, const uint16_t *g, int32_t i) {
-        return bf16_to_f32(g[i]);
-    }
-};
-template <>
-struct Fetch<int32_t, true> {
-    using T = int32_t;
-    static __device__ __forceinline__ int32_t get(const int32_t *lds, const int32_t *, int32_t i) { return lds[i]; }
-};
-template <>
-struct Fetch<int32_t, false> {
-    using T = int32_t;
-    static __device__ __forceinline__ int32_t get(const int32_t *, const int32_t *g, int32_t i) { return g[i]; }
+    using Raw = uint32_t;
+    static __device__ __forceinline__ T value(Raw r) { return __uint_as_float(r << 16); }
 };
 
 template <typename T>
@@ -125,25 +110,18 @@ struct SpanState {
     int32_t nflags; // row starts seen in earlier chunks
 };
 
+// Where a wave's rows go: row row0, and the rows from there to the buffer's end.
+struct RowOut {
+    void *base;
+    int32_t rows;
+};
+
 // 16-byte loads per lane per chunk for edge words of type W.
 template <typename W>
 constexpr int kLoads = kEPT * (int)sizeof(W) / 16;
 
-// Processes one chunk of kChunk edges (this lane: kEPT consecutive edges).
-// rel0 is the chunk's first edge relative to the wave's share [0, len) (it is
-// negative for a first chunk that starts before the share); FULL chunks lie
-// entirely inside the share and skip the per-edge bounds tests. Rows finished
-// in the chunk are exactly chunk_nf consecutive rows starting at row0 + nflags
-// - 1; they are collected in `stage` and written with coalesced stores.
-template <class Op, typename VT, bool STAGED, typename W, bool FULL>
-__device__ __forceinline__ void process_chunk(const v4i (&wv)[kLoads<W>], int32_t rel0, int32_t len,
-                                              const VT *seg_vals, const VT *gvals, typename Op::T *stage,
-                                              __amdgpu_buffer_rsrc_t out, SpanState<typename Op::T> &S) {
-    using T = typename Op::T;
-    using F = Fetch<VT, STAGED>;
-    const int lane = __lane_id();
-    const int32_t rel = rel0 + lane * kEPT;
-    uint32_t w[kEPT];
+template <typename W>
+__device__ __forceinline__ void unpack_words(const v4i (&wv)[kLoads<W>], uint32_t (&w)[kEPT]) {
     if constexpr (sizeof(W) == 4) {
 #pragma unroll
         for (int j = 0; j < kLoads<W>; ++j)
@@ -156,20 +134,49 @@ __device__ __forceinline__ void process_chunk(const v4i (&wv)[kLoads<W>], int32_
             w[2 * c + 1] = (uint32_t)wv[0][c] >> 16;
         }
     }
+}
+
+// Starts the loads of a chunk's staged source values. Words outside the share read
+// some staged or unwritten place of the segment's LDS; their values are not used.
+template <typename VT, typename W>
+__device__ __forceinline__ void load_values(const v4i (&wv)[kLoads<W>], typename Fetch<VT>::Raw (&raw)[kEPT]) {
+    uint32_t w[kEPT];
+    unpack_words<W>(wv, w);
+#pragma unroll
+    for (int i = 0; i < kEPT; ++i) raw[i] = staged<VT>(w[i] & EdgeWord<W>::kIndex);
+}
+
+// Processes one chunk of kChunk edges (this lane: kEPT consecutive edges).
+// rel0 is the chunk's first edge relative to the wave's share [0, len) (it is
+// negative for a first chunk that starts before the share); FULL chunks lie
+// entirely inside the share and skip the per-edge bounds tests. Rows finished
+// in the chunk are exactly chunk_nf consecutive rows starting at row0 + nflags
+// - 1; they are collected in `stage` and written with coalesced stores.
+//
+// LONG (tiles of many chunks per wave, STAGED): raw holds the edges' source values,
+// already on their way from LDS, and the stores test nothing; otherwise the values
+// are loaded here.
+template <class Op, typename VT, bool STAGED, typename W, bool LONG, bool FULL>
+__device__ __forceinline__ void process_chunk(const v4i (&wv)[kLoads<W>],
+                                              const typename Fetch<VT>::Raw (&raw)[kEPT], int32_t rel0, int32_t len,
+                                              const VT *gvals, typename Op::T *stage, const RowOut &out,
+                                              SpanState<typename Op::T> &S) {
+    using T = typename Op::T;
+    using F = Fetch<VT>;
+    const int lane = __lane_id();
+    const int32_t rel = rel0 + lane * kEPT;
+    uint32_t w[kEPT];
+    unpack_words<W>(wv, w);
     bool fl[kEPT];  // row starts
     T v[kEPT];
 #pragma unroll
     for (int i = 0; i < kEPT; ++i) {
-        if constexpr (FULL) {
-            fl[i] = (w[i] & EdgeWord<W>::kFlag) != 0u;
-            v[i] = F::get(seg_vals, gvals, (int32_t)(w[i] & EdgeWord<W>::kIndex));
-        } else {
-            const bool valid = (uint32_t)(rel + i) < (uint32_t)len;
-            fl[i] = valid && (w[i] & EdgeWord<W>::kFlag) != 0u;
-            // words outside the share may belong to another segment: read index 0 instead
-            const T x = F::get(seg_vals, gvals, valid ? (int32_t)(w[i] & EdgeWord<W>::kIndex) : 0);
-            v[i] = valid ? x : Op::identity();
-        }
+        const bool valid = FULL || (uint32_t)(rel + i) < (uint32_t)len;
+        fl[i] = valid && (w[i] & EdgeWord<W>::kFlag) != 0u;
+        // words outside the share may belong to another segment: global index 0 instead
+        const uint32_t at = valid ? w[i] & EdgeWord<W>::kIndex : 0u;
+        const typename F::Raw x = LONG ? raw[i] : STAGED ? staged<VT>(at) : (typename F::Raw)gvals[at];
+        v[i] = valid ? F::value(x) : Op::identity();
     }
     int32_t nf = 0;
 #pragma unroll
@@ -188,7 +195,7 @@ __device__ __forceinline__ void process_chunk(const v4i (&wv)[kLoads<W>], int32_
     for (int i = 0; i < kEPT; ++i) {
         if (fl[i]) *slot = run;
         slot += fl[i] ? 1 : 0;
-        run = fl[i] ? v[i] : Op::apply(run, v[i]);
+        run = i == 0 || fl[i] ? v[i] : Op::apply(run, v[i]);
     }
     // segmented inclusive scan of (has row start, tail value) over the wave
     T sv = run;
@@ -203,14 +210,25 @@ __device__ __forceinline__ void process_chunk(const v4i (&wv)[kLoads<W>], int32_
     // had not seen a row start yet: that one is completed across waves later
     const bool head_here = S.nflags == 0 && chunk_nf > 0;
     const int32_t rbase = S.nflags - 1;  // staged index 0 <-> row row0 + rbase
+    // LONG: a descriptor that ends at the chunk's last row (or the buffer's) drops
+    // what lies past it, in place of tests of every store; it takes a dozen scalar
+    // instructions to make, which the short spans do not get back
+    const int32_t nrows = LONG ? min(chunk_nf, out.rows - rbase) : out.rows;
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(static_cast<T *>(out.base) + (LONG ? rbase : 0)), 0, max(nrows, 0) * (int32_t)sizeof(T), kBufFlags);
 #pragma unroll
     for (int r = 0; r < kEPT; ++r) {
         if (r * kWave >= chunk_nf) break;  // uniform: chunk_nf is wave-wide
         const int32_t i = r * kWave + lane;
         const T val = stage[i];
-        const bool ok = i < chunk_nf && !(head_here && i == 0);
-        const uint32_t off = ok ? (uint32_t)(rbase + i) * (uint32_t)sizeof(T) : kOutOfRange;
-        __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const int32_t *>(&val), out, off, 0, 0);
+        uint32_t off = (uint32_t)lane * (uint32_t)sizeof(T);
+        if constexpr (LONG) {
+            if (r == 0) off = head_here && lane == 0 ? kOutOfRange : off;
+            off += (uint32_t)(r * kWave * sizeof(T));
+        } else {
+            off = i < chunk_nf && !(head_here && i == 0) ? (uint32_t)(rbase + i) * (uint32_t)sizeof(T) : kOutOfRange;
+        }
+        __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const int32_t *>(&val), rows, off, 0, 0);
     }
     if (head_here) S.head = stage[0];
     __builtin_amdgcn_wave_barrier();
@@ -235,7 +253,9 @@ __device__ __forceinline__ void load_chunk(v4i (&r)[kLoads<W>], __amdgpu_buffer_
 constexpr int kStagesDeep = 8;
 constexpr int kStagesDefault = 4;
 constexpr int32_t kDeepTileEdges = 131072;  // tiles at least this long take kStagesDeep
-constexpr int64_t kSplitEdges = 49152;      // shorter tiles stay whole (split_plan)
+// Tiles at least this long read a chunk's source values ahead, store through a
+// descriptor per chunk (both below), and may be cut into parts (split_plan).
+constexpr int64_t kLongTileEdges = 49152;
 constexpr int kXcds = 8, kXcdCus = 32;
 
 // Tile t; with SPLIT, part `part` of nparts (1, 2, 4, 8 or 16) of its spans.
@@ -243,7 +263,7 @@ constexpr int kXcds = 8, kXcdCus = 32;
 // and the others read on only as far as the first row start of the spans that
 // follow, whose heads complete the part's last row. The heads are summed as
 // in the whole tile, so the result does not depend on the split.
-template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool SPLIT>
+template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool LONG, bool SPLIT, bool MULTI = false>
 __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int64_t Q,
                                             const int32_t *__restrict__ tile_edge,
                                             const int32_t *__restrict__ tile_seg,
@@ -253,13 +273,18 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
                                             const uint32_t *__restrict__ seg_active) {
     using T = typename Op::T;
     VT *seg_vals = reinterpret_cast<VT *>(smem + kStageBytes);
-    const int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
+    // the compiler loads per lane where it cannot see that a value is uniform; where
+    // it can, these would keep it from loading through the scalar cache (3% of short
+    // tiles)
+    const auto listed = [](auto x) { return MULTI ? uniform(x) : x; };
+    const auto placed = [](auto x) { return MULTI || SPLIT ? uniform(x) : x; };
+    const int64_t e0 = listed(tile_edge[t]), e1 = listed(tile_edge[t + 1]);
     if (e0 >= e1) return;  // empty tile (uniform over the workgroup)
-    if (SPLIT && nparts > 1 && e1 - e0 < kSplitEdges) {  // uniform: not worth it
+    if (SPLIT && nparts > 1 && e1 - e0 < kLongTileEdges) {  // uniform: not worth it
         if (part > 0) return;
         nparts = 1;
     }
-    const int32_t s = tile_seg[t];
+    const int32_t s = listed(tile_seg[t]);
     // an inactive segment (no source in the frontier) contributes nothing: its
     // rows are skipped here and by the merge
     if (seg_active && !((seg_active[s >> 5] >> (s & 31)) & 1u)) return;
@@ -282,7 +307,8 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
     if (w0 > e1 || (SPLIT && sp >= kGatherWaves)) w0 = e1;
     int64_t w1 = w0 + sl;
     if (w1 > e1) w1 = e1;
-    const int32_t row0 = span_row[(int64_t)t * kGatherWaves + (SPLIT ? min(sp, kGatherWaves - 1) : w)];
+    const int32_t row0 = placed(
+        span_row[(int64_t)t * kGatherWaves + (SPLIT ? min(sp, kGatherWaves - 1) : w)]);
 
     // Buffer descriptors: loads past the share read zero, and stores to rows
     // outside [row0, Q) are dropped, so the loop needs no bounds branches.
@@ -295,31 +321,49 @@ __device__ __forceinline__ void gather_tile(const W *__restrict__ edge_src, int6
     int64_t rows_left = Q - row0;
     if (rows_left > (1 << 28)) rows_left = 1 << 28;
     if (rows_left < 0 || head_only) rows_left = 0;
-    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(partial + row0), 0, (int32_t)(rows_left * (int64_t)sizeof(T)), kBufFlags);
+    const RowOut out{placed(partial + row0), placed((int32_t)rows_left)};
 
     SpanState<T> S{Op::identity(), Op::identity(), 0};
     T *stage = reinterpret_cast<T *>(smem) + (size_t)w * kStageRows;
     const int64_t len = w1 - ebase;
     const int32_t share = (int32_t)(w1 - w0);
+    [[maybe_unused]] const int32_t most_flags = head_only ? 0 : 0x7fffffff;  // a head ends with the first one
     const uint32_t lane_off = (uint32_t)(lane * kEPT * kWB);
     constexpr int kSt = DEPTH;
     v4i R[kSt][kLoads<W>];
 #pragma unroll
-    for (int c = 0; c < kSt - 1; ++c) load_chunk<W>(R[c], ein, (uint32_t)(c * kChunk * kWB) + lane_off);
+    for (int c = 0; c < kSt - 1; ++c) {
+        load_chunk<W>(R[c], ein, (uint32_t)(c * kChunk * kWB) + lane_off);
+        if constexpr (LONG) __builtin_amdgcn_sched_barrier(0);  // in this order, which the loop's waits rely on
+    }
+    // A chunk is a chain of LDS and cross-lane steps, and only four waves share a
+    // SIMD (the staged segment fills the LDS): with LONG the source values of the
+    // next chunk are read before a chunk's chain begins. Per 512 edges that leaves
+    // 113 vector instructions of 128, 61% of the issue slots beside 50% of the LDS
+    // cycles (half of those are bank conflicts of the random reads). R-MAT 22 / ef
+    // 24: 97 -> 93 us; 128 M undirected edges: 130 -> 125 us; R-MAT 25 / ef 32,
+    // bound by memory: 986 -> 966 us. Tiles of 16,384 edges and less lose up to 3%.
+    static_assert(!LONG || STAGED);
+    static_assert(kSt % 2 == 0, "the two sets of values alternate");
+    typename Fetch<VT>::Raw raw[2][kEPT];
+    if constexpr (LONG) load_values<VT, W>(R[0], raw[0]);
     for (int64_t cc = 0; cc < len; cc += kSt * kChunk) {
-        if (SPLIT && head_only && S.nflags > 0) break;
+        if (SPLIT && S.nflags > most_flags) break;
 #pragma unroll
         for (int c = 0; c < kSt; ++c) {
             if (cc + c * kChunk >= len) break;  // uniform: len and cc are wave-wide
-            if (SPLIT && head_only && S.nflags > 0) break;  // uniform
+            if (SPLIT && S.nflags > most_flags) break;  // uniform
+            if constexpr (LONG) {
+                load_values<VT, W>(R[(c + 1) % kSt], raw[(c + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             load_chunk<W>(R[(c + kSt - 1) % kSt], ein,
                           (uint32_t)((cc + (c + kSt - 1) * kChunk) * kWB) + lane_off);
             const int32_t rel0 = (int32_t)(ebase + cc + c * kChunk - w0);
             if (rel0 >= 0 && rel0 + kChunk <= share)
-                process_chunk<Op, VT, STAGED, W, true>(R[c], rel0, share, seg_vals, gvals, stage, out, S);
+                process_chunk<Op, VT, STAGED, W, LONG, true>(R[c], raw[c & 1], rel0, share, gvals, stage, out, S);
             else
-                process_chunk<Op, VT, STAGED, W, false>(R[c], rel0, share, seg_vals, gvals, stage, out, S);
+                process_chunk<Op, VT, STAGED, W, LONG, false>(R[c], raw[c & 1], rel0, share, gvals, stage, out, S);
         }
     }
 
@@ -355,7 +399,7 @@ struct SplitPlan {
     int32_t whole, parts;
 };
 
-template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool SPLIT>
+template <class Op, typename VT, bool STAGED, typename W, int DEPTH, bool LONG, bool SPLIT>
 __global__ __launch_bounds__(kGatherThreads) void k_gather(
     const W *__restrict__ edge_src, int64_t E, int64_t Q, const int32_t *__restrict__ tile_edge,
     const int32_t *__restrict__ tile_seg, const int32_t *__restrict__ span_row, const VT *__restrict__ values,
@@ -363,8 +407,6 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(
     const uint32_t *__restrict__ seg_active, unsigned long long *__restrict__ clear, SplitPlan plan) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     (void)E;
-    // the counter of the merge that follows on the stream (null: none)
-    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0ull;
     int t = 0, part = 0, parts = 1;
     if constexpr (SPLIT) {
         const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
@@ -380,8 +422,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather(
     } else {
         t = xcd_remap(blockIdx.x, ntiles);
     }
-    gather_tile<Op, VT, STAGED, W, DEPTH, SPLIT>(edge_src, Q, tile_edge, tile_seg, span_row, values, V, N, t, part,
+    gather_tile<Op, VT, STAGED, W, DEPTH, LONG, SPLIT>(edge_src, Q, tile_edge, tile_seg, span_row, values, V, N, t, part,
                                                  parts, partial, smem, seg_active);
+    // the counter of the merge that follows on the stream (null: none); a store
+    // before the tile's loads would keep them out of the scalar cache
+    if (blockIdx.x == 0 && threadIdx.x == 0 && clear) *clear = 0ull;
 }
 
 // Over many graphs: workgroups stride over a global tile list.
@@ -391,17 +436,18 @@ __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc
                                                                  unsigned long long *__restrict__ tickets,
                                                                  int32_t ngraphs) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    for (int64_t gt = blockIdx.x; gt < total_tiles; gt += gridDim.x) {
+        __syncthreads();  // LDS reuse across tiles
+        const int gi = uniform(tile_graph[gt]);
+        const MultiDesc &d = desc[gi];
+        gather_tile<OpSum, float, true, uint16_t, kStagesDefault, true, false, true>(
+            uniform(static_cast<const uint16_t *>(d.edge_src)), d.Q, uniform(d.tile_edge), uniform(d.tile_seg),
+            uniform(d.tile_span_row), uniform(d.contrib[parity]), uniform(d.V), uniform(d.N),
+            uniform((int32_t)(gt - d.tile_base)), 0, 1, uniform(d.partial), smem, nullptr);
+    }
     // the counters of the merge that follows on the stream
     if (blockIdx.x == 0)
         for (int32_t i = threadIdx.x; i < ngraphs; i += kGatherThreads) tickets[i] = 0ull;
-    for (int64_t gt = blockIdx.x; gt < total_tiles; gt += gridDim.x) {
-        __syncthreads();  // LDS reuse across tiles
-        const int gi = tile_graph[gt];
-        const MultiDesc &d = desc[gi];
-        gather_tile<OpSum, float, true, uint16_t, kStagesDefault, false>(
-            static_cast<const uint16_t *>(d.edge_src), d.Q, d.tile_edge, d.tile_seg, d.tile_span_row, d.contrib[parity],
-            d.V, d.N, (int)(gt - d.tile_base), 0, 1, d.partial, smem, nullptr);
-    }
 }
 
 // Tiles are long (they amortize a segment's staging), so a launch is a few rounds
@@ -434,22 +480,24 @@ template <class Op, typename VT, bool STAGED, typename W>
 static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values, typename Op::T *partial,
                                     const uint32_t *seg_active, unsigned long long *clear, hipStream_t st) {
     if (seg->ntiles == 0) return CAGRA_OK;
-    auto kern = k_gather<Op, VT, STAGED, W, kStagesDefault, false>;
+    auto kern = k_gather<Op, VT, STAGED, W, kStagesDefault, false, false>;
     const size_t lds = kStageBytes + (STAGED ? (size_t)seg->N * sizeof(VT) : 0);
     SplitPlan plan = {seg->ntiles, 1};
     int grid = seg->ntiles;
     if constexpr (STAGED) {
-        const bool deep = sizeof(W) == 2 && seg->tile_edges >= kDeepTileEdges;
-        if (seg->tile_edges >= kSplitEdges) {
+        if (seg->tile_edges >= kLongTileEdges) {
+            const bool deep = sizeof(W) == 2 && seg->tile_edges >= kDeepTileEdges;
             const int64_t n = ceil_div(seg->ntiles, kXcds);
             plan = split_plan(n, kXcdCus * (!deep && 2 * lds <= CAGRA_LDS_BYTES ? 2 : 1));
-            if (plan.parts > 1) grid = (int)(kXcds * (plan.whole + (n - plan.whole) * plan.parts));
+            const bool split = plan.parts > 1;
+            if (split) grid = (int)(kXcds * (plan.whole + (n - plan.whole) * plan.parts));
+            kern = split ? k_gather<Op, VT, STAGED, W, kStagesDefault, true, true>
+                         : k_gather<Op, VT, STAGED, W, kStagesDefault, true, false>;
+            if constexpr (sizeof(W) == 2)
+                if (deep)
+                    kern = split ? k_gather<Op, VT, STAGED, W, kStagesDeep, true, true>
+                                 : k_gather<Op, VT, STAGED, W, kStagesDeep, true, false>;
         }
-        if (plan.parts > 1) kern = k_gather<Op, VT, STAGED, W, kStagesDefault, true>;
-        if constexpr (sizeof(W) == 2)
-            if (deep)
-                kern = plan.parts > 1 ? k_gather<Op, VT, STAGED, W, kStagesDeep, true>
-                                      : k_gather<Op, VT, STAGED, W, kStagesDeep, false>;
     }
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
     kern<<<grid, kGatherThreads, lds, st>>>(static_cast<const W *>(seg->edge_src), seg->E, seg->Q, seg->tile_edge,

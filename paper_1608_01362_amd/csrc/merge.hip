@@ -20,6 +20,7 @@
 #include <math.h>
 
 #include "blockwalk.h"
+#include "wave.h"
 #include "common.h"
 
 namespace cagra {
@@ -759,15 +760,16 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     for (int64_t gb = blockIdx.x; gb < total_blocks; gb += gridDim.x) {
         __syncthreads();  // LDS reuse across blocks
-        const int gi = block_graph[gb];
+        const int gi = uniform(block_graph[gb]);
         const MultiDesc &d = desc[gi];
         // kept within 64 VGPRs (two workgroups per CU): at 66 one fitted, and the
         // merge of 48 graphs took 22.5 us and its sums 4.6 us more; now 21.4 us
         // with the sums
-        merge_pr_block<false, 4, true>(d.row_dst_lo, d.block_ptr, d.partial, d.V, d.k, d.B,
-                                              (int)(gb - d.block_base), 0, 1, d.rank[parity], d.out_degree,
-                                              d.scalars[parity], damping, -1, d.rank[1 - parity],
-                                              d.contrib[1 - parity], blk + gb * 4, nullptr, nullptr, smem);
+        merge_pr_block<false, 4, true>(uniform(d.row_dst_lo), uniform(d.block_ptr), uniform(d.partial), uniform(d.V),
+                                       uniform(d.k), uniform(d.B), uniform((int32_t)(gb - d.block_base)), 0, 1,
+                                       uniform(d.rank[parity]), uniform(d.out_degree), uniform(d.scalars[parity]),
+                                       damping, -1, uniform(d.rank[1 - parity]), uniform(d.contrib[1 - parity]),
+                                       blk + gb * 4, nullptr, nullptr, smem);
         if (!tickets) continue;
         // the last block of a graph adds that graph's sums (its descriptor is
         // read again rather than held in registers over the merge)

@@ -37,6 +37,17 @@ __device__ __forceinline__ int32_t wave_incl_sum(int32_t x) {
     return x;
 }
 
+// A value that is the same in the whole wave, in scalar registers (the compiler
+// loads it per lane where the kernel also writes memory).
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename P>
+__device__ __forceinline__ P *uniform(P *p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(a >> 32));
+    return reinterpret_cast<P *>(((uint64_t)hi << 32) | lo);
+}
+
 constexpr int32_t kBufFlags = 0x00020000;   // raw buffer descriptor word 3 (gfx9)
 constexpr int kNonTemporal = 2;             // cache policy: streaming
 constexpr uint32_t kOutOfRange = 0x80000000u;
