@@ -240,9 +240,13 @@ __global__ __launch_bounds__(kFwdThreads) void k_mlp_forward(const float *__rest
 // orientation (h1, dz2, dz1) goes through the wave's own LDS tile, one after
 // the other. The weights sit in LDS as FP32, once in each orientation.
 //
+// The forward sums keep the order of the units (a matrix instruction adds its two
+// products one after the other, and the units go in as 2 j, 2 j + 1), so y and the
+// loss have the bits of one FP32 chain per sum.
+//
 // Bound by the matrix instructions (10 us for 65,536 rows at the FP32 rate) and
 // by 128 GELUs with their derivatives per row. 65,536 rows: 318 us with scalar
-// FP32 and one thread per row, 34 us now (30 and 4 of the reduction).
+// FP32 and one thread per row, 35 us now (30 and 5 of the reduction).
 constexpr int kBwdWaves = 8;
 constexpr int kBwdThreads = kBwdWaves * kWave;
 constexpr int kBwdRows = 32;   // rows of a wave's tile
@@ -258,31 +262,26 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The value of the lane whose number differs in bit M < 32 (ds_swizzle, xor mode).
-template <int M>
-__device__ __forceinline__ float swap_lanes(float x) {
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), (M << 10) | 0x1f));
-}
-
-// Each lane keeps K of the 2 K sums in a (the upper K when its bit M is set),
-// its own plus those of the lane across bit M.
-template <int M, int K>
-__device__ __forceinline__ void halve_rows(float (&a)[16], int lane) {
-    const bool up = lane & M;
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const float send = up ? a[q] : a[q + K], keep = up ? a[q + K] : a[q];
-        a[q] = keep + swap_lanes<M>(send);
-    }
+// Units 2 j, 2 j + 1 of the two halves of the wave, in registers v[0..3] of a group
+// of eight (half h holds 2 j + h), to the products' order (half h holds 4 h + j).
+__device__ __forceinline__ void to_product_order(float (&v)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+    v[0] = __uint_as_float(a[0]);
+    v[1] = __uint_as_float(a[1]);
+    v[2] = __uint_as_float(b[0]);
+    v[3] = __uint_as_float(b[1]);
 }
 
 struct BwdLds {
-    float w2[kH * kPitch];                     // W2[n][i]
+    float w2[kH * kPitch];                     // W2[n][i], i in each group of 8 at 4 (i & 1) + (i >> 1)
     float w2t[kH * kPitch];                    // W2[n][i] at [i][n]
     float w1[kH * 4];                          // W1[i][0..2], b1[i]
     float tile[kBwdWaves][kBwdRows * kPitch];  // [row][unit]: h1, then dz2, then dz1
+    float half[kBwdWaves][kBwdRows / 2 * kPitch];  // [row][unit]: h2, half of the rows at a time
+    float w3[kH];
     float x[kBwdWaves][kBwdRows * 4];          // [row]: standardized features, 1
-    float dy[kBwdWaves][kBwdRows];             // [row]: y, then the loss gradient
+    float dy[kBwdWaves][kBwdRows];             // [row]: the loss gradient
 };
 // after the row loop the same memory holds the waves' sums (see wave_sums)
 constexpr int kBwdRegs = 64 + 2 + 2 + 8 + 1;   // W2, w3, b2, W1 and b1, b3
@@ -302,12 +301,13 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
     const int c = lane & 31, h = lane >> 5;  // row or unit within a 32-wide tile, half
     for (int i = tid; i < kH * kH; i += kBwdThreads) {
         const float v = bf16_to_f32(wb[kOffW2 + i]);
-        L.w2[(i >> 6) * kPitch + (i & 63)] = v;
+        L.w2[(i >> 6) * kPitch + (i & 56) + 4 * (i & 1) + ((i >> 1) & 3)] = v;
         L.w2t[(i & 63) * kPitch + (i >> 6)] = v;
     }
     if (tid < kH) {
         for (int q = 0; q < 3; ++q) L.w1[tid * 4 + q] = bf16_to_f32(wb[kOffW1 + 3 * tid + q]);
         L.w1[tid * 4 + 3] = bf16_to_f32(wb[kOffB1 + tid]);
+        L.w3[tid] = bf16_to_f32(wb[kOffW3 + tid]);
     }
     float w3[2], b2[2];
 #pragma unroll
@@ -328,8 +328,10 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
     // offsets from these (a separate address each would fill the registers)
     float *by_row = &L.tile[w][c * kPitch + 4 * h];        // lane = row: units 32 t + 8 q + 4 h ...
     float *by_unit = &L.tile[w][4 * h * kPitch + c];       // lane = unit: rows 8 q + 4 h ...
-    const float *w1 = &L.w1[16 * h], *wn = &L.w2[c * kPitch + 4 * h], *wi = &L.w2t[c * kPitch + 4 * h];
+    const float *w1 = &L.w1[4 * h], *wn = &L.w2[c * kPitch + 4 * h], *wi = &L.w2t[c * kPitch + 4 * h];
     const float *x_half = &xs[16 * h], *dy_half = &dys[4 * h];
+    float *half_unit = &L.half[w][4 * h * kPitch + c];       // lane = unit: rows 8 q + 4 h ...
+    const float *half_row = &L.half[w][(lane & 15) * kPitch];  // lane = row
 
     // tiles go to workgroups first, then to their waves, so that few rows still use many CUs
     const int64_t tiles = (n + kBwdRows - 1) / kBwdRows;
@@ -364,15 +366,12 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
             for (int q = 0; q < 4; ++q) {
                 constexpr int kHalf = 32 * kPitch;
                 const int u = 32 * t + 8 * q;
-                f32x4 hv;
+                float hv[4], dg[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(&w1[(u + j) * 4]);
-                    float g;
-                    gelu_both(fmaf(wv[2], x2, fmaf(wv[1], x1, fmaf(wv[0], x0, wv[3]))), g, dg1[16 * t + 4 * q + j]);
-                    hv[j] = g;
+                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(&w1[(u + 2 * j) * 4]);
+                    gelu_both(fmaf(wv[2], x2, fmaf(wv[1], x1, fmaf(wv[0], x0, wv[3]))), hv[j], dg[j]);
                 }
-                *reinterpret_cast<f32x4 *>(&by_row[u]) = hv;
                 const f32x4 wa = *reinterpret_cast<const f32x4 *>(&wn[u]);
                 const f32x4 wc = *reinterpret_cast<const f32x4 *>(&wn[kHalf + u]);
 #pragma unroll
@@ -380,11 +379,17 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
                     z2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(hv[j], wa[j], z2[0], 0, 0, 0);
                     z2[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(hv[j], wc[j], z2[1], 0, 0, 0);
                 }
+                to_product_order(hv);
+                to_product_order(dg);
+                *reinterpret_cast<f32x4 *>(&by_row[u]) = f32x4{hv[0], hv[1], hv[2], hv[3]};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dg1[16 * t + 4 * q + j] = dg[j];
                 __builtin_amdgcn_sched_barrier(0);
             }
-        // output layer: a[q] = this lane's two units of row (q, h); h2 and its derivative replace z2
+        // output layer: h2 and its derivative replace z2; the sum over a row's units
+        // is taken with lane = row, 16 rows at a time
         f32x16 h2[2];
-        float a[16];
+        float out[2];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             float g0, g1, d0, d1;
@@ -394,27 +399,30 @@ __global__ __launch_bounds__(kBwdThreads) void k_mlp_backward(const float *__res
             h2[1][q] = g1;
             z2[0][q] = d0;
             z2[1][q] = d1;
-            a[q] = fmaf(w3[1], g1, w3[0] * g0);
+            float *to = &half_unit[(8 * ((q & 7) >> 2) + (q & 3)) * kPitch];
+            to[0] = g0;
+            to[32] = g1;
+            if ((q & 7) == 7) {
+                wave_lds_order();
+                float o = b3;
+#pragma unroll 4
+                for (int u = 0; u < kH; u += 4) {
+                    const f32x4 hv = *reinterpret_cast<const f32x4 *>(&half_row[u]);
+                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(&L.w3[u]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o = fmaf(wv[j], hv[j], o);
+                }
+                out[q >> 3] = o;
+                wave_lds_order();
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // sum over the 32 lanes: each exchange halves the rows a lane carries
-        halve_rows<16, 8>(a, lane);
-        halve_rows<8, 4>(a, lane);
-        halve_rows<4, 2>(a, lane);
-        halve_rows<2, 1>(a, lane);
-        a[0] += swap_lanes<1>(a[0]);
-        {
-            const int q = c >> 1;  // the row register this lane ended with: bits 4..1 of the lane
-            if ((c & 1) == 0) dys[8 * (q >> 2) + 4 * h + (q & 3)] = a[0];
-        }
-        wave_lds_order();
-        const float res = live ? dys[c] + b3 - tg : 0.0f;
+        const float res = live ? (c < 16 ? out[0] : out[1]) - tg : 0.0f;
         const float dy = res * inv_n2;
         if (h == 0) {
             loss += (double)res * (double)res;
             gb3 += dy;
         }
-        wave_lds_order();
         if (h == 0) dys[c] = dy;
         wave_lds_order();
         // dz2 = dy * w3 * gelu'(z2) (lane = output unit), and the weight gradient
