@@ -14,7 +14,8 @@ cagra_status launch_gather_active(const cagra_segments *seg, int32_t op, int32_t
 cagra_status launch_merge_active(const cagra_segments *seg, int32_t op, const void *partial, void *out,
                                  const uint32_t *seg_active, hipStream_t st);
 
-constexpr int kBcThreads = 256;
+constexpr int kBcThreads = 256;       // the start and the backward update
+constexpr int kBcSpanThreads = 1024;  // the kernels over spans
 
 __global__ void k_bc_start(int32_t V, int32_t source, int32_t *__restrict__ depth, float *__restrict__ sigma,
                            float *__restrict__ delta) {
@@ -36,55 +37,88 @@ __global__ void k_zero_words(uint32_t *__restrict__ w, int32_t n) {
 // per non-zero word; the new-frontier count is reduced in the workgroup and
 // added once. (One global atomic per wave on a handful of words serialises:
 // half a million of them took 1.5-1.9 ms per level at scale 25.)
-// The span shrinks with the graph so that about kBcWorkgroups workgroups
-// cover it: with 16,384 vertices each, 2 M vertices gave 128 workgroups, half
-// the chip's CUs, each walking 64 dependent steps.
+// The span shrinks with the graph so that about kBcWorkgroups workgroups cover
+// it: with 16,384 vertices each, 2 M vertices gave 128 workgroups, half the
+// chip's CUs. More and smaller ones lose again: their atomics on the one count
+// and the few words go through memory one after the other, about 13 ns each
+// (2,048 workgroups of 1,024 vertices: 28-31 us where the frontier is dense,
+// 13-18 us now; a word that has the bits already is left alone).
 constexpr int kBcMaxSpan = 16384;                 // vertices per workgroup
-constexpr int kBcMinSpan = 1024;
-constexpr int kBcWorkgroups = 2048;
+constexpr int kBcMinSpan = 4096;
+constexpr int kBcWorkgroups = 512;
 constexpr int kBcMaskWords = kBcMaxSpan / 32 + 2; // segments of a span, in 32-bit words, for N >= 1
 
+// A thread takes kBcBatch vertices of the span per round and loads all they may
+// need before it looks at any (also sigma and delta of vertices outside the
+// frontier, which are bytes, not round trips).
+constexpr int kBcBatch = 4;
+static_assert(kBcMinSpan % (kBcBatch * kBcSpanThreads) == 0, "a span is whole rounds");
+
 struct SpanMask {
-    int64_t v0, v1;     // the workgroup's vertices [v0, v1)
+    int32_t v0, v1;     // the workgroup's vertices [v0, v1)
     int32_t w_lo, w_hi; // global mask words covering their segments
+    int32_t seg;        // their segment, or -1 if the span covers several
 };
 
 __device__ __forceinline__ SpanMask span_begin(int32_t V, int32_t N, int32_t span, uint32_t *lmask) {
     SpanMask m;
-    m.v0 = (int64_t)blockIdx.x * span;
-    m.v1 = m.v0 + span < V ? m.v0 + span : V;
-    m.w_lo = (int32_t)(m.v0 / N) >> 5;
-    m.w_hi = (int32_t)((m.v1 - 1) / N) >> 5;
-    for (int i = threadIdx.x; i <= m.w_hi - m.w_lo; i += kBcThreads) lmask[i] = 0u;
+    m.v0 = (int32_t)blockIdx.x * span;
+    m.v1 = V - m.v0 < span ? V : m.v0 + span;
+    const int32_t s0 = m.v0 / N, s1 = (m.v1 - 1) / N;
+    m.w_lo = s0 >> 5;
+    m.w_hi = s1 >> 5;
+    m.seg = s0 == s1 ? s0 : -1;
+    for (int i = threadIdx.x; i <= m.w_hi - m.w_lo; i += kBcSpanThreads) lmask[i] = 0u;
     __syncthreads();
     return m;
 }
 
-// Marks v's segment in the span's LDS mask: one LDS atomic per wave when the
-// wave's active vertices share a segment.
-__device__ __forceinline__ void mark_segment(uint32_t *lmask, int32_t w_lo, int64_t v, int32_t N, bool active) {
-    const uint64_t any = __ballot(active);
-    if (!any) return;
-    const int32_t s = active ? (int32_t)(v / N) : 0;
-    const int first = (int)__builtin_ctzll(any);
-    const int32_t s0 = __builtin_amdgcn_readlane(s, first);
-    if (__ballot(active && s != s0) == 0) {
-        if (__lane_id() == first) atomicOr(&lmask[(s0 >> 5) - w_lo], 1u << (s0 & 31));
-    } else if (active) {
-        atomicOr(&lmask[(s >> 5) - w_lo], 1u << (s & 31));
+// Marks the segments of the wave's active vertices (active[u]: vertex v + u *
+// kBcSpanThreads) in the span's LDS mask: one LDS atomic per wave where they share one.
+__device__ __forceinline__ void mark_segments(const SpanMask &m, uint32_t *lmask, uint32_t v, int32_t N,
+                                              const bool (&active)[kBcBatch]) {
+    if (m.seg >= 0) {  // uniform
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < kBcBatch; ++u) any |= active[u];
+        if (__builtin_amdgcn_ballot_w64(any) && __lane_id() == 0)
+            atomicOr(&lmask[(m.seg >> 5) - m.w_lo], 1u << (m.seg & 31));
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < kBcBatch; ++u) {
+        const uint64_t any = __builtin_amdgcn_ballot_w64(active[u]);
+        if (!any) continue;
+        const int32_t s = active[u] ? (int32_t)((v + u * kBcSpanThreads) / (uint32_t)N) : 0;
+        const int first = (int)__builtin_ctzll(any);
+        const int32_t s0 = __builtin_amdgcn_readlane(s, first);
+        if (__builtin_amdgcn_ballot_w64(active[u] && s != s0) == 0) {
+            if (__lane_id() == first) atomicOr(&lmask[(s0 >> 5) - m.w_lo], 1u << (s0 & 31));
+        } else if (active[u]) {
+            atomicOr(&lmask[(s >> 5) - m.w_lo], 1u << (s & 31));
+        }
     }
 }
 
 __device__ __forceinline__ void span_flush(const SpanMask &m, const uint32_t *lmask, uint32_t *mask) {
     __syncthreads();
-    for (int i = threadIdx.x; i <= m.w_hi - m.w_lo; i += kBcThreads) {
+    for (int i = threadIdx.x; i <= m.w_hi - m.w_lo; i += kBcSpanThreads) {
         const uint32_t bits = lmask[i];
-        if (bits) atomicOr(&mask[m.w_lo + i], bits);
+        // bits are only ever added: an old value read here costs an atomic, no more
+        if (bits && (mask[m.w_lo + i] & bits) != bits) atomicOr(&mask[m.w_lo + i], bits);
     }
 }
 
+// x[u] = a[v + u * kBcSpanThreads], clamped to the span. (Unsigned: the last span may
+// end at the largest int32.)
+template <typename T>
+__device__ __forceinline__ void load_batch(T (&x)[kBcBatch], const T *a, uint32_t v, uint32_t v1) {
+#pragma unroll
+    for (int u = 0; u < kBcBatch; ++u) x[u] = a[min(v + u * kBcSpanThreads, v1 - 1u)];
+}
+
 // vals[u] = sigma[u] for the frontier (depth d), else 0; frontier segments marked.
-__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
+__global__ __launch_bounds__(kBcSpanThreads) void k_bc_fwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
                                                               const int32_t *__restrict__ depth,
                                                               const float *__restrict__ sigma,
                                                               float *__restrict__ vals, uint32_t *__restrict__ mask,
@@ -92,30 +126,45 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_fwd_values(int32_t V, int32_t
     __shared__ uint32_t lmask[kBcMaskWords];
     const SpanMask m = span_begin(V, N, span, lmask);
     if (blockIdx.x == 0 && threadIdx.x == 0) *count = 0;  // next frontier size, counted by k_bc_fwd_update
-    for (int64_t v0 = m.v0; v0 < m.v1; v0 += kBcThreads) {
-        const int64_t v = v0 + threadIdx.x;
-        const bool in = v < m.v1 && depth[v] == d;
-        if (v < m.v1) vals[v] = in ? sigma[v] : 0.0f;
-        mark_segment(lmask, m.w_lo, v, N, in);
+    for (int32_t r = 0; r < m.v1 - m.v0; r += kBcBatch * kBcSpanThreads) {
+        const uint32_t v = (uint32_t)m.v0 + r + threadIdx.x;
+        int32_t dep[kBcBatch];
+        float sg[kBcBatch];
+        bool in[kBcBatch];
+        load_batch(dep, depth, v, m.v1);
+        load_batch(sg, sigma, v, m.v1);
+#pragma unroll
+        for (int u = 0; u < kBcBatch; ++u) {
+            const bool own = v + u * kBcSpanThreads < (uint32_t)m.v1;
+            in[u] = own && dep[u] == d;
+            if (own) vals[v + u * kBcSpanThreads] = in[u] ? sg[u] : 0.0f;
+        }
+        mark_segments(m, lmask, v, N, in);
     }
     span_flush(m, lmask, mask);
 }
 
 // Unvisited vertices reached at this level: depth d + 1, sigma = the sum.
-__global__ __launch_bounds__(kBcThreads) void k_bc_fwd_update(int32_t V, int32_t span, int32_t d, const float *__restrict__ sums,
+__global__ __launch_bounds__(kBcSpanThreads) void k_bc_fwd_update(int32_t V, int32_t span, int32_t d, const float *__restrict__ sums,
                                                               int32_t *__restrict__ depth,
                                                               float *__restrict__ sigma,
                                                               int32_t *__restrict__ count) {
-    __shared__ int32_t red[kBcThreads / kWave];
-    const int64_t v0 = (int64_t)blockIdx.x * span;
-    const int64_t v1 = v0 + span < V ? v0 + span : V;
+    __shared__ int32_t red[kBcSpanThreads / kWave];
+    const int32_t v0 = (int32_t)blockIdx.x * span;
+    const int32_t v1 = V - v0 < span ? V : v0 + span;
     int32_t reached = 0;
-    for (int64_t v = v0 + threadIdx.x; v < v1; v += kBcThreads) {
-        if (depth[v] < 0) {
-            const float x = sums[v];
-            if (x > 0.0f) {
-                depth[v] = d + 1;
-                sigma[v] = x;
+    for (int32_t r = 0; r < v1 - v0; r += kBcBatch * kBcSpanThreads) {
+        const uint32_t v = (uint32_t)v0 + r + threadIdx.x;
+        int32_t dep[kBcBatch];
+        float x[kBcBatch];
+        load_batch(dep, depth, v, v1);
+        load_batch(x, sums, v, v1);
+#pragma unroll
+        for (int u = 0; u < kBcBatch; ++u) {
+            const uint32_t w = v + u * kBcSpanThreads;
+            if (w < (uint32_t)v1 && dep[u] < 0 && x[u] > 0.0f) {
+                depth[w] = d + 1;
+                sigma[w] = x[u];
                 ++reached;
             }
         }
@@ -125,25 +174,35 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_fwd_update(int32_t V, int32_t
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t t = 0;
-        for (int i = 0; i < kBcThreads / kWave; ++i) t += red[i];
+        for (int i = 0; i < kBcSpanThreads / kWave; ++i) t += red[i];
         if (t) atomicAdd(count, t);
     }
 }
 
 // vals[w] = (1 + delta[w]) / sigma[w] for the vertices at depth d + 1, else 0;
 // their segments (in the reverse graph's segmentation) marked.
-__global__ __launch_bounds__(kBcThreads) void k_bc_bwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
+__global__ __launch_bounds__(kBcSpanThreads) void k_bc_bwd_values(int32_t V, int32_t N, int32_t span, int32_t d,
                                                               const int32_t *__restrict__ depth,
                                                               const float *__restrict__ sigma,
                                                               const float *__restrict__ delta,
                                                               float *__restrict__ vals, uint32_t *__restrict__ mask) {
     __shared__ uint32_t lmask[kBcMaskWords];
     const SpanMask m = span_begin(V, N, span, lmask);
-    for (int64_t v0 = m.v0; v0 < m.v1; v0 += kBcThreads) {
-        const int64_t v = v0 + threadIdx.x;
-        const bool in = v < m.v1 && depth[v] == d + 1;
-        if (v < m.v1) vals[v] = in ? (1.0f + delta[v]) / sigma[v] : 0.0f;
-        mark_segment(lmask, m.w_lo, v, N, in);
+    for (int32_t r = 0; r < m.v1 - m.v0; r += kBcBatch * kBcSpanThreads) {
+        const uint32_t v = (uint32_t)m.v0 + r + threadIdx.x;
+        int32_t dep[kBcBatch];
+        float sg[kBcBatch], dl[kBcBatch];
+        bool in[kBcBatch];
+        load_batch(dep, depth, v, m.v1);
+        load_batch(sg, sigma, v, m.v1);
+        load_batch(dl, delta, v, m.v1);
+#pragma unroll
+        for (int u = 0; u < kBcBatch; ++u) {
+            const bool own = v + u * kBcSpanThreads < (uint32_t)m.v1;
+            in[u] = own && dep[u] == d + 1;
+            if (own) vals[v + u * kBcSpanThreads] = in[u] ? (1.0f + dl[u]) / sg[u] : 0.0f;
+        }
+        mark_segments(m, lmask, v, N, in);
     }
     span_flush(m, lmask, mask);
 }
@@ -164,7 +223,7 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_bwd_update(int32_t V, int32_t
 
 // Vertices per workgroup: whole rounds of the workgroup's threads.
 static int32_t span_for(int32_t V) {
-    const int64_t s = ceil_div(ceil_div(V, kBcWorkgroups), kBcThreads) * kBcThreads;
+    const int64_t s = ceil_div(ceil_div(V, kBcWorkgroups), kBcSpanThreads) * kBcSpanThreads;
     return (int32_t)(s < kBcMinSpan ? kBcMinSpan : (s > kBcMaxSpan ? kBcMaxSpan : s));
 }
 static unsigned spans_for(int32_t V) { return (unsigned)ceil_div(V > 0 ? V : 1, span_for(V)); }
@@ -184,12 +243,12 @@ cagra_status launch_bc_forward(const cagra_segments *seg, int32_t d, int32_t *de
     const int32_t V = seg->V, words = (int32_t)bc_mask_words(seg);
     k_zero_words<<<(unsigned)ceil_div(words, 256), 256, 0, st>>>(mask, words);
     CAGRA_LAUNCH_CHECK();
-    k_bc_fwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg->N, span_for(V), d, depth, sigma, vals, mask, count);
+    k_bc_fwd_values<<<spans_for(V), kBcSpanThreads, 0, st>>>(V, seg->N, span_for(V), d, depth, sigma, vals, mask, count);
     CAGRA_LAUNCH_CHECK();
     cagra_status s;
     if ((s = launch_gather_active(seg, CAGRA_SUM_F32, CAGRA_F32, vals, partial, mask, st)) != CAGRA_OK) return s;
     if ((s = launch_merge_active(seg, CAGRA_SUM_F32, partial, sums, mask, st)) != CAGRA_OK) return s;
-    k_bc_fwd_update<<<spans_for(V), kBcThreads, 0, st>>>(V, span_for(V), d, sums, depth, sigma, count);
+    k_bc_fwd_update<<<spans_for(V), kBcSpanThreads, 0, st>>>(V, span_for(V), d, sums, depth, sigma, count);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
@@ -200,7 +259,7 @@ cagra_status launch_bc_backward(const cagra_segments *seg_t, int32_t d, int32_t 
     const int32_t V = seg_t->V, words = (int32_t)bc_mask_words(seg_t);
     k_zero_words<<<(unsigned)ceil_div(words, 256), 256, 0, st>>>(mask, words);
     CAGRA_LAUNCH_CHECK();
-    k_bc_bwd_values<<<spans_for(V), kBcThreads, 0, st>>>(V, seg_t->N, span_for(V), d, depth, sigma, delta, vals, mask);
+    k_bc_bwd_values<<<spans_for(V), kBcSpanThreads, 0, st>>>(V, seg_t->N, span_for(V), d, depth, sigma, delta, vals, mask);
     CAGRA_LAUNCH_CHECK();
     cagra_status s;
     if ((s = launch_gather_active(seg_t, CAGRA_SUM_F32, CAGRA_F32, vals, partial, mask, st)) != CAGRA_OK) return s;
