@@ -6,6 +6,7 @@
 #pragma once
 
 #include "common.h"
+#include "wave.h"
 
 namespace cagra {
 
@@ -103,24 +104,33 @@ __device__ __forceinline__ unsigned long long fix56_wave(float x) {
 }
 
 // Walk of a wave over its block's ranges in windows of 64 consecutive flattened
-// entries (ofs, pre: load_block_ranges). The wave steps over the range starts
-// inside a window together, each lane keeping the offset of the last range that
-// starts at or before its entry. The offsets and ends of the next 64 ranges are
-// held one per lane, so a range start costs two lane reads, a compare and a
-// select, and a window without one costs nothing. A search per lane, also for
-// ranges far shorter than a window, is slower: 25.3 against 22.9 us with ranges
-// of 431 entries in the mean, 62.0 against 56.8 with 20, 720 against 671 with
-// 0.8 (the merge of a 2 M-vertex R-MAT graph, edge factor 8).
+// entries (ofs, pre: load_block_ranges). The wave steps over the range starts inside
+// a window together, each lane keeping the offset of the last range that starts at
+// or before its entry. The offsets and ends of the next 64 ranges are held one per
+// lane, so a range start costs two lane reads, a compare and a select, and a window
+// without one costs nothing. DENSE: a window with more than kFew starts marks them
+// as bits of the window instead, and every entry takes the offset of the range that
+// its count of bits names.
+//
+// Merge of R-MAT graphs, DENSE = false (a search per lane before): 25 -> 19 us
+// with ranges of 1,052 entries in the mean, 47 -> 44 with 412. After clustering,
+// where most blocks' ranges are much shorter than the mean, with DENSE: 310 -> 229
+// us (mean 76; 255 without) and 464 -> 373 (19; 534 without) of 2^24 vertices,
+// 232 -> 156 (8.4; 265 without) of 2^22, and 633 -> 534 of 2^25 (716 without).
+template <bool DENSE>
 struct RangeWalk {
+    static constexpr int kFew = 6;  // 4 to 24: within 5%
     const int32_t *ofs, *pre;
     int32_t k, s0, j;    // ranges; range of lane 0; the current range's lane
     int32_t o, nxt;      // the current range's offset and end (uniform)
     int32_t vo, vn;      // those of range s0 + lane
+    int32_t vp;          // its start (DENSE)
 
     __device__ __forceinline__ void fetch() {
         const int32_t s = min(s0 + (int32_t)(threadIdx.x & 63), k - 1);
         vo = ofs[s];
         vn = pre[s + 1];
+        if constexpr (DENSE) vp = pre[s];
         asm volatile("" : "+v"(vo), "+v"(vn));  // here now: no wait for LDS in the loop's steps
     }
     __device__ __forceinline__ void take() {
@@ -133,8 +143,10 @@ struct RangeWalk {
         fetch();
         take();
     }
-    // Entry index of flattened entry f of a window that ends at wend < pre[k].
+    // Entry index of flattened entry f (lane 0: the window's first) of a window that
+    // ends at wend < pre[k].
     __device__ __forceinline__ int32_t index(int32_t wend, int32_t f) {
+        if constexpr (DENSE) return index_dense(wend, f);
         int32_t ov = o;
         while (nxt <= wend) {
             if (++j == kWave) {
@@ -148,7 +160,53 @@ struct RangeWalk {
         }
         return ov + f;
     }
+    __device__ __forceinline__ int32_t index_dense(int32_t wend, int32_t f) {
+        int32_t ov = o;
+        while (nxt <= wend) {
+            if (j == kWave - 1) {
+                s0 += kWave;
+                j = -1;
+                fetch();
+            }
+            // held ranges after the current one that start in the window (starts ascend;
+            // lanes past the last range repeat it)
+            int32_t n = (int32_t)__popcll(__builtin_amdgcn_ballot_w64(vp <= wend)) - 1 - j;
+            if (n <= kFew) {
+                for (; n > 0; --n) {
+                    ++j;
+                    const int32_t at = __builtin_amdgcn_readlane(vp, j);
+                    o = __builtin_amdgcn_readlane(vo, j);
+                    ov = f >= at ? o : ov;
+                }
+                nxt = __builtin_amdgcn_readlane(vn, j);
+            } else {
+                // the non-empty ones among them start at entries of their own
+                const int32_t lane = __lane_id();
+                const bool in = lane > j && vp <= wend && vn > vp;
+                const uint32_t at = (uint32_t)(vp - __builtin_amdgcn_readfirstlane(f)) & 63u;
+                // bit i: one starts at lane i's entry
+                const uint64_t starts = wave_or64(in ? 1ull << at : 0ull);
+                // lane r receives the offset of the r-th (the other lanes fill the lanes after)
+                const uint64_t from = __builtin_amdgcn_ballot_w64(in);
+                const int32_t rank = lanes_below(from);
+                const int32_t to = in ? rank : (int32_t)__popcll(from) + lane - rank;
+                const int32_t listed = __builtin_amdgcn_ds_permute(to << 2, vo);
+                const int32_t r = lanes_below(starts >> 1) + (int32_t)(starts & 1ull);  // starts up to this entry
+                const int32_t its = __builtin_amdgcn_ds_bpermute((r - 1) << 2, listed);
+                ov = r > 0 ? its : ov;
+                j += n;
+                take();
+            }
+        }
+        return ov + f;
+    }
 };
+// Rule for DENSE: mean entries per (subgraph, block) range below one and a half
+// windows. Merge with and without DENSE, us: mean 48: 389 and 396, 76 (clustered):
+// 229 and 255, 103: 70 and 67, 192: 305 and 303.
+static inline bool short_ranges(const cagra_segments *seg) {
+    return seg->Q < (int64_t)(kWave + kWave / 2) * seg->k * seg->nb;
+}
 
 constexpr int kUnroll = 8;
 

@@ -307,7 +307,7 @@ __device__ __forceinline__ unsigned long long fix24(float x) {
 // default cache policy: the cache line at each end of a (subgraph, block) range
 // is shared with the neighbouring block, which is merged at the same time on
 // the same XCD and finds the line in L2.
-template <typename PT, class Apply>
+template <typename PT, bool DENSE, class Apply>
 __device__ __forceinline__ void stream_block(const uint16_t *__restrict__ dlo, const PT *__restrict__ partial,
                                              const int32_t *ofs, const int32_t *pre, int32_t k, int32_t F0,
                                              int32_t F1, Apply apply) {
@@ -315,7 +315,7 @@ __device__ __forceinline__ void stream_block(const uint16_t *__restrict__ dlo, c
     const int32_t share = ((((F1 - F0) + 15) / 16) + 63) & ~63;
     const int32_t fa = min(F0 + w * share, F1), fb = min(fa + share, F1);
     if (fa >= fb) return;  // uniform over the wave
-    RangeWalk walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
+    RangeWalk<DENSE> walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
     int32_t f0 = fa;
     for (; f0 + kWave * kUnroll <= fb; f0 += kWave * kUnroll) {
         uint16_t d[kUnroll];
@@ -556,7 +556,7 @@ __device__ __forceinline__ void pr_epilogue_small(const unsigned long long *acc,
 // sums in its own slot of the workspace and the absolute sum of its buffer
 // values in *item_abs, and k_merge_pr_finish adds the S slots of the block
 // (exactly, so the split does not change any result) and applies the update.
-template <bool BF16OUT, int EPI = kEpiBatch, bool SMALL = false>
+template <bool BF16OUT, bool DENSE, int EPI = kEpiBatch, bool SMALL = false>
 __device__ __forceinline__ void merge_pr_block(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const float *__restrict__ partial, int32_t V, int32_t k, int32_t B, int b, int32_t j, int32_t S,
@@ -583,7 +583,7 @@ __device__ __forceinline__ void merge_pr_block(
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
     const int32_t F0 = (int32_t)((int64_t)P * j / S), F1 = (int32_t)((int64_t)P * (j + 1) / S);
     float am = 0.0f;  // this thread's share of the absolute buffer mass (range check)
-    stream_block<float>(row_dst_lo, partial, ofs, pre, k, F0, F1, [&](int32_t d, float x) {
+    stream_block<float, DENSE>(row_dst_lo, partial, ofs, pre, k, F0, F1, [&](int32_t d, float x) {
         atomicAdd(&acc[d], fix56_wave(x));
         am += fabsf(x);
     });
@@ -612,7 +612,7 @@ __device__ __forceinline__ int64_t split_slot(int32_t items_b, int32_t b, int32_
 
 constexpr int32_t kItemGroup = 4;  // work items per XCD group (1, 2, 4 and 16 time alike; contiguous is slower)
 
-template <bool BF16OUT>
+template <bool BF16OUT, bool DENSE>
 __global__ __launch_bounds__(kMergeThreads) void k_merge_pr(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const int32_t *__restrict__ block_items, const float *__restrict__ partial, int32_t V, int32_t k, int32_t B,
@@ -639,8 +639,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_pr(
     const int32_t b = ip.b, j = ip.j, S = ip.S;
     unsigned long long *slot = S > 1 ? slots + split_slot(block_items[b], b, j) * B : nullptr;
     double *ia = S > 1 ? item_abs + block_items[b] + j : nullptr;
-    merge_pr_block<BF16OUT>(row_dst_lo, block_ptr, partial, V, k, B, b, j, S, rank_in, outdeg, scalars_in,
-                                  damping, seed, rank_out, contrib_out, blk + (int64_t)b * 4, slot, ia, smem);
+    merge_pr_block<BF16OUT, DENSE>(row_dst_lo, block_ptr, partial, V, k, B, b, j, S, rank_in, outdeg, scalars_in,
+                                   damping, seed, rank_out, contrib_out, blk + (int64_t)b * 4, slot, ia, smem);
 }
 
 // The merge of a small graph: every block is one work item, and the last block
@@ -654,7 +654,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_pr_small(
     unsigned long long *__restrict__ ticket, double *scalars_out) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int b = xcd_remap(blockIdx.x, nb);
-    merge_pr_block<BF16OUT, kEpiBatch, true>(row_dst_lo, block_ptr, partial, V, k, B, b, 0, 1, rank_in, outdeg,
+    merge_pr_block<BF16OUT, false, kEpiBatch, true>(row_dst_lo, block_ptr, partial, V, k, B, b, 0, 1, rank_in, outdeg,
                                                    scalars_in, damping, seed, rank_out, contrib_out,
                                                    blk + (int64_t)b * 4, nullptr, nullptr, smem);
     if (last_of(ticket, nb, reinterpret_cast<int32_t *>(smem)))
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_sum_fixed24(
     const int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);
     for (int i = threadIdx.x; i < nv; i += kMergeThreads) acc[i] = 0ull;
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
-    stream_block<float>(row_dst_lo, partial, ofs, pre, k, 0, P,
+    stream_block<float, false>(row_dst_lo, partial, ofs, pre, k, 0, P,
                                [&](int32_t d, float x) { atomicAdd(&acc[d], fix24(x)); });
     __syncthreads();
     for (int i = threadIdx.x; i < nv; i += kMergeThreads)
@@ -765,11 +765,11 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8
         // kept within 64 VGPRs (two workgroups per CU): at 66 one fitted, and the
         // merge of 48 graphs took 22.5 us and its sums 4.6 us more; now 21.4 us
         // with the sums
-        merge_pr_block<false, 4, true>(uniform(d.row_dst_lo), uniform(d.block_ptr), uniform(d.partial), uniform(d.V),
-                                       uniform(d.k), uniform(d.B), uniform((int32_t)(gb - d.block_base)), 0, 1,
-                                       uniform(d.rank[parity]), uniform(d.out_degree), uniform(d.scalars[parity]),
-                                       damping, -1, uniform(d.rank[1 - parity]), uniform(d.contrib[1 - parity]),
-                                       blk + gb * 4, nullptr, nullptr, smem);
+        merge_pr_block<false, false, 4, true>(
+            uniform(d.row_dst_lo), uniform(d.block_ptr), uniform(d.partial), uniform(d.V), uniform(d.k), uniform(d.B),
+            uniform((int32_t)(gb - d.block_base)), 0, 1, uniform(d.rank[parity]), uniform(d.out_degree),
+            uniform(d.scalars[parity]), damping, -1, uniform(d.rank[1 - parity]), uniform(d.contrib[1 - parity]),
+            blk + gb * 4, nullptr, nullptr, smem);
         if (!tickets) continue;
         // the last block of a graph adds that graph's sums (its descriptor is
         // read again rather than held in registers over the merge)
@@ -845,6 +845,7 @@ cagra_status launch_multi_merge(const MultiDesc *desc, const int32_t *block_grap
     return CAGRA_OK;
 }
 
+template <bool DENSE>
 __global__ __launch_bounds__(kMergeThreads) void k_merge_lp(
     const uint16_t *__restrict__ row_dst_lo, const int32_t *__restrict__ block_ptr,
     const int32_t *__restrict__ partial, int32_t V, int32_t k, int32_t B, int32_t nb,
@@ -875,8 +876,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_lp(
         }
     }
     const int32_t P = load_block_ranges(block_ptr, b, k, ofs, pre, tmp);
-    stream_block<int32_t>(row_dst_lo, partial, ofs, pre, k, 0, P,
-                          [&](int32_t d, int32_t x) { atomicMin(&acc[d], x); });
+    stream_block<int32_t, DENSE>(row_dst_lo, partial, ofs, pre, k, 0, P,
+                                 [&](int32_t d, int32_t x) { atomicMin(&acc[d], x); });
     __syncthreads();
     int32_t changed = 0;
     for (int i0 = threadIdx.x; i0 < nv; i0 += kMergeThreads * kEpiBatch) {
@@ -1003,19 +1004,19 @@ cagra_status launch_pr_init(const cagra_graph *g, int32_t contrib_type, const fl
     return CAGRA_OK;
 }
 
-template <bool BF16OUT>
+template <bool BF16OUT, bool DENSE>
 static cagra_status launch_merge_pr_t(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t seed,
                                       const float *rank_in, const double *scalars_in, const float *partial,
                                       float *rank_out, void *contrib_out, double *scalars_out, void *ws,
                                       hipStream_t st) {
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr<BF16OUT>)) return a_;
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr<BF16OUT, DENSE>)) return a_;
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_pr_finish<BF16OUT>)) return a_;
     double *blk = reinterpret_cast<double *>(ws);
     double *item_abs = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + ws_blk_bytes(seg->V, seg->nb));
     unsigned long long *slots = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ws) +
                                                                        ws_blk_bytes(seg->V, seg->nb) +
                                                                        ws_item_bytes(seg));
-    k_merge_pr<BF16OUT><<<seg->max_items, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
+    k_merge_pr<BF16OUT, DENSE><<<seg->max_items, kMergeThreads, merge_fused_lds_bytes(seg->B, seg->k, 8), st>>>(
         seg->row_dst_lo, seg->block_ptr, seg->block_items, partial, seg->V, seg->k, seg->B, seg->nb, rank_in,
         g->out_degree, scalars_in, damping, seed, rank_out, contrib_out, blk, slots, item_abs,
         seg->max_items == seg->nb ? 1 : 0);
@@ -1042,7 +1043,9 @@ cagra_status launch_merge_pr(const cagra_graph *g, const cagra_segments *seg, do
                              int32_t contrib_type,
                              const float *rank_in, const double *scalars_in, const float *partial, float *rank_out,
                              void *contrib_out, double *scalars_out, void *ws, hipStream_t st) {
-    auto f = contrib_type == CAGRA_BF16 ? launch_merge_pr_t<true> : launch_merge_pr_t<false>;
+    const bool dense = short_ranges(seg);
+    auto f = contrib_type == CAGRA_BF16 ? (dense ? launch_merge_pr_t<true, true> : launch_merge_pr_t<true, false>)
+                                        : (dense ? launch_merge_pr_t<false, true> : launch_merge_pr_t<false, false>);
     return f(g, seg, damping, seed, rank_in, scalars_in, partial, rank_out, contrib_out, scalars_out, ws, st);
 }
 
@@ -1096,9 +1099,10 @@ cagra_status launch_merge_lp(const cagra_segments *seg, const int32_t *labels_in
                              int32_t *labels_out, int32_t *changed_out, void *ws, hipStream_t st) {
     int32_t *blk = reinterpret_cast<int32_t *>(ws);
     const size_t lds = merge_fused_lds_bytes(seg->B, seg->k, 4);
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_lp)) return a_;
-    k_merge_lp<<<seg->nb, kMergeThreads, lds, st>>>(seg->row_dst_lo, seg->block_ptr, partial, seg->V, seg->k, seg->B,
-                                                    seg->nb, labels_in, labels_out, blk);
+    auto merge = short_ranges(seg) ? k_merge_lp<true> : k_merge_lp<false>;
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)merge)) return a_;
+    merge<<<seg->nb, kMergeThreads, lds, st>>>(seg->row_dst_lo, seg->block_ptr, partial, seg->V, seg->k, seg->B,
+                                               seg->nb, labels_in, labels_out, blk);
     CAGRA_LAUNCH_CHECK();
     k_reduce_i32<<<1, 256, 0, st>>>(blk, seg->nb, changed_out);
     CAGRA_LAUNCH_CHECK();

@@ -153,7 +153,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_push_plan(PushPlan plan) {
 // items (the block's rows flattened over subgraphs, cut into S equal parts).
 // The last workgroup makes the scatter's plan meanwhile: on its own it was a
 // launch of one workgroup, 10 us of search latency per iteration.
-__global__ __launch_bounds__(kMergeThreads) void k_push_expand(const uint16_t *__restrict__ row_dst_lo,
+template <bool DENSE>
+__global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_push_expand(const uint16_t *__restrict__ row_dst_lo,
                                                                const int32_t *__restrict__ block_ptr,
                                                                const int32_t *__restrict__ block_items,
                                                                const uint32_t *__restrict__ x, int32_t V, int32_t k,
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_push_expand(const uint16_t *_
     const int32_t share = ((((F1 - F0) + 15) / 16) + 63) & ~63;
     const int32_t fa = min(F0 + w * share, F1), fb = min(fa + share, F1);
     if (fa >= fb) return;  // uniform over the wave
-    RangeWalk walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
+    RangeWalk<DENSE> walk(ofs, pre, k, __builtin_amdgcn_readfirstlane(run_of(pre, k, fa)));
     int32_t f0 = fa;
     for (; f0 + kWave * kExpandUnroll <= fb; f0 += kWave * kExpandUnroll) {
         uint32_t idx[kExpandUnroll];
@@ -632,8 +633,9 @@ static cagra_status push_edges(const cagra_segments *seg, const void *x, void *v
                            ws.pfirst,     ws.piece_tile,  ws.piece_seg};
     if (seg->Q > 0) {
         const size_t lds = push_expand_lds_bytes(seg->B, seg->k);
-        if (cagra_status a_ = ensure_dynamic_lds((const void *)k_push_expand)) return a_;
-        k_push_expand<<<seg->max_items + 1, kMergeThreads, lds, st>>>(
+        auto expand = short_ranges(seg) ? k_push_expand<true> : k_push_expand<false>;
+        if (cagra_status a_ = ensure_dynamic_lds((const void *)expand)) return a_;
+        expand<<<seg->max_items + 1, kMergeThreads, lds, st>>>(
             seg->row_dst_lo, seg->block_ptr, seg->block_items, static_cast<const uint32_t *>(x), seg->V, seg->k,
             seg->B, seg->nb, static_cast<uint32_t *>(vals), plan);
         CAGRA_LAUNCH_CHECK();

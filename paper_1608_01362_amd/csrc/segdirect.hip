@@ -344,21 +344,6 @@ struct EdgeTag<uint32_t> {
     __device__ __forceinline__ uint32_t word() const { return x; }
 };
 
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ void max_step(int32_t &x) {
-    x = max(x, dpp_i<CTRL, ROWMASK>(0, x));
-}
-// Inclusive maximum over the wave of values >= 0.
-__device__ __forceinline__ int32_t wave_incl_max(int32_t x) {
-    max_step<kDppRowShr1, 0xf>(x);
-    max_step<kDppRowShr2, 0xf>(x);
-    max_step<kDppRowShr4, 0xf>(x);
-    max_step<kDppRowShr8, 0xf>(x);
-    max_step<kDppRowBcast15, 0xa>(x);
-    max_step<kDppRowBcast31, 0xc>(x);
-    return x;
-}
-
 // LDS of the scatter: the ranking's marks and per-wave counts, then (over them)
 // a tile's edge words or its runs by output position; and the positions of each
 // segment's part.

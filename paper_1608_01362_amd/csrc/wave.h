@@ -37,6 +37,43 @@ __device__ __forceinline__ int32_t wave_incl_sum(int32_t x) {
     return x;
 }
 
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ void max_step(int32_t &x) {
+    x = max(x, dpp_i<CTRL, ROWMASK>(0, x));
+}
+// Inclusive maximum over the wave of values >= 0.
+__device__ __forceinline__ int32_t wave_incl_max(int32_t x) {
+    max_step<kDppRowShr1, 0xf>(x);
+    max_step<kDppRowShr2, 0xf>(x);
+    max_step<kDppRowShr4, 0xf>(x);
+    max_step<kDppRowShr8, 0xf>(x);
+    max_step<kDppRowBcast15, 0xa>(x);
+    max_step<kDppRowBcast31, 0xc>(x);
+    return x;
+}
+
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ void or_step(int32_t &x) {
+    x |= dpp_i<CTRL, ROWMASK>(0, x);
+}
+__device__ __forceinline__ uint32_t wave_or(int32_t x) {
+    or_step<kDppRowShr1, 0xf>(x);
+    or_step<kDppRowShr2, 0xf>(x);
+    or_step<kDppRowShr4, 0xf>(x);
+    or_step<kDppRowShr8, 0xf>(x);
+    or_step<kDppRowBcast15, 0xa>(x);
+    or_step<kDppRowBcast31, 0xc>(x);
+    return (uint32_t)__builtin_amdgcn_readlane(x, 63);
+}
+// The wave's values OR-ed, in scalar registers.
+__device__ __forceinline__ uint64_t wave_or64(uint64_t x) {
+    return (uint64_t)wave_or((int32_t)(uint32_t)(x >> 32)) << 32 | wave_or((int32_t)(uint32_t)x);
+}
+// Bits of a uniform mask below the lane's.
+__device__ __forceinline__ int32_t lanes_below(uint64_t m) {
+    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // A value that is the same in the whole wave, in scalar registers (the compiler
 // loads it per lane where the kernel also writes memory).
 __device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
