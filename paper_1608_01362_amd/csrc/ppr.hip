@@ -14,22 +14,41 @@
 #include <math.h>
 
 #include "common.h"
+#include "wave.h"
 
 namespace cagra {
 
 constexpr int kCols = CAGRA_PPR_COLS;
 constexpr int kPprWaves = CAGRA_TILE_WAVES;
 constexpr int kPprThreads = kPprWaves * kWave;
-constexpr int kBatch = 16;  // source rows loaded ahead per wave
+constexpr int kBatch = 16;  // source rows per wave whose loads are in flight together
+static_assert(kWave == 4 * kBatch, "four batches per 64 edge words");
 constexpr int kMergeBatch = 8;  // merge rows / vertices per wave whose loads are in flight together
 
-template <typename W>
-__global__ __launch_bounds__(kPprThreads) void k_gather_cols(const W *__restrict__ edge_src, int64_t E,
+// Each wave takes an equal share of the tile's edges; lane j adds column j. Row sums
+// are FP64 (at least as exact as FP32 with a compensation term, and a conversion and
+// an add per edge instead of seven instructions), a row's place comes from the lane
+// that read the edge word as the load's scalar offset, and the row starts of 64 edges
+// are one mask: 3 vector instructions per edge (11 before, which kept the vector unit
+// busy 86% of the time).
+//
+// Bound by the source rows: from the caches at 2^18 vertices (16 edges each, tiles of
+// 16,384 edges) 208 -> 168 us for an iteration; at 2^21, where 60% of the lines miss L2,
+// by memory's rate for scattered lines: 785 -> 750 us for the gather. (Half rows per
+// workgroup, each L2 holding twice as many, cut these misses by 18% and took 819 us.)
+//
+// FAR: segments of 4 GiB and more, whose rows a scalar offset does not reach.
+// AHEAD: the next 16 source rows are loaded before the last 16 are added, on one
+// workgroup per CU instead of two. STREAM: edge words and buffer rows leave no copy
+// in the caches. The rules for both are at the launch.
+template <typename W, bool FAR, bool AHEAD, bool STREAM>
+__global__ __launch_bounds__(kPprThreads) void k_gather_cols(const W *__restrict__ edge_src,
                                                              const int32_t *__restrict__ tile_edge,
                                                              const int32_t *__restrict__ tile_seg,
                                                              const int32_t *__restrict__ span_row,
                                                              const float *__restrict__ values, int32_t N,
-                                                             int32_t ntiles, float *__restrict__ partial) {
+                                                             uint32_t seg_bytes, int32_t ntiles,
+                                                             float *__restrict__ partial) {
     __shared__ float fix_head[kPprWaves][kCols];
     __shared__ float fix_last[kPprWaves][kCols];
     __shared__ int32_t fix_row[kPprWaves];
@@ -47,43 +66,89 @@ __global__ __launch_bounds__(kPprThreads) void k_gather_cols(const W *__restrict
     if (w1 > e1) w1 = e1;
     int32_t row = span_row[(int64_t)t * kPprWaves + w] - 1;  // row open at the share's start
     int32_t seen = 0;
-    // Neumaier-compensated row sums: rows of L2/Infinity-Cache-sized segments
-    // can hold thousands of terms
-    float acc = 0.0f, comp = 0.0f, head = 0.0f;
-    const float *vals = values + vbase * kCols + lane;
+    double acc = 0.0;
+    float head = 0.0f;
+    const float *vals = values + vbase * kCols;
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(vals), 0, (int)seg_bytes, kBufFlags);
 
-    for (int64_t b0 = w0; b0 < w1; b0 += kWave) {
-        const int64_t e = b0 + lane;
-        const uint32_t word = e < w1 ? (uint32_t)edge_src[e] : 0u;
-        const int n = (int)(w1 - b0 < kWave ? w1 - b0 : kWave);
-        for (int jb = 0; jb < n; jb += kBatch) {
-            uint32_t wv[kBatch];
-            float x[kBatch];
+    auto load_word = [&](int64_t e) {
+        return e >= w1 ? 0u : (uint32_t)(STREAM ? __builtin_nontemporal_load(edge_src + e) : edge_src[e]);
+    };
+    // a row's index (FAR) or byte offset in the segment
+    auto place = [](uint32_t word) {
+        return FAR ? word & EdgeWord<W>::kIndex : (word & EdgeWord<W>::kIndex) * (kCols * 4u);
+    };
+    // the rows of edges jb .. jb + kBatch - 1 of the 64 (the segment's first for those past the share)
+    auto load = [&](float (&x)[kBatch], uint32_t at, int jb) {
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                wv[u] = (uint32_t)__builtin_amdgcn_readlane((int32_t)word, jb + u);
-                x[u] = vals[(int64_t)(wv[u] & EdgeWord<W>::kIndex) * kCols];
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int32_t)at, jb + u);
+            if constexpr (FAR) x[u] = vals[(int64_t)o * kCols + lane];
+            else x[u] = __int_as_float((int32_t)__builtin_amdgcn_raw_buffer_load_b32(rows, lane * 4, o, 0));
+        }
+    };
+    auto add = [&](float (&x)[kBatch], uint64_t starts, int jb, int n) {
+        if (n - jb < kBatch) {  // the share ends here: the edges after it add nothing
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) x[u] = jb + u < n ? x[u] : 0.0f;
+        }
+        const uint32_t m = (uint32_t)(starts >> jb);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (m >> u & 1u) {  // a row starts: the open row is complete
+                float *const to = partial + (int64_t)row * kCols + lane;
+                if (!seen) head = (float)acc;
+                else if constexpr (STREAM) __builtin_nontemporal_store((float)acc, to);
+                else *to = (float)acc;
+                seen = 1;
+                ++row;
+                acc = 0.0;
             }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                if (jb + u < n) {
-                    if (wv[u] & EdgeWord<W>::kFlag) {  // a row starts: the open row is complete
-                        if (seen) partial[(int64_t)row * kCols + lane] = acc + comp;
-                        else head = acc + comp;
-                        seen = 1;
-                        ++row;
-                        acc = 0.0f;
-                        comp = 0.0f;
-                    }
-                    const float tsum = acc + x[u];
-                    comp += fabsf(acc) >= fabsf(x[u]) ? (acc - tsum) + x[u] : (x[u] - tsum) + acc;
-                    acc = tsum;
-                }
+            acc += (double)x[u];
+        }
+    };
+
+    if constexpr (AHEAD) {
+        if (w0 < w1) {
+            float xa[kBatch], xb[kBatch];
+            uint32_t word = load_word(w0 + lane), next = load_word(w0 + kWave + lane), at = place(word);
+            load(xa, at, 0);
+            for (int64_t b0 = w0; b0 < w1; b0 += kWave) {
+                const uint64_t starts = __builtin_amdgcn_ballot_w64((word & EdgeWord<W>::kFlag) != 0);
+                const int n = (int)(w1 - b0 < kWave ? w1 - b0 : kWave);
+                word = next;
+                next = load_word(b0 + 2 * kWave + lane);
+                // the barriers keep each batch's loads before the sums of the one before it
+                load(xb, at, kBatch);
+                __builtin_amdgcn_sched_barrier(0);
+                add(xa, starts, 0, n);
+                load(xa, at, 2 * kBatch);
+                __builtin_amdgcn_sched_barrier(0);
+                add(xb, starts, kBatch, n);
+                load(xb, at, 3 * kBatch);
+                __builtin_amdgcn_sched_barrier(0);
+                add(xa, starts, 2 * kBatch, n);
+                at = place(word);
+                load(xa, at, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                add(xb, starts, 3 * kBatch, n);
+            }
+        }
+    } else {
+        for (int64_t b0 = w0; b0 < w1; b0 += kWave) {
+            const uint32_t word = load_word(b0 + lane), at = place(word);
+            const uint64_t starts = __builtin_amdgcn_ballot_w64((word & EdgeWord<W>::kFlag) != 0);
+            const int n = (int)(w1 - b0 < kWave ? w1 - b0 : kWave);
+            for (int jb = 0; jb < n; jb += kBatch) {
+                float x[kBatch];
+                load(x, at, jb);
+                add(x, starts, jb, n);
             }
         }
     }
-    fix_head[w][lane] = seen ? head : acc + comp;
-    fix_last[w][lane] = acc + comp;
+    fix_head[w][lane] = seen ? head : (float)acc;
+    fix_last[w][lane] = (float)acc;
     if (lane == 0) {
         fix_row[w] = row;
         fix_has[w] = seen;
@@ -258,19 +323,36 @@ cagra_status launch_ppr_init(const cagra_graph *g, int32_t ncols, const int32_t 
     return CAGRA_OK;
 }
 
+template <typename W>
+static void launch_gather_cols(const cagra_segments *seg, const float *values, float *partial, hipStream_t st) {
+    const int64_t row_bytes = kCols * 4, bytes = (seg->N < seg->V ? seg->N : seg->V) * row_bytes;
+    const bool far = bytes > UINT32_MAX;
+    // Shares of 512 edges and more gain from loading ahead, shorter ones from the
+    // second workgroup. An iteration with and without, us: 2^20 vertices, shares of
+    // 1,024 edges 637 and 707, of 256 edges 682 and 629; 2^18, 4,096 edges 327 and 357,
+    // 256 edges 165 and 156.
+    const bool ahead = seg->E >= (int64_t)512 * kPprWaves * seg->ntiles;
+    // Values and buffer rows that exceed the 256 MB of Infinity Cache: streams that
+    // leave no copies keep the values in it. With and without, us: 2^21 vertices, eight
+    // segments 1,360 and 1,435; 2^20 619 and 629; but 2^18 of eight segments (218 MB)
+    // 214 and 205, 2^14 99 and 97.
+    const bool stream = ((int64_t)seg->V + seg->Q) * row_bytes > (int64_t)256 << 20;
+    auto kern = ahead ? (stream ? k_gather_cols<W, false, true, true> : k_gather_cols<W, false, true, false>)
+                      : (stream ? k_gather_cols<W, false, false, true> : k_gather_cols<W, false, false, false>);
+    if constexpr (sizeof(W) == 4)
+        if (far) kern = k_gather_cols<W, true, false, true>;
+    kern<<<seg->ntiles, kPprThreads, 0, st>>>(static_cast<const W *>(seg->edge_src), seg->tile_edge, seg->tile_seg,
+                                              seg->tile_span_row, values, seg->N, (uint32_t)bytes, seg->ntiles,
+                                              partial);
+}
+
 cagra_status launch_ppr_iter(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t ncols,
                              const int32_t *seeds, const float *rank_in, const float *contrib_in,
                              const double *scalars_in, float *partial, float *rank_out, float *contrib_out,
                              double *scalars_out, double *blk, hipStream_t st) {
     if (seg->ntiles > 0) {
-        if (edge16(seg->N))
-            k_gather_cols<uint16_t><<<seg->ntiles, kPprThreads, 0, st>>>(
-                static_cast<const uint16_t *>(seg->edge_src), seg->E, seg->tile_edge, seg->tile_seg,
-                seg->tile_span_row, contrib_in, seg->N, seg->ntiles, partial);
-        else
-            k_gather_cols<uint32_t><<<seg->ntiles, kPprThreads, 0, st>>>(
-                static_cast<const uint32_t *>(seg->edge_src), seg->E, seg->tile_edge, seg->tile_seg,
-                seg->tile_span_row, contrib_in, seg->N, seg->ntiles, partial);
+        if (edge16(seg->N)) launch_gather_cols<uint16_t>(seg, contrib_in, partial, st);
+        else launch_gather_cols<uint32_t>(seg, contrib_in, partial, st);
         CAGRA_LAUNCH_CHECK();
     }
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_ppr)) return a_;
