@@ -40,22 +40,35 @@ constexpr int kMergeBatch = 8;  // merge rows / vertices per wave whose loads ar
 // FAR: segments of 4 GiB and more, whose rows a scalar offset does not reach.
 // AHEAD: the next 16 source rows are loaded before the last 16 are added, on one
 // workgroup per CU instead of two. STREAM: edge words and buffer rows leave no copy
-// in the caches. The rules for both are at the launch.
-template <typename W, bool FAR, bool AHEAD, bool STREAM>
+// in the caches. SPLIT: a tile is the work of `parts` workgroups (a divisor of its
+// shares). A part takes the rows that start in its shares, to their ends, so no sum
+// crosses workgroups; its own shares' first rows are found by counting row starts.
+// The rules for these are at the launch.
+template <typename W, bool FAR, bool AHEAD, bool STREAM, bool SPLIT>
 __global__ __launch_bounds__(kPprThreads) void k_gather_cols(const W *__restrict__ edge_src,
                                                              const int32_t *__restrict__ tile_edge,
                                                              const int32_t *__restrict__ tile_seg,
                                                              const int32_t *__restrict__ span_row,
                                                              const float *__restrict__ values, int32_t N,
                                                              uint32_t seg_bytes, int32_t ntiles,
+                                                             const int32_t *__restrict__ row_ptr, int32_t parts,
                                                              float *__restrict__ partial) {
     __shared__ float fix_head[kPprWaves][kCols];
     __shared__ float fix_last[kPprWaves][kCols];
     __shared__ int32_t fix_row[kPprWaves];
     __shared__ int32_t fix_has[kPprWaves];
 
-    const int t = xcd_remap(blockIdx.x, ntiles);
-    const int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
+    const int tp = xcd_remap(blockIdx.x, SPLIT ? ntiles * parts : ntiles), t = SPLIT ? tp / parts : tp;
+    int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
+    int32_t first = 0;  // SPLIT: first row of the part
+    if constexpr (SPLIT) {
+        const int part = tp - t * parts;
+        const int32_t *span = span_row + (int64_t)t * kPprWaves + part * (kPprWaves / parts);
+        first = span[0];
+        const int64_t end = part == parts - 1 ? e1 : row_ptr[span[kPprWaves / parts]];
+        if (part > 0) e0 = row_ptr[first];
+        if (end < e1) e1 = end;
+    }
     if (e0 >= e1) return;
     const int64_t vbase = (int64_t)tile_seg[t] * N;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -64,7 +77,22 @@ __global__ __launch_bounds__(kPprThreads) void k_gather_cols(const W *__restrict
     if (w0 > e1) w0 = e1;
     int64_t w1 = w0 + sl;
     if (w1 > e1) w1 = e1;
-    int32_t row = span_row[(int64_t)t * kPprWaves + w] - 1;  // row open at the share's start
+    int32_t row;  // row open at the share's start
+    if constexpr (SPLIT) {
+        int32_t n = 0;
+        for (int64_t e = w0; e < w1; e += kWave) {
+            const uint32_t word = e + lane < w1 ? (uint32_t)edge_src[e + lane] : 0u;
+            n += (int32_t)__popcll(__builtin_amdgcn_ballot_w64((word & EdgeWord<W>::kFlag) != 0));
+        }
+        if (lane == 0) fix_row[w] = n;
+        __syncthreads();
+        row = first - 1;
+        for (int i = 0; i < w; ++i) row += fix_row[i];
+        row = __builtin_amdgcn_readfirstlane(row);
+        __syncthreads();  // fix_row is written again at the end
+    } else {
+        row = span_row[(int64_t)t * kPprWaves + w] - 1;
+    }
     int32_t seen = 0;
     double acc = 0.0;
     float head = 0.0f;
@@ -327,23 +355,33 @@ template <typename W>
 static void launch_gather_cols(const cagra_segments *seg, const float *values, float *partial, hipStream_t st) {
     const int64_t row_bytes = kCols * 4, bytes = (seg->N < seg->V ? seg->N : seg->V) * row_bytes;
     const bool far = bytes > UINT32_MAX;
+    // Few tiles are split until there is a workgroup per CU, as long as parts keep 256
+    // edges. An iteration, whole tiles and split, us: 2^10 vertices, one tile 72 and 29;
+    // 2^14, 1 / 4 / 14 tiles 898 and 90 / 273 and 41 / 93 and 39; 2^17, 30 / 119 tiles 289
+    // and 91 / 103 and 89; 2^19, 122 tiles 405 and 341. Two workgroups per CU: 30 tiles
+    // 104, 119 tiles 99, 241 tiles 195 against 166 whole.
+    int32_t parts = 1;
+    while (!far && seg->row_ptr && parts < kPprWaves && (int64_t)seg->ntiles * parts * 2 <= 256 &&
+           seg->E >= (int64_t)256 * 2 * parts * seg->ntiles)
+        parts *= 2;
     // Shares of 512 edges and more gain from loading ahead, shorter ones from the
     // second workgroup. An iteration with and without, us: 2^20 vertices, shares of
     // 1,024 edges 637 and 707, of 256 edges 682 and 629; 2^18, 4,096 edges 327 and 357,
     // 256 edges 165 and 156.
-    const bool ahead = seg->E >= (int64_t)512 * kPprWaves * seg->ntiles;
+    const bool ahead = seg->E >= (int64_t)512 * kPprWaves * parts * seg->ntiles;
     // Values and buffer rows that exceed the 256 MB of Infinity Cache: streams that
     // leave no copies keep the values in it. With and without, us: 2^21 vertices, eight
     // segments 1,360 and 1,435; 2^20 619 and 629; but 2^18 of eight segments (218 MB)
     // 214 and 205, 2^14 99 and 97.
     const bool stream = ((int64_t)seg->V + seg->Q) * row_bytes > (int64_t)256 << 20;
-    auto kern = ahead ? (stream ? k_gather_cols<W, false, true, true> : k_gather_cols<W, false, true, false>)
-                      : (stream ? k_gather_cols<W, false, false, true> : k_gather_cols<W, false, false, false>);
+    auto kern = ahead ? (stream ? k_gather_cols<W, false, true, true, false> : k_gather_cols<W, false, true, false, false>)
+                      : (stream ? k_gather_cols<W, false, false, true, false> : k_gather_cols<W, false, false, false, false>);
+    if (parts > 1) kern = ahead ? k_gather_cols<W, false, true, false, true> : k_gather_cols<W, false, false, false, true>;
     if constexpr (sizeof(W) == 4)
-        if (far) kern = k_gather_cols<W, true, false, true>;
-    kern<<<seg->ntiles, kPprThreads, 0, st>>>(static_cast<const W *>(seg->edge_src), seg->tile_edge, seg->tile_seg,
-                                              seg->tile_span_row, values, seg->N, (uint32_t)bytes, seg->ntiles,
-                                              partial);
+        if (far) kern = k_gather_cols<W, true, false, true, false>;
+    kern<<<seg->ntiles * parts, kPprThreads, 0, st>>>(static_cast<const W *>(seg->edge_src), seg->tile_edge,
+                                                      seg->tile_seg, seg->tile_span_row, values, seg->N,
+                                                      (uint32_t)bytes, seg->ntiles, seg->row_ptr, parts, partial);
 }
 
 cagra_status launch_ppr_iter(const cagra_graph *g, const cagra_segments *seg, double damping, int32_t ncols,

@@ -87,3 +87,32 @@ def test_segment_of_4_gib(cagra):
     want = torch.zeros((800, 64), dtype=torch.float64, device="cuda")
     want.index_add_(0, 5 + torch.arange(len(u), device="cuda") % 700, x.double())
     _check(st, seg, 800, want, slice(0, 800))
+
+
+# few tiles: cut into parts that hold the rows starting in them
+SPLIT = [("star", 40000, 2047, 40000, 512, 65536), ("star", 40000, 2048, 40000, 512, 65536),
+         ("star", 40000, 30000, 32768, 512, 65536), ("random", 64, 2500, 64, 64, 65536),
+         ("random", 700, 5000, 700, 64, 65536), ("random", 3000, 20000, 40000, 512, 65536),
+         ("random", 30000, 200000, 40000, 512, 65536), ("random", 30000, 200000, 8000, 512, 16384),
+         ("random", 5000, 300000, 5000, 512, 1 << 20), ("random", 60000, 900000, 32768, 128, 1 << 20)]
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=[f"{c[0]}-{c[1]}-{c[2]}-{c[3]}" for c in SPLIT])
+def test_split_tiles(cagra, case):
+    test_sums(cagra, case)
+
+
+def test_split_equals_a_tile_per_part(cagra):
+    """Rows of one edge: nothing is added, so the buffer of split tiles equals that of many small ones."""
+    import torch
+    V = 6000
+    p = np.random.default_rng(1).permutation(V)
+    g = graphgen.from_edge_list(V, [(int(p[i]), int(p[i - 1])) for i in range(V)])
+    x = torch.randn((V, 64), device="cuda")
+    out = []
+    for T in (64, 65536):
+        _, st = _start(cagra, g, 2500, 512, T)
+        st.contrib[0].copy_(x.reshape(-1))
+        st.step(0.85)
+        out.append(st.ranks().clone())
+    assert torch.equal(out[0], out[1])
