@@ -198,7 +198,8 @@ int cagra_cluster(const cagra_graph *g, int32_t *perm, int32_t *in_offsets, int3
 cagra_status cagra_segment_edge_values(const cagra_graph *g, const cagra_segments *seg, const float *in_values,
                                        float *seg_values, hipStream_t stream);
 
-/* Device workspace of cagra_cf_iter (one FP64 value per gather tile). */
+/* Device workspace of cagra_cf_iter (one FP64 value per workgroup of the gather:
+   per tile, or per part of a tile where few tiles are split). */
 size_t cagra_cf_workspace_bytes(const cagra_segments *seg);
 
 /*

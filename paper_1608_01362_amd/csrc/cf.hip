@@ -111,22 +111,33 @@ __device__ __forceinline__ float dot4(float4 a, float4 b) {
 // written when the row closes inside the part; rows that continue across parts
 // are completed after a barrier in part order. The row open at a part's start
 // is the share's open row advanced by the row starts before the part.
-template <typename W>
+// SPLIT: a tile is the work of `parts` workgroups (a divisor of its shares), each with
+// the rows that start in its shares, to their ends.
+template <typename W, bool SPLIT>
 __global__ __launch_bounds__(kCfThreads) void k_cf_gather(
     const W *__restrict__ edge_src, const float *__restrict__ vals, const int32_t *__restrict__ tile_edge,
     const int32_t *__restrict__ tile_seg, const int32_t *__restrict__ span_row, const int32_t *__restrict__ row_dst,
-    const float *__restrict__ X, int32_t N, int32_t ntiles, float *__restrict__ partial,
-    double *__restrict__ tile_sq) {
+    const float *__restrict__ X, int32_t N, int32_t ntiles, const int32_t *__restrict__ row_ptr, int32_t parts,
+    float *__restrict__ partial, double *__restrict__ tile_sq) {
     __shared__ float4 fix_head[kCfGroups][kGroup];
     __shared__ float4 fix_last[kCfGroups][kGroup];
     __shared__ int32_t fix_row[kCfGroups];
     __shared__ int32_t fix_has[kCfGroups];
     __shared__ double red_sq[kCfGroups];
 
-    const int t = xcd_remap(blockIdx.x, ntiles);
-    const int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
+    const int tp = xcd_remap(blockIdx.x, SPLIT ? ntiles * parts : ntiles), t = SPLIT ? tp / parts : tp;
+    int64_t e0 = tile_edge[t], e1 = tile_edge[t + 1];
+    int32_t first = 0;  // SPLIT: first row of the workgroup's part of the tile
+    if constexpr (SPLIT) {
+        const int p = tp - t * parts;
+        const int32_t *span = span_row + (int64_t)t * kCfWaves + p * (kCfWaves / parts);
+        first = span[0];
+        const int64_t end = p == parts - 1 ? e1 : row_ptr[span[kCfWaves / parts]];
+        if (p > 0) e0 = row_ptr[first];
+        if (end < e1) e1 = end;
+    }
     if (e0 >= e1) {  // an empty tile (uniform over the workgroup): nothing to read
-        if (threadIdx.x == 0) tile_sq[t] = 0.0;
+        if (threadIdx.x == 0) tile_sq[tp] = 0.0;
         return;
     }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -140,7 +151,21 @@ __global__ __launch_bounds__(kCfThreads) void k_cf_gather(
     const GroupPart part = group_part<W>(edge_src, w0, w1, g, lane);
     const int64_t a = part.a, b = part.b, gl = part.len;
     const int32_t before = part.before;
-    int32_t row = span_row[(int64_t)t * kCfWaves + w] - 1 + before;  // row open at the part's start
+    int32_t row = before;  // row open at the part's start
+    if constexpr (SPLIT) {
+        int32_t n = 0;  // row starts in the share
+        for (int64_t e = w0; e < w1; e += kWave) {
+            const uint32_t word = e + lane < w1 ? (uint32_t)edge_src[e + lane] : 0u;
+            n += (int32_t)__popcll(__builtin_amdgcn_ballot_w64((word & EdgeWord<W>::kFlag) != 0));
+        }
+        if (lane == 0) fix_row[w] = n;
+        __syncthreads();
+        row += first - 1;
+        for (int i = 0; i < w; ++i) row += fix_row[i];
+        __syncthreads();  // fix_row is written again at the end
+    } else {
+        row += span_row[(int64_t)t * kCfWaves + w] - 1;
+    }
     int32_t seen = 0;
     float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f), xv = acc;
     float sqf = 0.0f;
@@ -217,7 +242,7 @@ __global__ __launch_bounds__(kCfThreads) void k_cf_gather(
     if (threadIdx.x == 0) {
         double s2 = 0.0;
         for (int x2 = 0; x2 < kCfGroups; ++x2) s2 += red_sq[x2];
-        tile_sq[t] = s2;
+        tile_sq[tp] = s2;
     }
 }
 
@@ -289,18 +314,34 @@ __global__ __launch_bounds__(256) void k_sum_tiles(const double *__restrict__ ti
 
 size_t cf_merge_lds_bytes(int32_t B) { return (size_t)B * kCfK * sizeof(float); }
 
+// Few tiles are split until there is a workgroup per CU, as long as parts keep 256
+// edges. A step, whole tiles and split, us: 886 K edges, 14 / 55 tiles 304 and 40 / 100
+// and 52; 5 M, 78 tiles 310 and 184. The squared errors are FP32 sums within windows of
+// four edges, and the windows move with the parts: the total moves by 4e-9 of itself at
+// 2,700 edges, 5e-10 at 160 K, 1e-10 at 886 K. Below 2^18 edges it would not keep 1e-9
+// safely, and a step keeps its tiles.
+int32_t cf_parts(const cagra_segments *seg) {
+    int32_t parts = 1;
+    while (seg->row_ptr && seg->E >= 1 << 18 && parts < kCfWaves && (int64_t)seg->ntiles * parts * 2 <= 256 &&
+           seg->E >= (int64_t)256 * 2 * parts * seg->ntiles)
+        parts *= 2;
+    return parts;
+}
+
+// parts: 1 or cf_parts(seg); tile_sq holds seg->ntiles * parts values
 cagra_status launch_cf_iter(const cagra_segments *seg, const float *seg_values, double gamma, double lambda,
                             const float *x_in, float *partial, float *x_out, double *sq_out, double *tile_sq,
-                            hipStream_t st) {
+                            int32_t parts, hipStream_t st) {
     if (seg->ntiles > 0) {
-        if (edge16(seg->N))
-            k_cf_gather<uint16_t><<<seg->ntiles, kCfThreads, 0, st>>>(
-                static_cast<const uint16_t *>(seg->edge_src), seg_values, seg->tile_edge, seg->tile_seg,
-                seg->tile_span_row, seg->row_dst, x_in, seg->N, seg->ntiles, partial, tile_sq);
-        else
-            k_cf_gather<uint32_t><<<seg->ntiles, kCfThreads, 0, st>>>(
-                static_cast<const uint32_t *>(seg->edge_src), seg_values, seg->tile_edge, seg->tile_seg,
-                seg->tile_span_row, seg->row_dst, x_in, seg->N, seg->ntiles, partial, tile_sq);
+        auto launch = [&](auto kern, auto *edges) {
+            kern<<<seg->ntiles * parts, kCfThreads, 0, st>>>(edges, seg_values, seg->tile_edge, seg->tile_seg,
+                                                             seg->tile_span_row, seg->row_dst, x_in, seg->N,
+                                                             seg->ntiles, seg->row_ptr, parts, partial, tile_sq);
+        };
+        const auto *e16 = static_cast<const uint16_t *>(seg->edge_src);
+        const auto *e32 = static_cast<const uint32_t *>(seg->edge_src);
+        if (edge16(seg->N)) launch(parts > 1 ? k_cf_gather<uint16_t, true> : k_cf_gather<uint16_t, false>, e16);
+        else launch(parts > 1 ? k_cf_gather<uint32_t, true> : k_cf_gather<uint32_t, false>, e32);
         CAGRA_LAUNCH_CHECK();
     }
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_cf)) return a_;
@@ -308,7 +349,7 @@ cagra_status launch_cf_iter(const cagra_segments *seg, const float *seg_values, 
         seg->row_dst, seg->block_ptr, partial, seg->V, seg->k, seg->B, seg->nb, (float)gamma, (float)lambda, x_in,
         x_out);
     CAGRA_LAUNCH_CHECK();
-    k_sum_tiles<<<1, 256, 0, st>>>(tile_sq, seg->ntiles, sq_out);
+    k_sum_tiles<<<1, 256, 0, st>>>(tile_sq, seg->ntiles * parts, sq_out);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }
