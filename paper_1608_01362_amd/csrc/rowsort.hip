@@ -10,8 +10,9 @@
 //      prefix sums with 64 cells per power of two). In a row of n edges the
 //      slots are then spread over the n places almost evenly.
 //   2. LDS counts per slot, a scan, and every edge is placed among its slot's
-//      few edges (mean two) by comparing with them. The ids of a row are
-//      distinct, so the order is unique however the counting atomics fall.
+//      few edges (mean two) by comparing with them, equal ids (repeated edges)
+//      by their places there, so the result is unique however the counting
+//      atomics fall.
 // G only steers the work. A slot of more than kMaxSlot edges is spread over its
 // own places, linearly between its smallest and largest id (rows of neighbouring
 // ids, communities: one or two such passes), and what is still crowded after
@@ -298,15 +299,20 @@ __device__ __forceinline__ bool sort_tile(SortLds<ITEMS> &L, const uint32_t (&ke
         return false;
     }
     if (!ANY || !crowded) {
+        static_assert(kMaxSlot < 128, "a slot's edges and an edge's turn in seven bits each");
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j)
-            if (j * kRsThreads + tid < n) L.key[(lo[j] & 0xffffu) + (slot[j] >> 16)] = key[j];
+        for (int j = 0; j < ITEMS; ++j) {
+            const uint32_t turn = slot[j] >> 16;
+            if (j * kRsThreads + tid < n) L.key[(lo[j] & 0xffffu) + turn] = key[j];
+            lo[j] |= turn << 23;  // one register for all three: a register more each would spill
+        }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
-            const uint32_t a = lo[j] & 0xffffu, m = j * kRsThreads + tid < n ? lo[j] >> 16 : 0u;
-            uint32_t less = 0;
-            for (uint32_t q = 0; m > 1 && q < m; ++q) less += L.key[a + q] < key[j] ? 1u : 0u;
+            const uint32_t a = lo[j] & 0xffffu, m = j * kRsThreads + tid < n ? lo[j] >> 16 & 127u : 0u;
+            const uint32_t turn = lo[j] >> 23;
+            uint32_t less = 0;  // smaller ids, and equal ones placed before this one
+            for (uint32_t q = 0; m > 1 && q < m; ++q) less += L.key[a + q] < key[j] + (q < turn ? 1u : 0u) ? 1u : 0u;
             lo[j] = a + less;
         }
         __syncthreads();
@@ -563,8 +569,8 @@ constexpr int kMgThreads = 256;
 constexpr int kMgItems = kUnit / kMgThreads;
 static_assert(kRsCap == 2 * kUnit, "a piece is two merge units");
 
-// Number of A's elements among the first d of A and B merged (all distinct):
-// the first a in [max(0, d - nb), min(d, na)] with A[a] > B[d - 1 - a], found by
+// Number of A's elements among the first d of A and B merged (B's first among equals):
+// the first a in [max(0, d - nb), min(d, na)] with A[a] >= B[d - 1 - a], found by
 // the whole wave, 64 probes a round.
 __device__ __forceinline__ int32_t merge_split(const int32_t *__restrict__ A, int32_t na,
                                                const int32_t *__restrict__ B, int32_t nb, int32_t d) {
