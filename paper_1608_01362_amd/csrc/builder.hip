@@ -632,9 +632,11 @@ cagra_status build_segments(const cagra_graph *g, cagra_segments *seg, void *ws,
         CAGRA_LAUNCH_CHECK();
         return build_block_items(seg, ar, st);
     }
-    // 1.-3. rows, offsets and edge words in segment-major order
-    if (k <= kDirectMaxSegments) {
-        const size_t at = align_up(ar.used, 256);
+    // 1.-3. rows, offsets and edge words in segment-major order. The caller's struct
+    // says how much workspace is enough; where it is less than the direct form
+    // takes, the sorted form looks whether it fits
+    const size_t at = align_up(ar.used, 256);
+    if (k <= kDirectMaxSegments && at <= ws_bytes && ws_bytes - at >= direct_ws_bytes(g->V, E, k)) {
         s = build_direct(g, seg, ar.base + at, ws_bytes - at, st);
     } else {
         const size_t mark = ar.used;
