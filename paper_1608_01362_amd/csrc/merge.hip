@@ -129,19 +129,20 @@ __device__ __forceinline__ int32_t list_ranges(const uint16_t *__restrict__ dlo,
 }
 
 // HEAVY = false merges the blocks that are one work item (every block when
-// block_items is null), HEAVY = true the split ones, in kOrdParts parts.
+// block_items is null), HEAVY = true the split ones, in kOrdParts parts; of the nb
+// blocks from b0 on.
 template <class Op, bool COMP, int W, bool HEAVY>
 __global__ __launch_bounds__(W * 64) void k_merge_ordered(const uint16_t *__restrict__ row_dst_lo,
                                                           const int32_t *__restrict__ block_ptr,
                                                           const int32_t *__restrict__ block_items,
                                                           const typename Op::T *__restrict__ partial, int32_t V,
-                                                          int32_t k, int32_t B, int32_t nb,
+                                                          int32_t k, int32_t B, int32_t b0, int32_t nb,
                                                           typename Op::T *__restrict__ out,
                                                           const uint32_t *__restrict__ seg_active) {
     using T = typename Op::T;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int32_t tmp[W];
-    const int b = HEAVY ? (int)(blockIdx.x / kOrdParts) : xcd_remap(blockIdx.x, nb);
+    const int b = b0 + (HEAVY ? (int)(blockIdx.x / kOrdParts) : xcd_remap(blockIdx.x, nb));
     if (HEAVY || block_items)
         if ((block_items[b + 1] - block_items[b] > 1) != HEAVY) return;  // uniform over the workgroup
     const int64_t vb = (int64_t)b * B;
@@ -232,10 +233,16 @@ static cagra_status launch_ordered_w(const cagra_segments *seg, const void *part
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
     // no block is split when the item bound equals nb: the item table is not read then
     const int32_t *items = seg->max_items > seg->nb ? seg->block_items : nullptr;
-    kern<<<(unsigned)seg->nb * (HEAVY ? kOrdParts : 1), W * 64, ordered_lds(seg->B, seg->k, COMP, HEAVY), st>>>(
-        seg->row_dst_lo, seg->block_ptr, items, (const T *)partial, seg->V, seg->k, seg->B, seg->nb, (T *)out,
-        seg_active);
-    CAGRA_LAUNCH_CHECK();
+    // a launch has fewer than 2^32 threads: with small blocks of many vertices it takes several
+    constexpr int32_t parts = HEAVY ? kOrdParts : 1, most = (int32_t)(UINT32_MAX / (W * kWave * parts));
+    for (int32_t b0 = 0; b0 < seg->nb; b0 += most) {
+        const int32_t n = min(seg->nb - b0, most);
+        kern<<<(unsigned)n * parts, W * kWave, ordered_lds(seg->B, seg->k, COMP, HEAVY), st>>>(
+            seg->row_dst_lo, seg->block_ptr, items, (const T *)partial, seg->V, seg->k, seg->B, b0, n, (T *)out,
+            seg_active);
+        CAGRA_LAUNCH_CHECK();
+        if (n < most) break;  // b0 + most may not fit
+    }
     return CAGRA_OK;
 }
 
