@@ -162,6 +162,16 @@ static cagra_status check_built(const cagra_segments *seg) {
     return CAGRA_OK;
 }
 
+// A launch has fewer than 2^32 threads (beyond that the grid wraps, and most of the
+// work is silently not done), and the kernels over tiles and over merge blocks or work
+// items take a workgroup of 1,024 threads for each. blocks: those of the call's merge.
+static cagra_status check_launches(const cagra_segments *seg, int64_t blocks) {
+    constexpr int64_t most = UINT32_MAX / 1024;
+    if (seg->ntiles > most) return fail(CAGRA_E_CAPACITY, "%d tiles exceed one launch", seg->ntiles);
+    if (blocks > most) return fail(CAGRA_E_CAPACITY, "%lld merge blocks exceed one launch", (long long)blocks);
+    return CAGRA_OK;
+}
+
 static size_t iter_ws_bytes(const cagra_segments *seg) {
     return ws_blk_bytes(seg->V, seg->nb) + ws_item_bytes(seg) + ws_slot_bytes(seg) + 256;
 }
@@ -222,6 +232,7 @@ cagra_status cagra_cf_iter(const cagra_graph *g, const cagra_segments *seg, cons
     if ((s = check_built(seg)) != CAGRA_OK) return s;
     if (seg->V != g->V || seg->E != g->E) return fail(CAGRA_E_INVALID, "segments belong to a different graph");
     if (seg->B > kMaxPprBlock) return fail(CAGRA_E_CAPACITY, "the CF merge needs B <= %d (got %d)", kMaxPprBlock, seg->B);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!x_in || !x_out || !sq_out || (seg->Q > 0 && (!partial || !seg_values)))
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if ((const void *)x_in == (const void *)x_out) return fail(CAGRA_E_INVALID, "x_in and x_out must not alias");
@@ -255,6 +266,7 @@ static cagra_status check_bc(const cagra_segments *seg, const void *depth, const
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if (merge_ordered_lds_bytes(seg->B, CAGRA_SUM_F32) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "merge block B=%d too large", seg->B);
+    if ((s = check_launches(seg, 0)) != CAGRA_OK) return s;
     if (!workspace || workspace_bytes < cagra_bc_workspace_bytes(seg))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", cagra_bc_workspace_bytes(seg),
                     workspace_bytes);
@@ -343,6 +355,7 @@ cagra_status cagra_segment_gather(const cagra_segments *seg, int32_t op, int32_t
         !(op == CAGRA_MIN_I32 && value_type == CAGRA_I32))
         return fail(CAGRA_E_INVALID, "unsupported gather op %d with value type %d", op, value_type);
     if (!values || (seg->Q > 0 && !partial)) return fail(CAGRA_E_INVALID, "values or partial is NULL");
+    if ((s = check_launches(seg, 0)) != CAGRA_OK) return s;
     return launch_gather(seg, op, value_type, values, partial, stream);
 }
 
@@ -381,7 +394,7 @@ static cagra_status check_pagerank_core(const cagra_graph *g, const cagra_segmen
         return fail(CAGRA_E_INVALID, "contrib_type must be CAGRA_F32 or CAGRA_BF16");
     if (merge_fused_lds_total(seg->B, seg->k, 8) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
-    return CAGRA_OK;
+    return check_launches(seg, seg->max_items);
 }
 
 static cagra_status check_pagerank(const cagra_graph *g, const cagra_segments *seg, double damping,
@@ -573,6 +586,7 @@ cagra_status cagra_labelprop_iter(const cagra_segments *seg, const int32_t *labe
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if (merge_fused_lds_total(seg->B, seg->k, 4) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!workspace || workspace_bytes < iter_ws_bytes(seg))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", iter_ws_bytes(seg),
                     workspace_bytes);
@@ -647,6 +661,7 @@ cagra_status cagra_labelprop_solve(const cagra_segments *seg, int32_t max_iters,
     if (labels0 == labels1) return fail(CAGRA_E_INVALID, "the two label buffers must differ");
     if (merge_fused_lds_total(seg->B, seg->k, 4) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!workspace || workspace_bytes < iter_ws_bytes(seg))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", iter_ws_bytes(seg),
                     workspace_bytes);
@@ -676,6 +691,7 @@ cagra_status cagra_degree_features(const cagra_graph *g, const cagra_segments *s
     if (!features) return fail(CAGRA_E_INVALID, "features is NULL");
     if (merge_fused_lds_total(seg->B, seg->k, 8) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!workspace || workspace_bytes < features_ws_bytes(seg))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", features_ws_bytes(seg), workspace_bytes);
     return launch_features(g, seg, features, workspace, stream);
@@ -753,6 +769,7 @@ cagra_status cagra_learned_start(const cagra_graph *g, const cagra_segments *seg
     if (!weights || !norm || !rank0 || !scalars_out) return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if (merge_fused_lds_total(seg->B, seg->k, 8) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!workspace || workspace_bytes < learned_start_ws_bytes(seg))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", learned_start_ws_bytes(seg),
                     workspace_bytes);
@@ -798,6 +815,7 @@ cagra_status cagra_ppr_iter(const cagra_graph *g, const cagra_segments *seg, dou
     if (!(damping >= 0.0 && damping <= 1.0)) return fail(CAGRA_E_INVALID, "damping must be in [0, 1]");
     if (ncols < 1 || ncols > CAGRA_PPR_COLS) return fail(CAGRA_E_INVALID, "ncols must be in [1, %d]", CAGRA_PPR_COLS);
     if (seg->B > kMaxPprBlock) return fail(CAGRA_E_CAPACITY, "batched merge needs B <= %d (got %d)", kMaxPprBlock, seg->B);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!seeds || !rank_in || !contrib_in || !scalars_in || !rank_out || !contrib_out || !scalars_out ||
         (seg->Q > 0 && !partial))
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
@@ -878,6 +896,7 @@ cagra_status cagra_ppr_solve(const cagra_graph *g, const cagra_segments *seg, co
     if (p->max_iters < 1 || p->check_every < 1) return fail(CAGRA_E_INVALID, "max_iters and check_every must be >= 1");
     if (ncols < 1 || ncols > CAGRA_PPR_COLS) return fail(CAGRA_E_INVALID, "ncols must be in [1, %d]", CAGRA_PPR_COLS);
     if (seg->B > kMaxPprBlock) return fail(CAGRA_E_CAPACITY, "batched merge needs B <= %d (got %d)", kMaxPprBlock, seg->B);
+    if ((s = check_launches(seg, seg->nb)) != CAGRA_OK) return s;
     if (!seeds || !rank0 || !rank1 || !contrib0 || !contrib1 || !scalars || (seg->Q > 0 && !partial))
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if (rank0 == rank1 || contrib0 == contrib1) return fail(CAGRA_E_INVALID, "the two buffers of a pair must differ");
@@ -913,6 +932,7 @@ static cagra_status check_push(const cagra_segments *seg, int acc_bytes, const v
                     acc_bytes);
     if (push_expand_lds_total(seg->B, seg->k) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the expand kernel's LDS", seg->B, seg->k);
+    if ((s = check_launches(seg, (int64_t)seg->max_items + 1)) != CAGRA_OK) return s;  // and the plan's workgroup
     if (push_max_pieces(seg) > INT32_MAX / 2) return fail(CAGRA_E_OVERFLOW, "too many push pieces");
     if (seg->Q > 0 && !vals) return fail(CAGRA_E_INVALID, "vals is NULL");
     if (!workspace || workspace_bytes < push_ws_bytes(seg))

@@ -1,12 +1,13 @@
 """Limits that the host checks before any launch, without a GPU: a build workspace
-smaller than the builder takes."""
+smaller than the builder takes, and more tiles or merge blocks than one launch
+of 2^32 threads holds."""
 import ctypes
 
 import pytest
 
 from test_abi_cpu import _fake_built, _graph, cagra  # noqa: F401
 
-BUFFER = -4
+CAPACITY, BUFFER = -3, -4
 
 
 @pytest.mark.parametrize("V,N", [(1000, 100), (2000, 1), (5000, 1)])  # 10 and 2,000 segments; 5,000: the sorted form
@@ -18,3 +19,27 @@ def test_build_workspace_below_the_builders_needs(cagra, V, N, more):  # noqa: F
     s.build_workspace_bytes = 0
     n = (s.k + 1) * 4 + more
     assert cagra.lib().cagra_build_segments(ctypes.byref(g), ctypes.byref(s), 4096, n, None) == BUFFER
+
+
+MOST = 2 ** 32 // 1024 - 1
+
+
+@pytest.mark.parametrize("tiles,blocks", [(MOST + 1, 10), (1, MOST + 1)])
+def test_more_workgroups_than_a_launch(cagra, tiles, blocks):  # noqa: F811
+    L, r = cagra.lib(), ctypes.byref
+    g, s = _graph(cagra, V=blocks, E=50), _fake_built(cagra, V=blocks, N=blocks, B=1)
+    s.ntiles = tiles
+    gs, big = (r(g), r(s)), 1 << 40
+    assert L.cagra_pagerank_iter(*gs, 0.85, -1, 0, 1, 1, 1, 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_pagerank_merge(*gs, 0.85, -1, 0, 1, 1, 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_labelprop_iter(r(s), 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_degree_features(*gs, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_learned_start(*gs, 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_ppr_iter(*gs, 0.85, 1, 1, 1, 1, 1, 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    assert L.cagra_cf_iter(*gs, 1, 0.1, 0.1, 1, 1, 2, 1, 4096, big, None) == CAPACITY
+    if tiles > MOST:
+        assert L.cagra_segment_gather(r(s), 0, 0, 1, 1, None) == CAPACITY
+        assert L.cagra_bc_forward_level(r(s), 0, 1, 1, 1, 1, 1, 1, 4096, big, None) == CAPACITY
+    s.N, s.k, s.ntiles = 20000, -(-blocks // 20000), 1
+    s.max_items = max(MOST, s.nb)
+    assert L.cagra_labelprop_push_iter(r(s), 1, 1, 1, 1, 4096, big, None) == CAPACITY
