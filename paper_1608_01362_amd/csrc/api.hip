@@ -62,6 +62,7 @@ cagra_status launch_gather(const cagra_segments *seg, int32_t op, int32_t value_
                            void *partial, hipStream_t st);
 size_t merge_ordered_lds_bytes(int32_t B, int32_t op);
 size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes);
+size_t merge_pr_lds_total(int32_t B, int32_t k);
 cagra_status launch_merge(const cagra_segments *seg, int32_t op, const void *partial, void *out, hipStream_t st);
 int32_t init_blocks(int32_t V);
 cagra_status launch_pr_init(const cagra_graph *g, int32_t contrib_type, const float *rank, void *contrib_out,
@@ -392,7 +393,7 @@ static cagra_status check_pagerank_core(const cagra_graph *g, const cagra_segmen
     if (!(damping >= 0.0 && damping <= 1.0)) return fail(CAGRA_E_INVALID, "damping must be in [0, 1]");
     if (contrib_type != CAGRA_F32 && contrib_type != CAGRA_BF16)
         return fail(CAGRA_E_INVALID, "contrib_type must be CAGRA_F32 or CAGRA_BF16");
-    if (merge_fused_lds_total(seg->B, seg->k, 8) > CAGRA_LDS_BYTES)
+    if (merge_pr_lds_total(seg->B, seg->k) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "B=%d with k=%d exceeds the merge kernel's LDS", seg->B, seg->k);
     return check_launches(seg, seg->max_items);
 }

@@ -30,8 +30,10 @@ cagra_status launch_gather(const cagra_segments *seg, int32_t op, int32_t value_
 cagra_status launch_gather_clear(const cagra_segments *seg, int32_t op, int32_t value_type, const void *values,
                                  void *partial, unsigned long long *clear, hipStream_t st);
 
-// Dynamic LDS of the fused merges; kFusedStaticLds covers their static arrays.
+// Dynamic LDS of the fused merges, and all of it: kPrStaticLds are the static arrays
+// of the PageRank merges (merge_pr_block), kFusedStaticLds covers those of the others.
 constexpr size_t kFusedStaticLds = 256;
+constexpr size_t kPrStaticLds = 16 * sizeof(int32_t) + 4 * (kMergeThreads / 64) * sizeof(double);
 // At least what the last block's sums need (reduce4_rows).
 size_t merge_fused_lds_bytes(int32_t B, int32_t k, int acc_bytes) {
     const size_t n = align_up((size_t)B * acc_bytes, 16) + (size_t)(2 * (int64_t)k + 2) * sizeof(int32_t) + 64;
@@ -40,6 +42,7 @@ size_t merge_fused_lds_bytes(int32_t B, int32_t k, int acc_bytes) {
 size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes) {
     return merge_fused_lds_bytes(B, k, acc_bytes) + kFusedStaticLds;
 }
+size_t merge_pr_lds_total(int32_t B, int32_t k) { return merge_fused_lds_bytes(B, k, 8) + kPrStaticLds; }
 
 // ---------------------------------------------------------------- ordered (paper) merge
 
@@ -576,6 +579,7 @@ __device__ __forceinline__ void merge_pr_block(
     int32_t *pre = ofs + k;
     __shared__ int32_t tmp[16];
     __shared__ double red[4 * (kMergeThreads / 64)];
+    static_assert(sizeof(tmp) + sizeof(red) <= kPrStaticLds, "the LDS that the capacity check counts");
 
     const int64_t vb = (int64_t)b * B;
     const int32_t nv = (int32_t)((int64_t)V - vb < B ? (int64_t)V - vb : B);

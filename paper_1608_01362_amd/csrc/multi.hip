@@ -10,7 +10,7 @@
 namespace cagra {
 
 cagra_status fail(cagra_status st, const char *fmt, ...);
-size_t merge_fused_lds_total(int32_t B, int32_t k, int acc_bytes);
+size_t merge_pr_lds_total(int32_t B, int32_t k);
 size_t merge_fused_lds_bytes(int32_t B, int32_t k, int acc_bytes);
 cagra_status launch_multi_gather(const MultiDesc *desc, const int32_t *tile_graph, int64_t total_tiles, int parity,
                                  unsigned long long *tickets, int32_t ngraphs, int grid, hipStream_t st);
@@ -42,7 +42,7 @@ static cagra_status check_multi_member(const cagra_graph *g, const cagra_segment
     if ((size_t)s->N * 4 > CAGRA_STAGE_BYTES)
         return fail(CAGRA_E_CAPACITY, "graph %d: N=%d is not LDS-staged (multi-graph runs need N*4 <= %d)", i, s->N,
                     CAGRA_STAGE_BYTES);
-    if (merge_fused_lds_total(s->B, s->k, 8) > CAGRA_LDS_BYTES)
+    if (merge_pr_lds_total(s->B, s->k) > CAGRA_LDS_BYTES)
         return fail(CAGRA_E_CAPACITY, "graph %d: B=%d with k=%d exceeds the merge LDS", i, s->B, s->k);
     return CAGRA_OK;
 }

@@ -1,6 +1,6 @@
 """Limits that the host checks before any launch, without a GPU: a build workspace
 smaller than the builder takes, and more tiles or merge blocks than one launch
-of 2^32 threads holds."""
+of 2^32 threads holds, and LDS for the PageRank merge."""
 import ctypes
 
 import pytest
@@ -43,3 +43,16 @@ def test_more_workgroups_than_a_launch(cagra, tiles, blocks):  # noqa: F811
     s.N, s.k, s.ntiles = 20000, -(-blocks // 20000), 1
     s.max_items = max(MOST, s.nb)
     assert L.cagra_labelprop_push_iter(r(s), 1, 1, 1, 1, 4096, big, None) == CAPACITY
+
+
+@pytest.mark.parametrize("k,fits", [(4015, True), (4016, False), (4055, False), (4056, False)])
+def test_lds_of_the_pagerank_merge(cagra, k, fits):  # noqa: F811
+    """8 B of accumulators, 8 k + 8 + 64 of ranges, and 576 bytes of static arrays in 160 KB."""
+    assert (8 * 16384 + 8 * k + 72 + 576 <= 160 * 1024) == fits
+    L, r = cagra.lib(), ctypes.byref
+    g, s = _graph(cagra, V=8 * k, E=50), _fake_built(cagra, V=8 * k, N=8, B=16384)
+    # what fits is refused for its workspace, the next thing checked
+    want = BUFFER if fits else CAPACITY
+    assert L.cagra_pagerank_iter(r(g), r(s), 0.85, -1, 0, 1, 1, 1, 1, 1, 1, 1, 4096, 8, None) == want
+    m = cagra.CMulti()
+    assert (L.cagra_multi_query(1, r(g), r(s), r(m)) == CAPACITY) == (not fits)
