@@ -14,7 +14,7 @@
 
 namespace cagra {
 
-cagra_status ensure_dynamic_lds(const void *fn) {
+cagra_status ensure_dynamic_lds(const void *fn, bool no_static) {
     int dev = 0;
     const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(CAGRA_E_HIP, "hipGetDevice failed: %s", hipGetErrorString(e));
@@ -22,7 +22,7 @@ cagra_status ensure_dynamic_lds(const void *fn) {
     static std::set<std::pair<int, const void *>> done;  // (device, kernel) pairs already set
     std::lock_guard<std::mutex> lock(mu);
     if (done.count({dev, fn})) return CAGRA_OK;
-    const cagra_status s = allow_dynamic_lds(fn);
+    const cagra_status s = allow_dynamic_lds(fn, no_static);
     if (s == CAGRA_OK) done.insert({dev, fn});
     return s;
 }

@@ -49,10 +49,13 @@ struct ArenaSize {
 };
 
 // Lets `fn` use all LDS not taken by its static __shared__ arrays as dynamic LDS.
-static inline cagra_status allow_dynamic_lds(const void *fn) {
+static inline cagra_status allow_dynamic_lds(const void *fn, bool no_static) {
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, fn);
     if (e != hipSuccess) return fail(CAGRA_E_HIP, "hipFuncGetAttributes failed: %s", hipGetErrorString(e));
+    if (no_static && attr.sharedSizeBytes != 0)
+        return fail(CAGRA_E_INVALID, "internal: %zu bytes of static LDS where the dynamic LDS has to start at 0",
+                    (size_t)attr.sharedSizeBytes);
     int dyn = CAGRA_LDS_BYTES - (int)attr.sharedSizeBytes;
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
     if (e != hipSuccess) return fail(CAGRA_E_HIP, "hipFuncSetAttribute(%d) failed: %s", dyn, hipGetErrorString(e));
@@ -61,8 +64,9 @@ static inline cagra_status allow_dynamic_lds(const void *fn) {
 
 // allow_dynamic_lds for `fn` once per device (thread-safe; later calls on the
 // same device return at once). Every launch with more than 64 KB of dynamic
-// LDS goes through this.
-cagra_status ensure_dynamic_lds(const void *fn);
+// LDS goes through this. With no_static a kernel that has static LDS is refused:
+// for kernels that take their dynamic LDS to start at address 0.
+cagra_status ensure_dynamic_lds(const void *fn, bool no_static = false);
 
 // Per-graph descriptor of the persistent multi-graph kernels (device memory).
 struct MultiDesc {

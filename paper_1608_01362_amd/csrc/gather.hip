@@ -30,9 +30,9 @@ constexpr size_t kStageBytes = (size_t)kGatherWaves * kStageRows * 4;
 
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 
-// Staged value i. The kernels of this file have no static LDS, so their dynamic
-// LDS starts at address 0 and a value's address is a constant plus the word's
-// index bits: one instruction an edge less than an address from a pointer.
+// Staged value i. The kernels of this file have no static LDS (their launches check
+// that), so their dynamic LDS starts at address 0 and a value's address is a constant
+// plus the word's index bits: one instruction an edge less than an address from a pointer.
 template <typename VT>
 __device__ __forceinline__ VT staged(uint32_t i) {
     return *(const __attribute__((address_space(3))) VT *)(uint32_t)(kStageBytes + i * sizeof(VT));
@@ -468,7 +468,7 @@ static SplitPlan split_plan(int64_t n, int slots) {  // n: tiles, slots: workgro
 
 cagra_status launch_multi_gather(const MultiDesc *desc, const int32_t *tile_graph, int64_t total_tiles, int parity,
                                  unsigned long long *tickets, int32_t ngraphs, int grid, hipStream_t st) {
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_multi_gather)) return a_;
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)k_multi_gather, true)) return a_;
     if (total_tiles == 0) return CAGRA_OK;
     k_multi_gather<<<grid, kGatherThreads, kStageBytes + CAGRA_STAGE_BYTES, st>>>(
         desc, tile_graph, total_tiles, parity, tickets, ngraphs);
@@ -499,7 +499,7 @@ static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values,
                                  : k_gather<Op, VT, STAGED, W, kStagesDeep, true, false>;
         }
     }
-    if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
+    if (cagra_status a_ = ensure_dynamic_lds((const void *)kern, true)) return a_;
     kern<<<grid, kGatherThreads, lds, st>>>(static_cast<const W *>(seg->edge_src), seg->E, seg->Q, seg->tile_edge,
                                             seg->tile_seg, seg->tile_span_row, values, seg->V, seg->N, seg->ntiles,
                                             partial, seg_active, clear, plan);
