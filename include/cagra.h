@@ -199,7 +199,9 @@ cagra_status cagra_segment_edge_values(const cagra_graph *g, const cagra_segment
                                        float *seg_values, hipStream_t stream);
 
 /* Device workspace of cagra_cf_iter (one FP64 value per workgroup of the gather:
-   per tile, or per part of a tile where few tiles are split). */
+   per tile, or per part of a tile where few tiles are split). Depends on the sizes
+   in seg alone. cagra_cf_iter also takes one value per tile plus 256 bytes, with the
+   same results. */
 size_t cagra_cf_workspace_bytes(const cagra_segments *seg);
 
 /*

@@ -54,7 +54,7 @@ cagra_status launch_edge_values(const cagra_graph *g, const cagra_segments *seg,
                                  float *seg_values, hipStream_t st);
 cagra_status launch_cf_iter(const cagra_segments *seg, const float *seg_values, double gamma, double lambda,
                             const float *x_in, float *partial, float *x_out, double *sq_out, double *tile_sq,
-                            int32_t parts, hipStream_t st);
+                            hipStream_t st);
 int32_t cf_parts(const cagra_segments *seg);
 cagra_status cluster_graph(const cagra_graph *g, int32_t *perm, int32_t *in_offsets_new, int32_t *in_sources_new,
                            int32_t *outdeg_new, int32_t *hot, void *ws, size_t ws_bytes, hipStream_t st);
@@ -238,12 +238,11 @@ cagra_status cagra_cf_iter(const cagra_graph *g, const cagra_segments *seg, cons
         return fail(CAGRA_E_INVALID, "a vector argument is NULL");
     if ((const void *)x_in == (const void *)x_out) return fail(CAGRA_E_INVALID, "x_in and x_out must not alias");
     if (!(gamma >= 0.0) || !(lambda >= 0.0)) return fail(CAGRA_E_INVALID, "gamma and lambda must be >= 0");
-    // a value per tile is enough, without the tiles split
+    // a value per tile is enough: where it is less than was asked for, launch_cf_iter does without
     if (!workspace || workspace_bytes < cf_bytes(seg, 1))
         return fail(CAGRA_E_BUFFER, "workspace needs %zu bytes (got %zu)", cf_bytes(seg, 1), workspace_bytes);
-    const int32_t parts = workspace_bytes < cagra_cf_workspace_bytes(seg) ? 1 : cf_parts(seg);
-    return launch_cf_iter(seg, seg_values, gamma, lambda, x_in, partial, x_out, sq_out, (double *)workspace, parts,
-                          stream);
+    double *tile_sq = workspace_bytes < cagra_cf_workspace_bytes(seg) ? nullptr : (double *)workspace;
+    return launch_cf_iter(seg, seg_values, gamma, lambda, x_in, partial, x_out, sq_out, tile_sq, stream);
 }
 
 size_t cagra_bc_workspace_bytes(const cagra_segments *seg) {

@@ -318,20 +318,26 @@ size_t cf_merge_lds_bytes(int32_t B) { return (size_t)B * kCfK * sizeof(float); 
 // edges. A step, whole tiles and split, us: 886 K edges, 14 / 55 tiles 304 and 40 / 100
 // and 52; 5 M, 78 tiles 310 and 184. The squared errors are FP32 sums within windows of
 // four edges, and the windows move with the parts: the total moves by 4e-9 of itself at
-// 2,700 edges, 5e-10 at 160 K, 1e-10 at 886 K. Below 2^18 edges it would not keep 1e-9
-// safely, and a step keeps its tiles.
+// 2,700 edges, 5e-10 at 160 K, 1e-10 at 886 K. Below 2^18 edges a step therefore keeps
+// its tiles whole, and its total keeps its error. Depends on the sizes alone, so the
+// workspace can be asked for before the arrays exist. (Eight vertices: see launch_cf_iter.)
 int32_t cf_parts(const cagra_segments *seg) {
     int32_t parts = 1;
-    while (seg->row_ptr && seg->E >= 1 << 18 && parts < kCfWaves && (int64_t)seg->ntiles * parts * 2 <= 256 &&
+    while (seg->V >= 8 && seg->E >= 1 << 18 && parts < kCfWaves && (int64_t)seg->ntiles * parts * 2 <= 256 &&
            seg->E >= (int64_t)256 * 2 * parts * seg->ntiles)
         parts *= 2;
     return parts;
 }
 
-// parts: 1 or cf_parts(seg); tile_sq holds seg->ntiles * parts values
+// tile_sq holds seg->ntiles * cf_parts(seg) values, or is null: split tiles then leave
+// theirs (256 at most, the size of eight rows) in x_out, which the merge writes after
+// the sum has read them. So neither the results nor the time depend on the workspace.
 cagra_status launch_cf_iter(const cagra_segments *seg, const float *seg_values, double gamma, double lambda,
                             const float *x_in, float *partial, float *x_out, double *sq_out, double *tile_sq,
-                            int32_t parts, hipStream_t st) {
+                            hipStream_t st) {
+    const int32_t parts = cf_parts(seg);
+    static_assert(256 * sizeof(double) <= 8 * kCfK * sizeof(float), "tile sums in eight rows");
+    if (!tile_sq) tile_sq = reinterpret_cast<double *>(x_out);
     if (seg->ntiles > 0) {
         auto launch = [&](auto kern, auto *edges) {
             kern<<<seg->ntiles * parts, kCfThreads, 0, st>>>(edges, seg_values, seg->tile_edge, seg->tile_seg,
@@ -344,12 +350,12 @@ cagra_status launch_cf_iter(const cagra_segments *seg, const float *seg_values, 
         else launch(parts > 1 ? k_cf_gather<uint32_t, true> : k_cf_gather<uint32_t, false>, e32);
         CAGRA_LAUNCH_CHECK();
     }
+    k_sum_tiles<<<1, 256, 0, st>>>(tile_sq, seg->ntiles * parts, sq_out);
+    CAGRA_LAUNCH_CHECK();
     if (cagra_status a_ = ensure_dynamic_lds((const void *)k_merge_cf)) return a_;
     k_merge_cf<<<seg->nb, kCfThreads, cf_merge_lds_bytes(seg->B), st>>>(
         seg->row_dst, seg->block_ptr, partial, seg->V, seg->k, seg->B, seg->nb, (float)gamma, (float)lambda, x_in,
         x_out);
-    CAGRA_LAUNCH_CHECK();
-    k_sum_tiles<<<1, 256, 0, st>>>(tile_sq, seg->ntiles * parts, sq_out);
     CAGRA_LAUNCH_CHECK();
     return CAGRA_OK;
 }

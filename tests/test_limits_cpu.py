@@ -1,6 +1,7 @@
 """Limits that the host checks before any launch, without a GPU: a build workspace
 smaller than the builder takes, and more tiles or merge blocks than one launch
-of 2^32 threads holds, and LDS for the PageRank merge."""
+of 2^32 threads holds, LDS for the PageRank merge, and the workspace of a rating
+step asked for before the arrays exist."""
 import ctypes
 
 import pytest
@@ -56,3 +57,13 @@ def test_lds_of_the_pagerank_merge(cagra, k, fits):  # noqa: F811
     assert L.cagra_pagerank_iter(r(g), r(s), 0.85, -1, 0, 1, 1, 1, 1, 1, 1, 1, 4096, 8, None) == want
     m = cagra.CMulti()
     assert (L.cagra_multi_query(1, r(g), r(s), r(m)) == CAPACITY) == (not fits)
+
+
+def test_rating_workspace_before_the_arrays(cagra):  # noqa: F811
+    """The size that the query call's struct gives is the one that the step uses."""
+    L, r = cagra.lib(), ctypes.byref
+    s = _fake_built(cagra, V=10_000, N=5_000, B=128, E=1 << 20, Q=10_000)
+    full = L.cagra_cf_workspace_bytes(r(s))
+    assert full > 8 * s.ntiles + 256
+    s.row_ptr = None
+    assert L.cagra_cf_workspace_bytes(r(s)) == full
