@@ -50,9 +50,10 @@ constexpr int kBcMaskWords = kBcMaxSpan / 32 + 2; // segments of a span, in 32-b
 
 // A thread takes kBcBatch vertices of the span per round and loads all they may
 // need before it looks at any (also sigma and delta of vertices outside the
-// frontier, which are bytes, not round trips).
+// frontier, which are bytes, not round trips). The last round of a span may be a
+// part of one (2.5 M vertices: spans of 5,120).
 constexpr int kBcBatch = 4;
-static_assert(kBcMinSpan % (kBcBatch * kBcSpanThreads) == 0, "a span is whole rounds");
+static_assert(kBcMinSpan % (kBcBatch * kBcSpanThreads) == 0, "the shortest span is whole rounds");
 
 struct SpanMask {
     int32_t v0, v1;     // the workgroup's vertices [v0, v1)
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kBcThreads) void k_bc_bwd_update(int32_t V, int32_t
     if (v != source) bc[v] += dl;
 }
 
-// Vertices per workgroup: whole rounds of the workgroup's threads.
+// Vertices per workgroup: a multiple of its threads.
 static int32_t span_for(int32_t V) {
     const int64_t s = ceil_div(ceil_div(V, kBcWorkgroups), kBcSpanThreads) * kBcSpanThreads;
     return (int32_t)(s < kBcMinSpan ? kBcMinSpan : (s > kBcMaxSpan ? kBcMaxSpan : s));
