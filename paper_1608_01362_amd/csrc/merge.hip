@@ -66,6 +66,7 @@ constexpr int kOrdDepth = 8;       // pieces of ranges in flight
 constexpr int kOrdWindow = 2048;   // subgraphs whose ranges are listed at a time
 constexpr int kOrdParts = 8;       // parts of a heavy block
 constexpr int kOrdHeavyWaves = 16;
+constexpr int kChipWaves = 256 * 32;  // resident at once
 
 template <class Op, bool COMP>
 __device__ __forceinline__ void ord_apply(typename Op::T *acc, typename Op::T *cmp, int32_t d,
@@ -229,13 +230,11 @@ static size_t ordered_lds(int32_t B, int32_t k, bool comp, bool heavy) {
 }
 
 template <class Op, bool COMP, int W, bool HEAVY>
-static cagra_status launch_ordered_w(const cagra_segments *seg, const void *partial, void *out,
+static cagra_status launch_ordered_w(const cagra_segments *seg, const int32_t *items, const void *partial, void *out,
                                      const uint32_t *seg_active, hipStream_t st) {
     using T = typename Op::T;
     auto kern = k_merge_ordered<Op, COMP, W, HEAVY>;
     if (cagra_status a_ = ensure_dynamic_lds((const void *)kern)) return a_;
-    // no block is split when the item bound equals nb: the item table is not read then
-    const int32_t *items = seg->max_items > seg->nb ? seg->block_items : nullptr;
     // a launch has fewer than 2^32 threads: with small blocks of many vertices it takes several
     constexpr int32_t parts = HEAVY ? kOrdParts : 1, most = (int32_t)(UINT32_MAX / (W * kWave * parts));
     for (int32_t b0 = 0; b0 < seg->nb; b0 += most) {
@@ -259,18 +258,47 @@ static int ordered_waves(const cagra_segments *seg) {
     return mean <= 60.0 ? 2 : mean <= 160.0 ? 4 : mean <= 384.0 ? 8 : 16;
 }
 
+// An upper bound of the mean range length of a split block: the work items beyond nb are
+// those of the split blocks, an item has at most four times the mean entries of a block,
+// and a range has at most B entries.
+static double split_block_range(const cagra_segments *seg) {
+    const double item = 4.0 * (double)ceil_div(seg->Q, seg->nb);
+    const double most = item * ((double)seg->max_items - seg->nb + 1.0);
+    const double range = (most < (double)seg->Q ? most : (double)seg->Q) / seg->k;
+    return range < seg->B ? range : (double)seg->B;
+}
+
+// Split blocks get a launch of their own where their ranges take a workgroup more than two
+// steps: that launch is a chain over the subgraphs behind the first one's, which shorter
+// ranges do not get back. Up to eight waves are taken to make them short enough, as long
+// as all blocks stay resident at once; beyond that a split block's longer chain hides
+// behind the other blocks, and four steps are better still. FP32 sum, us, one wave per
+// block / always two launches / with this rule: 9 K vertices, one row in 9 ranges 8.8 /
+// 12.4 / 9.5; 500 K vertices, a block of 50 long rows over 489 segments 179 / 208 / 94;
+// clustered R-MAT 20 in blocks of 1,024 958 / 594 / 313, clustered R-MAT 21 in blocks of
+// 8,192 / 512 1,967 / 62 / 62 and 103 / 158 / 46.
 template <class Op, bool COMP>
 static cagra_status launch_ordered(const cagra_segments *seg, const void *partial, void *out,
                                    const uint32_t *seg_active, hipStream_t st) {
     cagra_status s;
-    switch (ordered_waves(seg)) {
-        case 2: s = launch_ordered_w<Op, COMP, 2, false>(seg, partial, out, seg_active, st); break;
-        case 4: s = launch_ordered_w<Op, COMP, 4, false>(seg, partial, out, seg_active, st); break;
-        case 8: s = launch_ordered_w<Op, COMP, 8, false>(seg, partial, out, seg_active, st); break;
-        default: s = launch_ordered_w<Op, COMP, 16, false>(seg, partial, out, seg_active, st);
+    int waves = ordered_waves(seg);
+    const int32_t *items = nullptr;  // not read where every block is merged whole
+    if (seg->max_items > seg->nb) {
+        const double range = split_block_range(seg);
+        auto resident = [&](int w) { return (int64_t)seg->nb * w <= kChipWaves; };
+        int w = waves;
+        while (2 * w * kWave < range && w < 8 && resident(2 * w)) w *= 2;
+        if ((resident(2 * w) ? 2 : 4) * w * kWave < range) items = seg->block_items;
+        else waves = w;
     }
-    if (s != CAGRA_OK || seg->max_items == seg->nb) return s;
-    return launch_ordered_w<Op, COMP, kOrdHeavyWaves, true>(seg, partial, out, seg_active, st);
+    switch (waves) {
+        case 2: s = launch_ordered_w<Op, COMP, 2, false>(seg, items, partial, out, seg_active, st); break;
+        case 4: s = launch_ordered_w<Op, COMP, 4, false>(seg, items, partial, out, seg_active, st); break;
+        case 8: s = launch_ordered_w<Op, COMP, 8, false>(seg, items, partial, out, seg_active, st); break;
+        default: s = launch_ordered_w<Op, COMP, 16, false>(seg, items, partial, out, seg_active, st);
+    }
+    if (s != CAGRA_OK || !items) return s;
+    return launch_ordered_w<Op, COMP, kOrdHeavyWaves, true>(seg, items, partial, out, seg_active, st);
 }
 
 size_t merge_ordered_lds_bytes(int32_t B, int32_t op) {
