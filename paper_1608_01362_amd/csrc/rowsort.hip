@@ -26,9 +26,12 @@
 // or seven passes of the edge-key sort it replaces. Clustering R-MAT 24 / ef 24:
 // 20.5 -> 9.2 ms (light tiles 5.4, pieces 1.9, merges 0.4), R-MAT 25 / ef 32
 // 59.5 -> 25.3 ms. What bounds it is the lookup of the new ids: one random
-// 4-byte read per edge through L2 and the Infinity Cache, about 65 G/s. Rows of
-// neighbouring ids (a band of width 300) take 2.1 against 2.0 ms, a star of 3 M
-// edges 0.53 against 0.40 ms (nine merge levels).
+// 4-byte read per edge through L2 and the Infinity Cache, about 65 G/s. Rows of 300
+// neighbouring ids (60 M edges) take 1.67 against 1.81 ms, a star of 3 M edges 0.30
+// against 0.32 ms (nine merge levels of runs in order). Dearer than the edge-key sort
+// are rows of 10^5 and more sources in no order with little beside them: each merge
+// level is a chain of some 20 us (five rows of 600,000 edges: 0.52 against 0.32 ms,
+// fifty of 80,000: 0.38 against 0.35).
 #include "rowsort.h"
 
 #include <type_traits>
@@ -445,8 +448,9 @@ __device__ __forceinline__ void load_table(SortLds<ITEMS> &L, const uint32_t *__
     for (int i = threadIdx.x; i <= kCells; i += kRsThreads) L.tab[i] = tab[i];
 }
 
-// One tile per workgroup; the crowded ones are listed for k_rs_light_crowded,
-// whose further passes need twice the registers, and the lengthy ones, whose last
+// One tile per workgroup; the crowded ones are listed for k_rs_light_crowded, whose
+// further passes need more registers (two workgroups per CU; at one, a graph of 60 M
+// edges between neighbours took 2.11 ms, 1.67 now), and the lengthy ones, whose last
 // rows run far past kRsTile, for k_rs_light_lengthy.
 __global__ __launch_bounds__(kRsThreads, 6) void k_rs_light(
     const int32_t *__restrict__ in_offsets, const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
@@ -482,7 +486,7 @@ __global__ __launch_bounds__(kRsThreads, 4) void k_rs_light_lengthy(
     }
 }
 
-__global__ __launch_bounds__(kRsThreads, 2) void k_rs_light_crowded(
+__global__ __launch_bounds__(kRsThreads, 4) void k_rs_light_crowded(
     const int32_t *__restrict__ in_offsets, const int32_t *__restrict__ in_sources, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ inv, RowList list, int64_t E, const uint32_t *__restrict__ tab,
     const HeavyCount *__restrict__ hc, const int32_t *__restrict__ crowded,
@@ -518,7 +522,38 @@ __device__ __forceinline__ bool sort_piece(SortLds<kRsItems> &L, const int32_t *
 #pragma unroll
     for (int j = 0; j < kRsItems; ++j) key[j] = (uint32_t)inv[key[j]];
 #pragma unroll
-    for (int j = 0; j < kRsItems; ++j) slot[j] = __umulhi((uint32_t)n, fraction(L.tab, key[j]));
+    for (int j = 0; j < kRsItems; ++j) {
+        const uint32_t f = fraction(L.tab, key[j]);
+        slot[j] = ANY ? f >> 1 : __umulhi((uint32_t)n, f);
+    }
+    if constexpr (ANY) {
+        // the piece's own span of G over its places: most crowded pieces hold neighbouring
+        // ids (a row's edges come in the old order, which most vertices keep)
+        int32_t least = 0x7fffffff, most = 0;
+#pragma unroll
+        for (int j = 0; j < kRsItems; ++j) {  // items past the piece hold its first edge again
+            least = min(least, (int32_t)slot[j]);
+            most = max(most, (int32_t)slot[j]);
+        }
+        least = __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - least), 63);
+        most = __builtin_amdgcn_readlane(wave_incl_max(most), 63);
+        if ((tid & 63) == 0) {
+            L.wsum[tid >> 6] = (uint32_t)least;
+            L.before[tid >> 6] = most;
+        }
+        __syncthreads();
+        for (int x = 0; x < kRsThreads / kWave; ++x) {
+            least = max(least, (int32_t)L.wsum[x]);
+            most = max(most, L.before[x]);
+        }
+        least = 0x7fffffff - least;
+        const float scale = (float)n / ((float)(most - least) + 1.0f);
+#pragma unroll
+        for (int j = 0; j < kRsItems; ++j) {  // rounding keeps the order
+            const uint32_t at = (uint32_t)((float)((int32_t)slot[j] - least) * scale);
+            slot[j] = min(at, (uint32_t)(n - 1));
+        }
+    }
     int32_t *to = merge_levels(len) & 1 ? tmp : out;
     return sort_tile<ANY>(L, key, slot, n, to + (int64_t)noff[row] + p0);
 }
@@ -614,6 +649,10 @@ __global__ __launch_bounds__(kMgThreads) void k_rs_merge(const int32_t *__restri
         const bool from_tmp = (levels - level) & 1;
         const int32_t *A = (from_tmp ? tmp : out) + (int64_t)noff[row] + p0, *B = A + na;
         int32_t *to = (from_tmp ? out : tmp) + (int64_t)noff[row] + o0;
+        if (nb == 0 || A[na - 1] <= B[0]) {  // uniform: in order already, as pieces of neighbouring ids are
+            for (int i = tid; i < n; i += kMgThreads) to[i] = A[d0 + i];
+            continue;
+        }
         if (w < 2) {
             const int32_t a = merge_split(A, na, B, nb, w == 0 ? d0 : d1);
             if ((tid & 63) == 0) split[w] = a;
@@ -707,7 +746,7 @@ cagra_status sort_rows(const int32_t *in_offsets, const int32_t *in_sources, int
     k_rs_light_lengthy<<<(unsigned)(tiles < 2048 ? tiles : 2048), kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
         in_offsets, in_sources, perm, inv, list, E, w.tab, w.hc, w.crowded, w.lengthy, out);
     CAGRA_LAUNCH_CHECK();
-    k_rs_light_crowded<<<(unsigned)(tiles < 256 ? tiles : 256), kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
+    k_rs_light_crowded<<<(unsigned)(tiles < 512 ? tiles : 512), kRsThreads, sizeof(SortLds<kRsItems>), st>>>(
         in_offsets, in_sources, perm, inv, list, E, w.tab, w.hc, w.crowded, out);
     CAGRA_LAUNCH_CHECK();
     if (E <= kLightMax) return CAGRA_OK;  // no heavy row
