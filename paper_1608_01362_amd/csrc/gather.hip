@@ -256,6 +256,10 @@ constexpr int32_t kDeepTileEdges = 131072;  // tiles at least this long take kSt
 // Tiles at least this long read a chunk's source values ahead, store through a
 // descriptor per chunk (both below), and may be cut into parts (split_plan).
 constexpr int64_t kLongTileEdges = 49152;
+// ... unless the mean tile is shorter than this, one per small segment. Plain and long
+// form, us: 1,563 tiles of 64 edges 17.6 and 20.0, 49 of 2,040 5.1 and 5.9, with eight
+// stages 1,954 of 511 16.8 and 25.4; but 4,096 of 3,927 45.2 and 43.8.
+constexpr int64_t kShortTileEdges = 3072;
 constexpr int kXcds = 8, kXcdCus = 32;
 
 // Tile t; with SPLIT, part `part` of nparts (1, 2, 4, 8 or 16) of its spans.
@@ -456,7 +460,12 @@ __global__ __launch_bounds__(kGatherThreads) void k_multi_gather(const MultiDesc
 // tiles are cut into as many parts as there are CUs for. R-MAT, 262,144-edge
 // tiles: 2 to 17 tiles 36-38 -> 24-27 us, 70 tiles 42 -> 34, 294 tiles 90 -> 79;
 // 65,536-edge tiles: 8 to 65 tiles 12.8-13.8 -> 10-12. Tiles of 32,768 edges lose
-// (9.6 -> 10.6 us), as does one more round after many (4,442 tiles: 0.3%).
+// (9.6 -> 10.6 us), as does one more round after many (4,442 tiles: 0.3%). Where all
+// tiles are that short below a longer nominal length, which is not known here, the
+// workgroups that find nothing to do cost up to 1 us (four tiles of 25,000 edges 10.7 ->
+// 11.8, 31 of 32,000 13.4 -> 14.3); a bound on the mean length instead would cost graphs
+// with a few long tiles among short ones more (clustered R-MAT 16, segments of 1,024:
+// 10.9 -> 12.4 and, tiles of 262,144, 26.7 -> 34.4).
 constexpr int kSplitRounds = 4;         // after more whole rounds the last one is too
 static SplitPlan split_plan(int64_t n, int slots) {  // n: tiles, slots: workgroups at a time, per XCD
     const int64_t left = n % slots;
@@ -485,7 +494,7 @@ static cagra_status launch_gather_w(const cagra_segments *seg, const VT *values,
     SplitPlan plan = {seg->ntiles, 1};
     int grid = seg->ntiles;
     if constexpr (STAGED) {
-        if (seg->tile_edges >= kLongTileEdges) {
+        if (seg->tile_edges >= kLongTileEdges && seg->E >= kShortTileEdges * seg->ntiles) {
             const bool deep = sizeof(W) == 2 && seg->tile_edges >= kDeepTileEdges;
             const int64_t n = ceil_div(seg->ntiles, kXcds);
             plan = split_plan(n, kXcdCus * (!deep && 2 * lds <= CAGRA_LDS_BYTES ? 2 : 1));
