@@ -40,7 +40,8 @@ typedef enum {
     CAGRA_OK = 0,
     CAGRA_E_INVALID = -1,   /* null pointer, bad size, unknown enum value */
     CAGRA_E_OVERFLOW = -2,  /* a count would not fit in int32 */
-    CAGRA_E_CAPACITY = -3,  /* parameter beyond a kernel capacity (LDS bytes, segment count) */
+    CAGRA_E_CAPACITY = -3,  /* parameter beyond a kernel capacity (LDS bytes, segment count,
+                               2^22 or more tiles or merge blocks in an iteration) */
     CAGRA_E_BUFFER = -4,    /* workspace too small or misaligned */
     CAGRA_E_HIP = -5,       /* a HIP runtime call or kernel launch failed */
     CAGRA_E_NOT_CONVERGED = -6, /* an iteration cap was reached before the stopping rule held */
@@ -167,7 +168,7 @@ int32_t cagra_edge_word_bytes(int32_t N);
  * order is stable (equal out-degrees keep their original order), and every
  * other vertex follows in its original order. The graph is relabelled: old
  * vertex perm[i] becomes vertex i, and each in-edge row lists its sources
- * ascending under the new ids. PageRank on the result, read through perm,
+ * ascending under the new ids (a repeated edge stays repeated). PageRank on the result, read through perm,
  * equals PageRank on the input.
  *
  *   g           input graph (device arrays; out_degree required)
@@ -627,8 +628,8 @@ cagra_status cagra_ppr_solve(const cagra_graph *g, const cagra_segments *seg, co
  * Plan for running PageRank on many graphs at once. Every graph keeps its own
  * segments (built with cagra_build_segments, N * 4 <= CAGRA_STAGE_BYTES); the
  * vectors of all graphs live in shared pools, graph i's at the running offset
- * of the earlier graphs' V (rank, contrib) and Q (partial). Persistent
- * workgroups stride over the global tile and merge-block lists, so each
+ * of the earlier graphs' V (rank, contrib) and Q (partial). One
+ * workgroup takes each entry of the global tile and merge-block lists, so an
  * iteration of all graphs is two kernel launches without host
  * synchronization (capturable into one HIP graph).
  */

@@ -270,7 +270,7 @@ MULTI_DEFAULT = (32768, 8192, 65536)
 
 
 def multi_candidates():
-    """(N, B, T) per size class: LDS-staged segments (the persistent kernels use
+    """(N, B, T) per size class: LDS-staged segments (the multi-graph kernels use
     16-bit edge words, N <= 32,768), merge blocks of 4 K and 8 K vertices, tiles
     of 16 K and 64 K edges. N is capped at the graph's V when used."""
     return [(N, B, T) for N in (8192, 16384, 32768) for B in (4096, 8192) for T in (16384, 65536)]
@@ -300,7 +300,7 @@ def _time_multi(dgs, segs, iters: int = 20, reps: int = 2) -> float:
 
 def tune_multi(dgs, cache_path: str | None = CACHE_DEFAULT, tag: str = "", log=None):
     """Per size class (size_class), the (N, B, T) of the graphs of that class in
-    the persistent multi-graph launch: one pass of coordinate descent over the
+    the multi-graph launch: one pass of coordinate descent over the
     classes present (largest first), each class's candidates timed on the whole
     launch (start + 20 iterations of every graph) with the other classes held
     at their current choice. Returns ({class: (N, B, T)}, [(class, N, B, T, ms)])."""

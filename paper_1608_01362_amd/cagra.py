@@ -776,7 +776,7 @@ def ppr(dg: DeviceGraph, seg: Segments, seeds, iters: int = 20, damping: float =
 # --------------------------------------------------------------------------- many graphs at once
 
 class MultiPageRank:
-    """PageRank on many independent graphs with persistent kernels over a global
+    """PageRank on many independent graphs, one launch per kernel over a global
     tile / merge-block list; `run` captures the whole run into one HIP graph."""
 
     def __init__(self, dgs, segs):

@@ -68,7 +68,7 @@ static inline cagra_status allow_dynamic_lds(const void *fn, bool no_static) {
 // for kernels that take their dynamic LDS to start at address 0.
 cagra_status ensure_dynamic_lds(const void *fn, bool no_static = false);
 
-// Per-graph descriptor of the persistent multi-graph kernels (device memory).
+// Per-graph descriptor of the multi-graph kernels (device memory).
 struct MultiDesc {
     const void *edge_src;  // 16-bit edge words (multi-graph runs use N <= CAGRA_EDGE16_MAX_N)
     const int32_t *tile_edge;

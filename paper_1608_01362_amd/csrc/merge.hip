@@ -57,9 +57,9 @@ size_t merge_pr_lds_total(int32_t B, int32_t k) { return merge_fused_lds_bytes(B
 // so W follows the mean range length (see ordered_waves). Blocks of high
 // in-degree destinations (after clustering the first few hold 30 times the mean
 // entries, and one workgroup per block left the chip waiting for the heaviest)
-// are cut by destination into kOrdParts parts, each a workgroup of its own with
-// its piece of every range found by binary search; the order per destination
-// stays the same. One wave per block before -> now, us, FP32 sum: R-MAT 21 / ef
+// are cut by destination into kOrdParts parts where their ranges are long (the
+// rule is at launch_ordered), each a workgroup of its own with its piece of
+// every range found by binary search; the order per destination stays the same. One wave per block before -> now, us, FP32 sum: R-MAT 21 / ef
 // 16 165 -> 23, R-MAT 25 / ef 32 1,698 -> 1,457 (compensated 3,722 -> 2,200),
 // the same graphs clustered 1,977 -> 57 and 41,000 -> 2,970.
 constexpr int kOrdDepth = 8;       // pieces of ranges in flight
@@ -792,7 +792,8 @@ cagra_status launch_merge_sum_fixed24(const cagra_segments *seg, const float *pa
     return CAGRA_OK;
 }
 
-// Persistent form over many graphs: workgroups stride over a global block list.
+// Many graphs: one workgroup per entry of the global block list (they stride past
+// the largest grid).
 __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_multi_merge(
     const MultiDesc *__restrict__ desc, const int32_t *__restrict__ block_graph, int64_t total_blocks, int parity,
     double damping, double *__restrict__ blk, unsigned long long *__restrict__ tickets) {
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(8
     }
 }
 
-// Uniform start vectors of many graphs (persistent over the block list).
+// Uniform start vectors of many graphs, over the block list as above.
 __global__ __launch_bounds__(256) void k_multi_start(const MultiDesc *__restrict__ desc,
                                                      const int32_t *__restrict__ block_graph, int64_t total_blocks,
                                                      double *__restrict__ blk) {

@@ -1,8 +1,8 @@
 // Many independent graphs in one launch per kernel: per-graph descriptors in
-// device memory, global tile and merge-block lists, and persistent workgroups
-// striding over them. A PageRank iteration of every graph is two kernel
-// launches with no host synchronization, so a whole run can be captured into
-// one HIP graph.
+// device memory and global tile and merge-block lists, one workgroup per tile
+// and per block. A PageRank iteration of every graph is two kernel launches
+// with no host synchronization, so a whole run can be captured into one HIP
+// graph.
 #include <vector>
 
 #include "common.h"
@@ -134,7 +134,7 @@ cagra_status cagra_multi_setup(cagra_multi *m, const cagra_graph *graphs, const 
     CAGRA_HIP_CHECK(hipMemcpyAsync(m->desc, host.data(), m->desc_bytes, hipMemcpyHostToDevice, stream));
     CAGRA_HIP_CHECK(hipStreamSynchronize(stream));  // the host staging copy goes out of scope
     // a workgroup per tile and per block, dispatched as the earlier ones end;
-    // past the bound they stride
+    // past kMaxGrid they stride over the list
     m->grid_gather = (int32_t)(m->total_tiles < 1 ? 1 : m->total_tiles < kMaxGrid ? m->total_tiles : kMaxGrid);
     m->grid_merge = (int32_t)(m->total_blocks < kMaxGrid ? m->total_blocks : kMaxGrid);
     return CAGRA_OK;
