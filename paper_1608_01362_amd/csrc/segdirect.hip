@@ -20,12 +20,13 @@
 // Bytes: 4 E (count) + 4 E + 2 E + 10 Q (scatter), against some 45 E + 40 Q of
 // the sorted form it replaces (row marks, flags, two scans over the edges, keys
 // and values through two digit passes). Query and build together, before ->
-// now: R-MAT 24 / ef 24 (N = 32,768) 13.0 -> 4.4 ms, R-MAT 25 / ef 32 35.3 ->
-// 14.6 ms. The scatter (2.5 ms of the 4.4) is bound by its ranking: 149 VALU
+// now: R-MAT 24 / ef 24 (N = 32,768) 13.2 -> 4.7 ms, R-MAT 25 / ef 32 35.3 ->
+// 15.9 ms. The scatter (2.5 ms of the 4.7) is bound by its ranking: 149 VALU
 // instructions per 64 edges, 1.4 ms of issue, and the barriers between its
-// phases. Tiles of 4,096 edges (more, smaller workgroups) took 4.8 and 17.8 ms,
-// chunks of one or two tiles 4.5 and 15 ms, the segment match with a bit loop
-// or waits between the steps 4.7 to 5.0 ms.
+// phases. Timed when it took 4.4 and 14.6 ms: tiles of 4,096 edges (more,
+// smaller workgroups) 4.8 and 17.8 ms, chunks of one or two tiles 4.5 and
+// 15 ms, the segment match with a bit loop or waits between the steps 4.7 to
+// 5.0 ms.
 #include "segdirect.h"
 
 #include "radix.h"
